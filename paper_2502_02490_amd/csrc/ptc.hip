@@ -9,8 +9,8 @@
 //   backward:  input gradient = the same layer kernel with weights W'[q][c'][c] = W[adj q][c][c']^dag
 //              (spin matrices commute with the transports, and T_p^dag = T_{adj p});
 //              weight gradient dL/dW*[p,c,c'] = sum_{x, colour} g_c(x) (T_p x_{c'})(x)^dag, a
-//              contraction over the sites done per 64-site tile in LDS, then reduced over tiles
-//              in index order (deterministic);
+//              contraction over the sites on the matrix cores, reduced over tiles in index order
+//              (deterministic);
 //   Adam on (Re W, Im W) with FP32 state.
 #include <cmath>
 #include <vector>
@@ -23,7 +23,7 @@ namespace dl {
 namespace {
 
 constexpr int kPaths = 9;
-constexpr int kTile = 64;  // sites per work-group of the weight-gradient kernel
+constexpr int kTile = 64;  // sites per tile of the weight-gradient kernel
 
 struct PtcGeom {
     Geom g;
@@ -160,24 +160,30 @@ DEV void transport_compute(const TRaw<A> &r, int path, C<float> t[12]) {
     C<float> f[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) f[k] = mk(lf[2 * k], lf[2 * k + 1]);
-    const bool back = ((path - 1) & 1) != 0;
+    C<float> ps[12];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        C<float> ps[3];
+    for (int k = 0; k < 12; ++k) ps[k] = mk(sp[2 * k], sp[2 * k + 1]);
+    // one branch for the whole spinor (it is uniform where the path is)
+    if (((path - 1) & 1) != 0) {
 #pragma unroll
-        for (int b = 0; b < 3; ++b) ps[b] = mk(sp[6 * s + 2 * b], sp[6 * s + 2 * b + 1]);
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            C<float> acc = mk(0.f, 0.f);
-            if (back) {
+            for (int a = 0; a < 3; ++a) {
+                C<float> acc = mk(0.f, 0.f);
 #pragma unroll
-                for (int b = 0; b < 3; ++b) cmadd(acc, f[3 * b + a], ps[b]);  // conj(F_ba) psi_b
-            } else {
-#pragma unroll
-                for (int b = 0; b < 3; ++b) madd(acc, f[3 * a + b], ps[b]);
+                for (int b = 0; b < 3; ++b) cmadd(acc, f[3 * b + a], ps[3 * s + b]);  // conj(F_ba) psi_b
+                t[3 * s + a] = acc;
             }
-            t[3 * s + a] = acc;
-        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                C<float> acc = mk(0.f, 0.f);
+#pragma unroll
+                for (int b = 0; b < 3; ++b) madd(acc, f[3 * a + b], ps[3 * s + b]);
+                t[3 * s + a] = acc;
+            }
     }
 }
 
@@ -450,148 +456,351 @@ __global__ __launch_bounds__(256) void k_ptc_tsum(PtcGeom a, int nparity, const 
         st_stream(dst + k * kSB, make_float4(acc[2 * k].r, acc[2 * k].i, acc[2 * k + 1].r, acc[2 * k + 1].i));
 }
 
-// Partial weight gradients: part[wg][path][c][c'][s][t] (complex float), one slice per work-group.
-// Persistent: work-group wg takes the 64-site tiles wg, wg + G, wg + 2G, ... (G = grid size) and
-// sums their contributions into its slice in that order.  Per tile, four wavefronts: the gradient
-// of the tile (all output channels) is staged in LDS once, as [site][colour][row] with the
-// R = 4 NOUT rows (c, s) innermost; then each wavefront takes one (path, c') pair at a time and
-// computes its transport at the 64 sites into its own LDS slot, as [site][colour][t].  The pair's
-// 4 NOUT x 4 block of outputs is formed by the wavefront's 64 lanes as R rows x S = 64 / R site
-// classes: lane (class k, row) sums g_row conj(t_t) for all four t over the sites k, k + S, ...
-// (site, then colour, in index order; one read of g feeds four products and the transport reads
-// are shared by the R lanes of a class), then the S class sums of a row are combined by a
-// butterfly over the lanes, which gives every lane the same bits.  The running sums of a slice
-// belong to one lane each: no atomics, deterministic.
-template <int NOUT, typename AI>
-__global__ __launch_bounds__(256) void k_ptc_wgrad(PtcGeom a, int nin, const typename Act<AI>::vec *__restrict__ xin,
-                                                   const float4 *__restrict__ g, float2 *__restrict__ part) {
-    constexpr int R = 4 * NOUT, S = kTile / R;
-    static_assert(kTile % R == 0, "the rows of a pair must divide the tile");
-    constexpr int GX = 3 * R + 1;  // complex per site in gs (one of padding: the staging writes of
-                                   // the 64 sites then fall in distinct banks)
-    constexpr int TX = 14;         // complex per site in ts (12 + 2: 16-byte rows, staggered banks)
-    __shared__ float2 gs[kTile * GX];
-    __shared__ float4 ts[4][kTile * TX / 2];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & (kTile - 1);
-    const int row = lane % R, cls = lane / R;  // this lane's output row (c, s) and site class
-    const int ntile = (2 * a.g.vh + kTile - 1) / kTile;
-    const size_t chg = chan_vecs<float>(a.g.vhp), hg = half_vecs<float>(a.g.vhp), chin = chan_vecs<AI>(a.g.vhp);
-    const int npair = kPaths * nin;
-    float2 *slice = part + (size_t)blockIdx.x * npair * NOUT * 16;
-    float4 *tw = ts[wave];
-#pragma nounroll
-    for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-        const bool first = tile == (int)blockIdx.x;
-        const int s = tile * kTile + lane;
-        const bool on = s < 2 * a.g.vh;
-        const int p = on && s >= a.g.vh;
-        const uint32_t i = on ? (uint32_t)(s - p * a.g.vh) : 0u;
-        int x[4] = {0, 0, 0, 0};
-        if (on) site_coords(a.g, (int)i, p, x);
-        __syncthreads();  // the previous tile's reads of gs and ts are done
-        for (int c = wave; c < NOUT; c += 4) {
-            float r[24];
-            if (on) load_field<float, 24>(g + c * chg + p * hg, i, r);
-#pragma unroll
-            for (int ss = 0; ss < 4; ++ss)
-#pragma unroll
-                for (int col = 0; col < 3; ++col)
-                    gs[lane * GX + col * R + 4 * c + ss] =
-                        on ? make_float2(r[2 * (3 * ss + col)], r[2 * (3 * ss + col) + 1]) : make_float2(0.f, 0.f);
-        }
-        // the gathers of a wavefront's next pair are issued before the reduction of the current one
-        TRaw<AI> raw;
-        if (on && wave < npair) transport_load<AI>(a, xin + (wave % nin) * chin, p, i, x, wave / nin, raw);
-#pragma nounroll
-        for (int base = 0; base < npair; base += 4) {
-            const int pr = base + wave;
-            const int path = pr / nin, cp = pr % nin;
-            C<float> t[12];
-            if (on && pr < npair) {
-                transport_compute<AI>(raw, path, t);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 12; ++k) t[k] = mk(0.f, 0.f);
-            }
-            const int nx = pr + 4;
-            if (on && nx < npair) transport_load<AI>(a, xin + (nx % nin) * chin, p, i, x, nx / nin, raw);
-            __syncthreads();  // the previous pairs' reads of ts (and the staging of gs) are done
-#pragma unroll
-            for (int col = 0; col < 3; ++col)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    tw[lane * (TX / 2) + 2 * col + h] = make_float4(t[3 * (2 * h) + col].r, t[3 * (2 * h) + col].i,
-                                                                    t[3 * (2 * h + 1) + col].r, t[3 * (2 * h + 1) + col].i);
-            __syncthreads();
-            if (pr < npair) {
-                float ar[4] = {0.f, 0.f, 0.f, 0.f}, ai[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-                for (int j = 0; j < R; ++j) {
-                    const int xs = j * S + cls;
-#pragma unroll
-                    for (int col = 0; col < 3; ++col) {
-                        // g_row[col] conj(t_t[col]), t = 0..3
-                        const float2 gv = gs[xs * GX + col * R + row];
-                        const float4 t01 = tw[xs * (TX / 2) + 2 * col], t23 = tw[xs * (TX / 2) + 2 * col + 1];
-                        const float tr[4] = {t01.x, t01.z, t23.x, t23.z}, ti[4] = {t01.y, t01.w, t23.y, t23.w};
-#pragma unroll
-                        for (int tt = 0; tt < 4; ++tt) {
-                            ar[tt] = fmaf(gv.y, ti[tt], fmaf(gv.x, tr[tt], ar[tt]));
-                            ai[tt] = fmaf(-gv.x, ti[tt], fmaf(gv.y, tr[tt], ai[tt]));
-                        }
-                    }
-                }
-#pragma unroll
-                for (int o = R; o < kTile; o <<= 1)
-#pragma unroll
-                    for (int tt = 0; tt < 4; ++tt) {
-                        ar[tt] += __shfl_xor(ar[tt], o, 64);
-                        ai[tt] += __shfl_xor(ai[tt], o, 64);
-                    }
-                if (cls == 0) {
-                    const int c = row >> 2, ss = row & 3;
-                    float4 *dst = (float4 *)(slice + ((size_t)path * NOUT * nin + (size_t)c * nin + cp) * 16 + ss * 4);
-                    if (first) {
-                        dst[0] = make_float4(ar[0], ai[0], ar[1], ai[1]);
-                        dst[1] = make_float4(ar[2], ai[2], ar[3], ai[3]);
-                    } else {
-                        const float4 o0 = dst[0], o1 = dst[1];
-                        dst[0] = make_float4(o0.x + ar[0], o0.y + ai[0], o0.z + ar[1], o0.w + ai[1]);
-                        dst[1] = make_float4(o1.x + ar[2], o1.y + ai[2], o1.z + ar[3], o1.w + ai[3]);
-                    }
-                }
-            }
-        }
-    }
+// Weight gradients on the BF16 matrix cores.  With Q_p = T_{adj p} (the adjoint of T_p),
+//   dL/dW*[p,c,c'][s][t] = sum_{x, colour} g_c(x)_s conj((T_p x_c')(x)_t)
+//                        = sum_{x, colour} (Q_p g_c)(x)_s conj(x_c'(x)_t),
+// so the transports may be taken of either factor.  The kernel calls the transported factor "far"
+// (NT channels) and the other, read at its own site, "near" (NL channels):
+//   a hidden or last layer takes far = g, near = x: x is the BF16 activation, exact on the matrix
+//   cores, and the last layer (one output channel) needs 9 transports per site instead of 72;
+//   the first layer takes far = x (one channel, 9 transports), near = g, both FP32.
+// The contraction is a real GEMM per 64-site tile: rows (pair = path NT + channel, spin, re/im) of
+// the transports, columns (near channel, spin, re/im), depth k = 64 colour + site; the four
+// (re/im, re/im) products of an output are combined in the final reduction.  FP32 operands are
+// split exactly into three BF16 parts (truncation: 8 + 8 + 8 bits), so every product is exact and
+// only the FP32 accumulation rounds, as in an FP32 contraction; of the nine products of two split
+// operands the last (2^-32 of the value) is left out.
+//
+// A work-group of eight wavefronts, one per compute unit, sweeps its tiles.  Per tile it transposes
+// the near factor through LDS into registers (B operands, kept for all paths); per group of 8 pairs
+// (64 rows) each wavefront forms one pair's transports at the 64 sites, splits them, exchanges
+// re and im between neighbouring lanes so that a lane packs two sites, and writes them to LDS
+// ([part][row][k]); then the wavefronts multiply.  LDS holds two such buffers used in turn, so a
+// group costs one barrier, and the raw data of the next group is loaded before the current one is
+// multiplied.  All nine paths of a tile run in one work-group (accumulators: 72 registers for 8 -> 8
+// channels), so the near factor is read once and the far factor's neighbours meet in L2.
+// The products of a group go to accumulators of their own, the smallest parts first, and are added
+// to the running ones in FP32: the matrix cores do not round their sums to nearest (a chain over all
+// tiles drifted to 2.4e-6 of the result at 32^3 x 64).  The running sums are added to the work-group's
+// slice every kFlush tiles; one lane owns each entry of a slice (no atomics, deterministic).
+// Measured at 32^3 x 64 (FP32 vector contraction with the transports of x before -> now): 8 -> 8
+// channels 9.5 -> 3.65 ms, 8 -> 1 3.3 -> 0.77 ms, 1 -> 8 1.65 -> 1.33 ms; errors against 64 bits
+// 1.2-2.9e-7 -> 1.2-1.4e-7.  The 8 -> 8 kernel is bound by none of its parts alone: vector ALU 55 %
+// busy (about 400 instructions per transport), matrix cores 18 %, 10 GB fetched; without cache
+// misses it takes 10 % less, without the matrix instructions 15 %, without the link products 5 %.
+template <int NT, int NL, bool NEARBF>
+struct WgradShape {
+    static constexpr int NPAIR = kPaths * NT;
+    static constexpr int NG = (NPAIR + 7) / 8;                    // groups of 8 pairs
+    static constexpr int NCT = NL == 8 ? 4 : NL == 4 ? 2 : 1;     // 16-column tiles
+    static constexpr int LS = NEARBF ? 1 : 3;                     // parts of the near factor
+    // wavefronts along the four row tiles of a group and along the column tiles (a split near factor
+    // of 8 channels takes one column tile per wavefront, which fits the registers); with one column
+    // tile half the wavefronts have nothing to multiply
+    static constexpr int WR = !NEARBF && NCT == 4 ? 2 : 4, WC = NCT == 1 ? 1 : 8 / WR;
+    static constexpr int RT = 4 / WR, CT = NCT / WC;
+    static constexpr int SLICE = NG * RT * CT * 64 * WR * WC;     // float4 per work-group
+};
+constexpr int kWRow = 384;      // bytes of a row of 192 BF16 in LDS
+constexpr int kWBuf = 3 * 64 * kWRow;
+// Byte offset of depth k = 64 colour + 8 chunk + ... of a row: the eight 16-byte chunks of a colour are
+// permuted by the row, so that the 16-byte reads of 16 rows (and the 4-byte writes of two adjacent
+// rows) fall in distinct banks.
+DEV int wgrad_at(int row, int col, int chunk) { return row * kWRow + 128 * col + 16 * (chunk ^ ((row >> 1) & 7)); }
+constexpr int kFlush = 16;      // tiles between additions of the accumulators to the slice
+
+// Order of the 64-site tiles of one parity: XCD k (work-groups k mod 8, which dispatch places there)
+// walks the time slices of its eighth of the x1 range where that is whole blocks, so the
+// neighbours of a tile are read by the same XCD within a few slices; otherwise it takes the k-th
+// contiguous eighth of the blocks.  Steps whose block is nbp or more are skipped.
+DEV int tile_order(const Geom &g, int per, int xcd, int j) {
+    if (g.L[1] % 8 != 0 || (g.vh / (g.L[0] * 8)) % kTile != 0) return xcd * per + j;
+    const int bps = g.vh / (g.L[0] * 8 * kTile);
+    return ((j / bps) * 8 + xcd) * bps + j % bps;
 }
 
-// out[k] += sum_b part[b][k] (b ascending), k < n complex entries.  A work-group of 256 threads
-// takes 64 entries; wavefront w sums the partials b = w, w + 4, ... in FP64 and the four sums
-// are added in the order w = 0..3 (deterministic).
-constexpr int kRedK = 64;
-__global__ __launch_bounds__(256) void k_ptc_reduce(int nblk, int n, const float2 *__restrict__ part,
-                                                    float2 *__restrict__ out) {
-    __shared__ double2 sum[4][kRedK];
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int k = blockIdx.x * kRedK + l;
-    double re = 0.0, im = 0.0;
-    if (k < n) {
-        for (int b = w; b < nblk; b += 4) {
-            const float2 v = part[(size_t)b * n + k];
-            re += v.x;
-            im += v.y;
+// v = hi + mid + lo exactly, each with at most 8 significant bits (BF16 in the upper half word)
+DEV void split3(float v, uint32_t o[3]) {
+    o[0] = __float_as_uint(v) & 0xffff0000u;
+    const float r1 = v - __uint_as_float(o[0]);
+    o[1] = __float_as_uint(r1) & 0xffff0000u;
+    o[2] = __float_as_uint(r1 - __uint_as_float(o[1]));
+}
+DEV uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }  // upper halves
+// the value of the neighbouring lane (lane ^ 1)
+DEV float lane_swap(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, false));
+}
+
+template <int NT, int NL, bool NEARBF>
+__global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *__restrict__ far_,
+                                                      const void *__restrict__ near_, float4 *__restrict__ part) {
+    using W = WgradShape<NT, NL, NEARBF>;
+    __shared__ __align__(16) unsigned char sm[2 * kWBuf];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool mul = wave < W::WR * W::WC;
+    const int wr = (wave / W::WC) % W::WR, wc = wave % W::WC;
+    const int xcd = (int)blockIdx.x & 7, nwg = (int)gridDim.x >> 3;
+    const int nbp = a.g.vhp / kTile, per = (nbp + 7) >> 3;
+    const size_t chf = chan_vecs<float>(a.g.vhp);
+    float4 *slice = part + (size_t)blockIdx.x * W::SLICE + tid;
+    f32x4_t acc[W::NG][W::RT][W::CT];
+    bool first = true, negate = (blockIdx.x & 8) != 0;
+    int since = 0, buf = 0;
+    auto clear = [&]() {
+#pragma unroll
+        for (int g = 0; g < W::NG; ++g)
+#pragma unroll
+            for (int r = 0; r < W::RT; ++r)
+#pragma unroll
+                for (int c = 0; c < W::CT; ++c) acc[g][r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    };
+    auto flush = [&]() {
+        if (mul) {
+#pragma unroll
+            for (int g = 0; g < W::NG; ++g)
+#pragma unroll
+                for (int r = 0; r < W::RT; ++r)
+#pragma unroll
+                    for (int c = 0; c < W::CT; ++c) {
+                        float4 *d = slice + ((g * W::RT + r) * W::CT + c) * (64 * W::WR * W::WC);
+                        const f32x4_t v = acc[g][r][c];
+                        const float4 o = first ? make_float4(0.f, 0.f, 0.f, 0.f) : *d;
+                        *d = make_float4(o.x + v[0], o.y + v[1], o.z + v[2], o.w + v[3]);
+                    }
         }
+        clear();
+        first = false;
+        since = 0;
+    };
+    clear();
+    // The lane's site of the tile being loaded (a lane past the end takes the last site: the near
+    // factor is zero there) and the raw data of its next transport.
+    int i = 0, x[4], lp = 0, lbase = 0;
+    TRaw<float> raw;
+    auto next_tile = [&](int j) {  // the first step at or after j with a block of the lattice
+        for (; j < 2 * per; j += nwg) {
+            lp = j >= per;
+            const int blk = tile_order(a.g, per, xcd, j - lp * per);
+            if (blk >= nbp) continue;
+            lbase = blk * kTile;
+            i = min(lbase + lane, a.g.vh - 1);
+            site_coords(a.g, i, lp, x);
+            break;
+        }
+        return j;
+    };
+    // LDS offsets that do not change: this lane's words of the four spins' rows of its pair, and its A
+    // operand rows (depth chunks 0..3 of a colour; chunks 4..7 sit 64 bytes away, across the swizzle)
+    int wofs[4], aofs[W::RT];
+#pragma unroll
+    for (int sp = 0; sp < 4; ++sp)
+        wofs[sp] = wgrad_at(8 * wave + 2 * sp + (lane & 1), 0, lane >> 3) + 4 * ((lane >> 1) & 3);
+#pragma unroll
+    for (int r = 0; r < W::RT; ++r) aofs[r] = wgrad_at(16 * (wr * W::RT + r) + (lane & 15), 0, lane >> 4);
+    auto load = [&](int grp) {
+        const int pair = 8 * grp + wave;
+        if (pair < W::NPAIR)
+            transport_load<float>(a, far_ + (pair % NT) * chf, lp, (uint32_t)i, x, pair / NT, raw);
+    };
+    int j = next_tile((int)blockIdx.x >> 3);
+    if (j < 2 * per) load(0);
+#pragma nounroll
+    while (j < 2 * per) {
+        const int p = lp, base = lbase;
+        int jn = j;
+        // Every other tile takes the near factor negated and its products subtracted: the matrix cores
+        // round their sums downwards, and the bias of the two kinds cancels.
+        const float sign = negate ? -1.f : 1.f;
+        const uint32_t flip = negate ? 0x80008000u : 0u;
+        negate = !negate;
+        // the near factor, two neighbouring sites per thread: [part][column][k]; sites past the end are zero
+        const int nc = tid >> 5, sp = tid & 31, s0 = base + 2 * sp;
+        if (nc < NL) {
+            const bool on0 = s0 < a.g.vh, on1 = s0 + 1 < a.g.vh;
+            unsigned char *dst = sm + buf * kWBuf + 4 * (sp & 3);
+            // real r = 6 t + 2 colour + ri of the spinor is column 2 t + ri, depth 64 colour + site
+            auto put = [&](int part_, int r, uint32_t w) {
+                *reinterpret_cast<uint32_t *>(
+                    dst + part_ * 64 * kWRow + wgrad_at(8 * nc + 2 * (r / 6) + (r & 1), (r % 6) >> 1, sp >> 2)) = w ^ flip;
+            };
+            if constexpr (NEARBF) {
+                const uint4 *q = site_ptr((const uint4 *)near_ + nc * chan_vecs<bf16s>(a.g.vhp) +
+                                              p * half_vecs<bf16s>(a.g.vhp), (uint32_t)s0, 3);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const uint4 u0 = q[k * kSB], u1 = q[k * kSB + 1];
+                    const uint32_t w0[4] = {u0.x, u0.y, u0.z, u0.w}, w1[4] = {u1.x, u1.y, u1.z, u1.w};
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const uint32_t v0 = on0 ? w0[m] : 0u, v1 = on1 ? w1[m] : 0u;
+                        put(0, 8 * k + 2 * m, __builtin_amdgcn_perm(v1, v0, 0x05040100u));  // lower halves
+                        put(0, 8 * k + 2 * m + 1, pack_hi(v0, v1));
+                    }
+                }
+            } else {
+                const float4 *q = site_ptr((const float4 *)near_ + nc * chf + p * half_vecs<float>(a.g.vhp),
+                                           (uint32_t)s0, 6);
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    const float4 u0 = q[k * kSB], u1 = q[k * kSB + 1];
+                    const float f0[4] = {u0.x, u0.y, u0.z, u0.w}, f1[4] = {u1.x, u1.y, u1.z, u1.w};
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        uint32_t y0[3], y1[3];
+                        split3(on0 ? f0[m] : 0.f, y0);
+                        split3(on1 ? f1[m] : 0.f, y1);
+#pragma unroll
+                        for (int q3 = 0; q3 < 3; ++q3) put(q3, 4 * k + m, pack_hi(y0[q3], y1[q3]));
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        bf16x8_t nb[W::LS][W::CT][6];
+#pragma unroll
+        for (int l = 0; l < W::LS; ++l)
+#pragma unroll
+            for (int c = 0; c < W::CT; ++c)
+#pragma unroll
+                for (int ks = 0; ks < 6; ++ks)
+                    nb[l][c][ks] = *reinterpret_cast<const bf16x8_t *>(
+                        sm + buf * kWBuf + 64 * l * kWRow +
+                        wgrad_at(16 * (wc * W::CT + c) + (lane & 15), ks >> 1, 4 * (ks & 1) + (lane >> 4)));
+        buf ^= 1;
+#pragma unroll
+        for (int grp = 0; grp < W::NG; ++grp) {
+            if (8 * grp + wave < W::NPAIR) {
+                C<float> t[12];
+                transport_compute<float>(raw, (8 * grp + wave) / NT, t);
+                // an even lane packs the real parts of its own and the next site (row 2 s), an odd lane
+                // the imaginary parts of the previous and its own site (row 2 s + 1)
+                const bool odd = (lane & 1) != 0;
+                const uint32_t sel = odd ? 0x03020706u : 0x07060302u;
+                unsigned char *dst = sm + buf * kWBuf;
+#pragma unroll
+                for (int k = 0; k < 12; ++k) {
+                    const float own = odd ? t[k].i : t[k].r, oth = lane_swap(odd ? t[k].r : t[k].i);
+                    uint32_t y0[3], y1[3];
+                    split3(own, y0);
+                    split3(oth, y1);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        *reinterpret_cast<uint32_t *>(dst + wofs[k / 3] + 64 * q * kWRow + 128 * (k % 3)) =
+                            __builtin_amdgcn_perm(y1[q], y0[q], sel);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (grp + 1 < W::NG) {
+                load(grp + 1);
+            } else {
+                jn = next_tile(j + nwg);
+                if (jn < 2 * per) load(0);
+            }
+            __syncthreads();
+            // row tiles holding no pair of the last group are skipped (their rows were not written)
+            constexpr int kLast = W::NPAIR - 8 * (W::NG - 1);
+            const int rtiles = grp + 1 < W::NG ? 4 : (kLast + 1) / 2;
+#pragma unroll
+            for (int r = 0; r < W::RT; ++r) {
+                if (!mul || wr * W::RT + r >= rtiles) continue;
+                // with a split near factor the products of the two largest parts are summed apart
+                f32x4_t v[W::LS > 1 ? 2 : 1][W::CT];
+#pragma unroll
+                for (auto &u : v)
+#pragma unroll
+                    for (auto &w : u) w = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                const unsigned char *a0 = sm + buf * kWBuf + aofs[r], *a1 = sm + buf * kWBuf + (aofs[r] ^ 64);
+#pragma unroll
+                for (int q = 2; q >= 0; --q) {
+#pragma unroll
+                    for (int ks = 0; ks < 6; ++ks) {
+                        const bf16x8_t A = *reinterpret_cast<const bf16x8_t *>(
+                            (ks & 1 ? a1 : a0) + 64 * q * kWRow + 128 * (ks >> 1));
+#pragma unroll
+                        for (int l = W::LS - 1; l >= 0; --l) {
+                            if (q + l == 4) continue;
+#pragma unroll
+                            for (int c = 0; c < W::CT; ++c) {
+                                f32x4_t &u = v[W::LS > 1 && q + l == 0][c];
+                                u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, nb[l][c][ks], u, 0, 0, 0);
+                            }
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);  // bounds the LDS reads in flight (registers)
+                }
+#pragma unroll
+                for (auto &u : v)
+#pragma unroll
+                    for (int c = 0; c < W::CT; ++c) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[grp][r][c][e] = fmaf(sign, u[c][e], acc[grp][r][c][e]);
+                    }
+            }
+            buf ^= 1;
+        }
+        if (++since == kFlush) flush();
+        j = jn;
     }
-    sum[w][l] = make_double2(re, im);
+    if (since || first) flush();
+}
+
+// out[k] += the weight gradients from the slices of k_ptc_wgrad.  A work-group of 256 threads takes
+// 16 consecutive float4 of the slices (one lane group of a 16 x 16 accumulator tile: 4
+// rows x 16 columns); 16 strands of threads sum the slices in FP64 and are added in order
+// (deterministic), then the four (re/im, re/im) sums of each of the 16 outputs are combined.
+template <int NT, int NL, bool NEARBF>
+__global__ __launch_bounds__(256) void k_ptc_reduce(int nwg, const float4 *__restrict__ part, float2 *__restrict__ out) {
+    using W = WgradShape<NT, NL, NEARBF>;
+    constexpr int SL = 16;
+    __shared__ double sum[SL][4][16];
+    constexpr int TL = 64 * W::WR * W::WC;  // float4 of one accumulator tile of every wavefront
+    const int f0 = (int)blockIdx.x * 16;
+    const int j = threadIdx.x & 15, sl = threadIdx.x >> 4;
+    const int tl = f0 / TL, wave = (f0 % TL) >> 6, lg = (f0 >> 4) & 3;
+    const int ct = (wave % W::WC) * W::CT + tl % W::CT;
+    const int rt = (wave / W::WC) * W::RT + (tl / W::CT) % W::RT, gl = tl / (W::CT * W::RT);
+    const int pair = 8 * gl + 2 * rt + (lg >> 1);
+    if (pair >= W::NPAIR) return;  // uniform over the work-group
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int b = sl; b < nwg; b += SL) {
+        const float4 q = part[(size_t)b * W::SLICE + f0 + j];
+        v[0] += q.x;
+        v[1] += q.y;
+        v[2] += q.z;
+        v[3] += q.w;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sum[sl][r][j] = v[r];
     __syncthreads();
-    if (w == 0 && k < n) {
-        for (int j = 1; j < 4; ++j) {
-            re += sum[j][l].x;
-            im += sum[j][l].y;
-        }
-        out[k].x += (float)re;
-        out[k].y += (float)im;
+    if (threadIdx.x < 64) {
+        const int r = threadIdx.x >> 4;
+        double s = sum[0][r][j];
+        for (int b = 1; b < SL; ++b) s += sum[b][r][j];
+        sum[0][r][j] = s;
     }
+    __syncthreads();
+    if (threadIdx.x >= 16) return;
+    // rows 2 rr + ri (far spin 2 (lg & 1) + rr), columns 2 cp + ri (near channel and spin)
+    const int rr = threadIdx.x >> 3, cp = threadIdx.x & 7;
+    const int cl = 2 * ct + (cp >> 2), sn = cp & 3, sf = 2 * (lg & 1) + rr;
+    if (cl >= NL) return;
+    const double re = sum[0][2 * rr][2 * cp] + sum[0][2 * rr + 1][2 * cp + 1];
+    const double im = sum[0][2 * rr + 1][2 * cp] - sum[0][2 * rr][2 * cp + 1];  // Im(far conj(near))
+    const int path = pair / NT, ch = pair % NT;
+    size_t k;
+    double sg = 1.0;
+    if (NEARBF) {  // far = g (NT = c_out), transported along the adjoint path; near = x (NL = c_in)
+        const int pa = path == 0 ? 0 : ((path - 1) ^ 1) + 1;
+        k = ((size_t)(pa * NT + ch) * NL + cl) * 16 + sf * 4 + sn;
+    } else {  // far = x (one channel), near = g (NL = c_out): g conj(x)
+        k = ((size_t)path * NL + cl) * 16 + sn * 4 + sf;
+        sg = -1.0;
+    }
+    out[k].x += (float)re;
+    out[k].y += (float)(sg * im);
 }
 
 // Adam on n real parameters (interleaved re, im); writes the BF16 working copy
@@ -714,32 +923,60 @@ void layer_dispatch(const PtcGeom &a, int nin, int nout, const void *x, const ui
     }
     HIP_CHECK(hipGetLastError());
 }
-// work-groups of the weight-gradient kernel: as many per compute unit as its LDS tiles and
-// registers let run at once (three for one or two output channels, two for four or eight), at
-// most one per tile
-int wgrad_grid(size_t vh, int nout) {
-    const size_t ntile = (2 * vh + kTile - 1) / kTile;
-    return (int)std::min(ntile, (size_t)(nout <= 2 ? 3 : 2) * compute_units());
+// Work-groups of the weight-gradient kernel, a multiple of 8 (the XCDs): one per compute unit (what its
+// LDS allows), at most one per tile of an XCD.
+int wgrad_groups(size_t vhp) {
+    const size_t per = 2 * ((vhp / kTile + 7) / 8);
+    return 8 * (int)std::max<size_t>(1, std::min(per, (size_t)compute_units() / 8));
 }
-template <int NOUT>
-void launch_wgrad(const PtcGeom &a, int nin, const void *x, bool x_bf16, const void *g, void *part, hipStream_t s) {
-    if (x_bf16)
-        k_ptc_wgrad<NOUT, bf16s><<<wgrad_grid(a.g.vh, NOUT), 256, 0, s>>>(a, nin, (const uint4 *)x, (const float4 *)g,
-                                                                    (float2 *)part);
-    else
-        k_ptc_wgrad<NOUT, float><<<wgrad_grid(a.g.vh, NOUT), 256, 0, s>>>(a, nin, (const float4 *)x, (const float4 *)g,
-                                                                    (float2 *)part);
+template <int NT, int NL, bool NEARBF>
+void launch_wgrad(const PtcGeom &a, const void *far_, const void *near_, void *part, float2 *out, hipStream_t s) {
+    using W = WgradShape<NT, NL, NEARBF>;
+    const int nwg = wgrad_groups(a.g.vhp);
+    k_ptc_wgrad<NT, NL, NEARBF><<<nwg, 512, 0, s>>>(a, (const float4 *)far_, near_, (float4 *)part);
+    k_ptc_reduce<NT, NL, NEARBF><<<W::SLICE / 16, 256, 0, s>>>(nwg, (const float4 *)part, out);
 }
-void wgrad_dispatch(const PtcGeom &a, int nin, int nout, const void *x, bool x_bf16, const void *g, void *part,
-                    hipStream_t s) {
+// Calls f with the shape of a layer's weight gradient: far and near channel counts, and whether the
+// near factor is the BF16 activation of a hidden layer (else the first layer: far = x, near = g).
+template <typename F> void wgrad_shape(int nin, int nout, bool x_bf16, F &&f) {
+    auto near_of = [&](auto nt, int nl, auto bf) {
+        switch (nl) {
+            case 1: f(nt, std::integral_constant<int, 1>(), bf); break;
+            case 2: f(nt, std::integral_constant<int, 2>(), bf); break;
+            case 4: f(nt, std::integral_constant<int, 4>(), bf); break;
+            case 8: f(nt, std::integral_constant<int, 8>(), bf); break;
+            default: throw Error(DIRAC_EUNSUPPORTED, "PTC channel counts must be 1, 2, 4 or 8");
+        }
+    };
+    if (!x_bf16) {
+        require(nin == 1, "the first layer of a PTC network has one input channel", DIRAC_EUNSUPPORTED);
+        near_of(std::integral_constant<int, 1>(), nout, std::false_type());
+        return;
+    }
     switch (nout) {
-        case 1: launch_wgrad<1>(a, nin, x, x_bf16, g, part, s); break;
-        case 2: launch_wgrad<2>(a, nin, x, x_bf16, g, part, s); break;
-        case 4: launch_wgrad<4>(a, nin, x, x_bf16, g, part, s); break;
-        case 8: launch_wgrad<8>(a, nin, x, x_bf16, g, part, s); break;
+        case 1: near_of(std::integral_constant<int, 1>(), nin, std::true_type()); break;
+        case 2: near_of(std::integral_constant<int, 2>(), nin, std::true_type()); break;
+        case 4: near_of(std::integral_constant<int, 4>(), nin, std::true_type()); break;
+        case 8: near_of(std::integral_constant<int, 8>(), nin, std::true_type()); break;
         default: throw Error(DIRAC_EUNSUPPORTED, "PTC output channels must be 1, 2, 4 or 8");
     }
+}
+// dW += the weight gradients of a layer with input x and output gradient g
+void wgrad_dispatch(const PtcGeom &a, int nin, int nout, const void *x, bool x_bf16, const void *g, void *part,
+                    float2 *dW, hipStream_t s) {
+    wgrad_shape(nin, nout, x_bf16, [&](auto nt, auto nl, auto bf) {
+        constexpr bool B = decltype(bf)::value;
+        launch_wgrad<decltype(nt)::value, decltype(nl)::value, B>(a, B ? g : x, B ? x : g, part, dW, s);
+    });
     HIP_CHECK(hipGetLastError());
+}
+size_t wgrad_part_bytes(size_t vhp, int nin, int nout, bool x_bf16) {
+    size_t n = 0;
+    wgrad_shape(nin, nout, x_bf16, [&](auto nt, auto nl, auto bf) {
+        using W = WgradShape<decltype(nt)::value, decltype(nl)::value, decltype(bf)::value>;
+        n = (size_t)wgrad_groups(vhp) * W::SLICE * sizeof(float4);
+    });
+    return n;
 }
 
 PtcGeom geom_of(dirac_ctx *c, hipStream_t s) {
@@ -829,10 +1066,10 @@ void ptc_ensure_acts(dirac_ctx *c, dirac_ptc *n) {
     for (int l = 0; l <= n->nlayers; ++l) maxc = std::max(maxc, n->ch[l]);
     n->gbuf.alloc(2 * (size_t)maxc * chanb);
     if (n->contract_last()) n->zbuf.alloc((size_t)kPaths * chanb);
-    size_t maxpart = 0;  // complex entries of the weight-gradient slices of the largest layer
+    size_t maxpart = 0;  // the weight-gradient slices of the largest layer
     for (int l = 0; l < n->nlayers; ++l)
-        maxpart = std::max(maxpart, (size_t)wgrad_grid(c->vh, n->ch[l + 1]) * ptc_nweights(n, l));
-    n->part.alloc(maxpart * 8);
+        maxpart = std::max(maxpart, wgrad_part_bytes(c->g.vhp, n->ch[l], n->ch[l + 1], act_bf16(n, l)));
+    n->part.alloc(maxpart);
 }
 
 float *ptc_act(dirac_ctx *c, dirac_ptc *n, int l) {
@@ -882,10 +1119,7 @@ void ptc_backward_acts(dirac_ctx *c, dirac_ptc *n, const void *g_out, void *gin,
     for (int l = n->nlayers - 1; l >= 0; --l) {
         const int nin = n->ch[l], nout = n->ch[l + 1];
         const int nw = (int)ptc_nweights(n, l);
-        wgrad_dispatch(a, nin, nout, ptc_act(c, n, l), act_bf16(n, l), gA, n->part.p, s);
-        k_ptc_reduce<<<(nw + kRedK - 1) / kRedK, 256, 0, s>>>(wgrad_grid(c->vh, nout), nw, (const float2 *)n->part.p,
-                                                      (float2 *)n->grad.p + n->off[l]);
-        HIP_CHECK(hipGetLastError());
+        wgrad_dispatch(a, nin, nout, ptc_act(c, n, l), act_bf16(n, l), gA, n->part.p, (float2 *)n->grad.p + n->off[l], s);
         if (l == 0 && !gin) break;
         k_adjoint_weights<<<(nw + 255) / 256, 256, 0, s>>>(nout, nin, (const uint32_t *)n->wbf.p + n->off[l],
                                                            (uint32_t *)n->wt.p + n->off[l]);
