@@ -68,6 +68,11 @@ void check_no_alias(const void *a, size_t na, const void *b, size_t nb) {
     require(x + na <= y || y + nb <= x, "output buffer overlaps an input buffer");
 }
 
+// device memory of one call, released when it returns or throws
+struct Scratch : dl::DevBuf {
+    ~Scratch() { release(); }
+};
+
 void check_ctx(const dirac_ctx *c) { require(c != nullptr, "context is NULL"); }
 
 void check_prec(int pr) { require(pr >= DIRAC_F64 && pr <= DIRAC_BF16, "unknown precision"); }
@@ -123,6 +128,7 @@ const char *dirac_last_error(void) { return g_err.c_str(); }
 dirac_status dirac_create(const dirac_params *prm, const void *su3_links, const double *u1_angles, void *stream,
                           dirac_ctx **out) {
     dirac_ctx *c = nullptr;
+    Scratch planes;
     g_err.clear();
     try {
         require(prm != nullptr && out != nullptr, "params and out must not be NULL");
@@ -153,19 +159,14 @@ dirac_status dirac_create(const dirac_params *prm, const void *su3_links, const 
         for (int m = 0; m < 4; ++m) c->g.B[m] = prm->dims[m];
         c->g.cs = prm->cstar;
         c->g.h1 = prm->dims[1] / 2;
-        c->U_lex.alloc((size_t)V * 4 * 9 * 16);
-        HIP_CHECK(hipMemcpyAsync(c->U_lex.p, su3_links, (size_t)V * 4 * 9 * 16, hipMemcpyDeviceToDevice, s));
-        if (u1_angles) {
-            c->theta_lex.alloc((size_t)V * 4 * 8);
-            HIP_CHECK(hipMemcpyAsync(c->theta_lex.p, u1_angles, (size_t)V * 4 * 8, hipMemcpyDeviceToDevice, s));
-        }
-        dl::import_links(c, s);
-        dl::clover_build(c, s);
+        // scratch, released on return: the compressed links and the clover field are built from it
+        planes.alloc_field(dl::link_planes_bytes(c->g));
+        dl::links_to_planes(c, su3_links, planes.p, s);
+        dl::import_links(c, planes.p, u1_angles, s);
+        dl::clover_build(c, planes.p, u1_angles, s);
         const int64_t bad = dl::clover_invert_parity(c, 1, s);
         HIP_CHECK(hipStreamSynchronize(s));
-        // the gauge input is no longer needed: links are compressed, the clover field is built
-        c->U_lex.release();
-        c->theta_lex.release();
+        planes.retire();  // read on `s` alone
         *out = c;
         if (bad >= 0) return fail(DIRAC_ESINGULAR, "singular odd-site clover block at Lambda = " + std::to_string(bad));
     } catch (const dl::Error &e) {
@@ -194,7 +195,7 @@ dirac_status dirac_set_cache_block(dirac_ctx *c, const int *block) {
 
 dirac_status dirac_create_openqxd(const dirac_params *prm, const int *block, const void *u_odd, const double *a_odd,
                                   void *stream, dirac_ctx **out) {
-    dl::DevBuf U, th;
+    Scratch U, th;
     g_err.clear();
     try {
         require(prm != nullptr && out != nullptr && block != nullptr, "params, block and out must not be NULL");
@@ -242,14 +243,12 @@ dirac_status dirac_create_openqxd(const dirac_params *prm, const int *block, con
 dirac_status dirac_destroy(dirac_ctx *c) {
     API_BEGIN
     if (!c) return DIRAC_OK;
-    (void)hipDeviceSynchronize();
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
     dl::free_bwork(c);
     dl::free_solver_work(c);
-    c->U_lex.release();
-    c->theta_lex.release();
     for (auto &f : c->f) {
         for (int p = 0; p < 2; ++p) {
-            f.links[p].release(); f.omega[p].release(); f.clov[p].release(); f.clinv[p].release();
+            for (dl::DevBuf *b : {&f.links[p], &f.omega[p], &f.clov[p], &f.clinv[p]}) idle ? b->retire() : b->release();
         }
         f.tmp_half.release(); f.user_in.release(); f.user_out.release();
     }

@@ -1,6 +1,8 @@
 // Clover field on the device (paper Sec. 4.3 and the outlook's "generate the clover
 // field on the GPU"): build A = (4 + m0) + C from the SU(3) and U(1) links in FP64,
 // invert its 6x6 chirality blocks in FP64 registers, and apply A or A^-1.
+#include <type_traits>
+
 #include "dirac_ops.h"
 #include "internal.h"
 
@@ -11,12 +13,14 @@ struct M3 {
     C<double> m[9];
 };
 
-DEV M3 ld(const double *__restrict__ U, int lam, int mu) {
-    const double2 *u = reinterpret_cast<const double2 *>(U + ((size_t)lam * 4 + mu) * 18);
+// link U_mu of site (parity, half index) from the plane copy of the gauge field (links_to_planes)
+DEV M3 ld(const Geom &g, const double2 *__restrict__ U, int parity, int i, int mu) {
+    asm volatile("" : "+v"(i));  // a link used twice is read twice (L1), not kept in 36 registers between
+    const double2 *u = site_ptr(U + (size_t)(4 * parity + mu) * 9 * g.vhp, (uint32_t)i, 9);
     M3 r;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        double2 v = u[k];
+        double2 v = u[k * kSB];
         r.m[k] = mk(v.x, v.y);
     }
     return r;
@@ -47,6 +51,19 @@ DEV M3 mul_nd(const M3 &a, const M3 &b) {  // a b^dag
         }
     return r;
 }
+DEV M3 mul_dd(const M3 &a, const M3 &b) {  // a^dag b^dag
+    M3 r;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            C<double> s = conj_mul(a.m[i], conj(b.m[3 * j]));
+            cmadd(s, a.m[3 + i], conj(b.m[3 * j + 1]));
+            cmadd(s, a.m[6 + i], conj(b.m[3 * j + 2]));
+            r.m[3 * i + j] = s;
+        }
+    return r;
+}
 DEV M3 mul_dn(const M3 &a, const M3 &b) {  // a^dag b
     M3 r;
 #pragma unroll
@@ -62,12 +79,16 @@ DEV M3 mul_dn(const M3 &a, const M3 &b) {  // a^dag b
 }
 
 // F'_{mu nu}(x) = c_sw (Q - Q^dag)/8 + c_qed qhat (q - q*)/8, Q / q the sum of the four
-// plaquette leaves at x in the (mu, nu) plane from U / from exp(i theta).
-DEV void plane_field(const Geom &g, const double *__restrict__ U, const double *__restrict__ th, const int x[4],
-                     int mu, int nu, double csw, double cq, M3 &F) {
-    int y[4];
+// plaquette leaves at x in the (mu, nu) plane from U / from exp(i theta).  F' is anti-Hermitian: out
+// holds its 9 independent reals, Im F_00, Im F_11, Im F_22, then (re, im) of F_01, F_02, F_12.
+template <int mu, int nu>
+DEV void plane_field(const Geom &g, int p, const double2 *__restrict__ U, const double *__restrict__ th, const int x[4],
+                     double csw, double cq, double out[9]) {
+    struct At {
+        int i, lam;
+    };
     auto at = [&](int dm, int dn) {
-        y[0] = x[0]; y[1] = x[1]; y[2] = x[2]; y[3] = x[3];
+        int y[4] = {x[0], x[1], x[2], x[3]};
         // each step that crosses the boundary of a C* direction also moves x1 (the shifts commute)
         auto step = [&](int d, int k) {
             if (k == 0) return;
@@ -77,96 +98,151 @@ DEV void plane_field(const Geom &g, const double *__restrict__ U, const double *
         };
         step(mu, dm);
         step(nu, dn);
-        return lex_index(g, y);
+        return At{half_index(g, y), lex_index(g, y)};
     };
-    const int x0 = at(0, 0), xpm = at(1, 0), xpn = at(0, 1), xmm = at(-1, 0), xmn = at(0, -1);
-    const int xmm_pn = at(-1, 1), xmm_mn = at(-1, -1), xpm_mn = at(1, -1);
-    M3 q = mul_nd(mul(ld(U, x0, mu), ld(U, xpm, nu)), mul(ld(U, x0, nu), ld(U, xpn, mu)));
-    M3 t = mul(mul_nd(ld(U, x0, nu), ld(U, xmm_pn, mu)), mul_dn(ld(U, xmm, nu), ld(U, xmm, mu)));
+    const At x0 = at(0, 0), xpm = at(1, 0), xpn = at(0, 1), xmm = at(-1, 0), xmn = at(0, -1);
+    const At xmm_pn = at(-1, 1), xmm_mn = at(-1, -1), xpm_mn = at(1, -1);
+    // sites an odd number of steps away have the other parity
+    auto e = [&](const At &y, int d) { return ld(g, U, p, y.i, d); };
+    auto o = [&](const At &y, int d) { return ld(g, U, 1 - p, y.i, d); };
+    // each leaf as a chain of products with one more link at a time (two halves multiplied at the end
+    // need one more matrix in registers)
+    M3 q, t;
+    auto add = [&]() {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) q.m[k] = q.m[k] + t.m[k];
-    t = mul_dn(mul(ld(U, xmm_mn, nu), ld(U, xmm, mu)), mul(ld(U, xmm_mn, mu), ld(U, xmn, nu)));
+        for (int k = 0; k < 9; ++k) q.m[k] = q.m[k] + t.m[k];
+    };
+    q = mul(e(x0, mu), o(xpm, nu));
+    q = mul_nd(q, o(xpn, mu));
+    q = mul_nd(q, e(x0, nu));
+    t = mul_nd(e(x0, nu), e(xmm_pn, mu));
+    t = mul_nd(t, o(xmm, nu));
+    t = mul(t, o(xmm, mu));
+    add();
+    t = mul_dd(o(xmm, mu), e(xmm_mn, nu));
+    t = mul(t, e(xmm_mn, mu));
+    t = mul(t, o(xmn, nu));
+    add();
+    t = mul_dn(o(xmn, nu), o(xmn, mu));
+    t = mul(t, e(xpm_mn, nu));
+    t = mul_nd(t, e(x0, mu));
+    add();
 #pragma unroll
-    for (int k = 0; k < 9; ++k) q.m[k] = q.m[k] + t.m[k];
-    t = mul(mul_dn(ld(U, xmn, nu), ld(U, xmn, mu)), mul_nd(ld(U, xpm_mn, nu), ld(U, x0, mu)));
-#pragma unroll
-    for (int k = 0; k < 9; ++k) q.m[k] = q.m[k] + t.m[k];
+    for (int a = 0; a < 3; ++a) out[a] = (csw * 0.125) * (q.m[4 * a].i - (-q.m[4 * a].i));
+    int k = 3;
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) F.m[3 * a + b] = (csw * 0.125) * (q.m[3 * a + b] - conj(q.m[3 * b + a]));
+        for (int b = a + 1; b < 3; ++b) {
+            const C<double> f = (csw * 0.125) * (q.m[3 * a + b] - conj(q.m[3 * b + a]));
+            out[k] = f.r;
+            out[k + 1] = f.i;
+            k += 2;
+        }
     if (th && cq != 0.0) {
-        auto T = [&](int s, int d) { return th[(size_t)s * 4 + d]; };
+        auto T = [&](const At &y, int d) { return th[(size_t)y.lam * 4 + d]; };
         const double a1 = T(x0, mu) + T(xpm, nu) - T(xpn, mu) - T(x0, nu);
         const double a2 = T(x0, nu) - T(xmm_pn, mu) - T(xmm, nu) + T(xmm, mu);
         const double a3 = -T(xmm, mu) - T(xmm_mn, nu) + T(xmm_mn, mu) + T(xmn, nu);
         const double a4 = -T(xmn, nu) + T(xmn, mu) + T(xpm_mn, nu) - T(x0, mu);
         // (q - q*) / 8 = i Im(q) / 4
-        const double im = cq * 0.25 * (sin(a1) + sin(a2) + sin(a3) + sin(a4));
+        double s1, s2, s3, s4, c;
+        sc(a1, s1, c);
+        sc(a2, s2, c);
+        sc(a3, s3, c);
+        sc(a4, s4, c);
+        const double im = cq * 0.25 * (s1 + s2 + s3 + s4);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) F.m[4 * a].i += im;
+        for (int a = 0; a < 3; ++a) out[a] += im;
     }
 }
 
-// One thread per site of parity p: A(x) packed as [72] reals, block + then block -.
+// A(x) packed as [72] reals, block + then block -, for the sites of parity p.
 // With sigma_0k = diag(s_k, -s_k), sigma_jk = -eps_jkl diag(s_l, s_l) (chiral basis) the
 // term (i/4) sum sigma_{mu nu} F_{mu nu} is, per chirality block, [[G3, G1 - i G2], [G1 + i G2, -G3]]:
 //   block +: G1 = (i/2)(F01 - F23), G2 = (i/2)(F02 + F13), G3 = (i/2)(F03 - F12)
 //   block -: G1 = -(i/2)(F01 + F23), G2 = -(i/2)(F02 - F13), G3 = -(i/2)(F03 + F12)
-__global__ __launch_bounds__(kBlock) void k_clover_build(Geom g, int p, const double *__restrict__ U,
-                                                          const double *__restrict__ th, double csw, double cq,
-                                                          double diag, double2 *__restrict__ out) {
-    int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= g.vh) return;
+// A work-group of six wavefronts takes 64 sites, one plane (mu, nu) per wavefront (the 12 links of a
+// plane and its products fit the registers; one thread for all six planes spilled 6 KB per lane), the
+// fields meet in LDS, and wavefront w forms planes 3 w .. 3 w + 2 of block + and of block -.  Bound by
+// the latency of its chain of link loads and FP64 products (7800 FMAs and 864 16-byte loads per
+// site: 0.15 ms per parity at full rates) at 1.5 wavefronts per SIMD.  At 24^3 x 48, both parities:
+// 4.0 -> 1.07 ms.
+constexpr int kFReals = 9;
+__global__ __launch_bounds__(384, 2) void k_clover_build(Geom g, int p, const double2 *__restrict__ U,
+                                                         const double *__restrict__ th, double csw, double cq,
+                                                         double diag, double2 *__restrict__ out) {
+    __shared__ double fs[6][kFReals][kSB];
+    const int lane = threadIdx.x & (kSB - 1), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int i = min((int)blockIdx.x * kSB + lane, g.vh - 1);  // lanes past the end repeat the last site
     int x[4];
     site_coords(g, i, p, x);
-    M3 F[6];
-    plane_field(g, U, th, x, 0, 1, csw, cq, F[0]);
-    plane_field(g, U, th, x, 0, 2, csw, cq, F[1]);
-    plane_field(g, U, th, x, 0, 3, csw, cq, F[2]);
-    plane_field(g, U, th, x, 1, 2, csw, cq, F[3]);
-    plane_field(g, U, th, x, 1, 3, csw, cq, F[4]);
-    plane_field(g, U, th, x, 2, 3, csw, cq, F[5]);
-    double pk[72];
+    double f[kFReals];
+    switch (w) {
+        case 0: plane_field<0, 1>(g, p, U, th, x, csw, cq, f); break;
+        case 1: plane_field<0, 2>(g, p, U, th, x, csw, cq, f); break;
+        case 2: plane_field<0, 3>(g, p, U, th, x, csw, cq, f); break;
+        case 3: plane_field<1, 2>(g, p, U, th, x, csw, cq, f); break;
+        case 4: plane_field<1, 3>(g, p, U, th, x, csw, cq, f); break;
+        default: plane_field<2, 3>(g, p, U, th, x, csw, cq, f); break;
+    }
+#pragma unroll
+    for (int k = 0; k < kFReals; ++k) fs[w][k][lane] = f[k];
+    __syncthreads();
+    if ((int)blockIdx.x * kSB + lane >= g.vh) return;  // no barrier follows
+    // element k = 3 a + b of the anti-Hermitian field of plane n
+    auto F = [&](int n, int k) -> C<double> {
+        const int a = k / 3, b = k % 3;
+        if (a == b) return mk(0.0, fs[n][a][lane]);
+        const int lo = a < b ? a : b, hi = a < b ? b : a;
+        const int q = 3 + 2 * (lo + hi - 1);
+        const double re = fs[n][q][lane], im = fs[n][q + 1][lane];
+        return a < b ? mk(re, im) : mk(-re, im);
+    };
+    double2 *dst = site_ptr(out, (uint32_t)i, 36);
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
-        C<double> G1[9], G2[9], G3[9];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            // block +: (F01 - F23, F02 + F13, F03 - F12) * (i/2); block -: -(F01 + F23, F02 - F13, F03 + F12) * (i/2)
-            C<double> f1 = blk == 0 ? F[0].m[k] - F[5].m[k] : -(F[0].m[k] + F[5].m[k]);
-            C<double> f2 = blk == 0 ? F[1].m[k] + F[4].m[k] : -(F[1].m[k] - F[4].m[k]);
-            C<double> f3 = blk == 0 ? F[2].m[k] - F[3].m[k] : -(F[2].m[k] + F[3].m[k]);
-            G1[k] = 0.5 * times_i(f1);
-            G2[k] = 0.5 * times_i(f2);
-            G3[k] = 0.5 * times_i(f3);
-        }
+        // G1, G2, G3 of the block: block + (F01 - F23, F02 + F13, F03 - F12) * (i/2), block -
+        // -(F01 + F23, F02 - F13, F03 + F12) * (i/2)
+        auto G1 = [&](int k) { return 0.5 * times_i(blk == 0 ? F(0, k) - F(5, k) : -(F(0, k) + F(5, k))); };
+        auto G2 = [&](int k) { return 0.5 * times_i(blk == 0 ? F(1, k) + F(4, k) : -(F(1, k) - F(4, k))); };
+        auto G3 = [&](int k) { return 0.5 * times_i(blk == 0 ? F(2, k) - F(3, k) : -(F(2, k) + F(3, k))); };
         auto B = [&](int r, int c) -> C<double> {
-            const int s = r / 3, a = r % 3, t = c / 3, b = c % 3;
-            const int k = 3 * a + b;
+            const int s = r / 3, t = c / 3, k = 3 * (r % 3) + c % 3;
             C<double> v;
-            if (s == 0 && t == 0) v = G3[k];
-            else if (s == 0 && t == 1) v = G1[k] - times_i(G2[k]);
-            else if (s == 1 && t == 0) v = G1[k] + times_i(G2[k]);
-            else v = -G3[k];
+            if (s == 0 && t == 0) v = G3(k);
+            else if (s == 0 && t == 1) v = G1(k) - times_i(G2(k));
+            else if (s == 1 && t == 0) v = G1(k) + times_i(G2(k));
+            else v = -G3(k);
             if (r == c) v.r += diag;
             return v;
         };
-        double *o = pk + 36 * blk;
-#pragma unroll
-        for (int r = 0; r < 6; ++r) o[r] = B(r, r).r;
-        int k = 6;
-#pragma unroll
-        for (int r = 0; r < 6; ++r)
-#pragma unroll
-            for (int c = r + 1; c < 6; ++c) {
-                C<double> v = B(r, c);
-                o[k] = v.r;
-                o[k + 1] = v.i;
-                k += 2;
+        // packed plane j: the diagonal in pairs for j < 3, then one strictly-upper entry each
+        auto plane = [&](int j) {
+            if (j < 3) return make_double2(B(2 * j, 2 * j).r, B(2 * j + 1, 2 * j + 1).r);
+            int r = 0, c = j - 2;  // entry j - 3 of the upper triangle, row-major
+            while (c > 5) {
+                ++r;
+                c = c - 5 + r;
             }
+            const C<double> v = B(r, c);
+            return make_double2(v.r, v.i);
+        };
+        auto put = [&](auto first) {
+            constexpr int J = decltype(first)::value;
+            dst[(18 * blk + J) * kSB] = plane(J);
+            dst[(18 * blk + J + 1) * kSB] = plane(J + 1);
+            dst[(18 * blk + J + 2) * kSB] = plane(J + 2);
+        };
+        switch (w) {
+            case 0: put(std::integral_constant<int, 0>()); break;
+            case 1: put(std::integral_constant<int, 3>()); break;
+            case 2: put(std::integral_constant<int, 6>()); break;
+            case 3: put(std::integral_constant<int, 9>()); break;
+            case 4: put(std::integral_constant<int, 12>()); break;
+            default: put(std::integral_constant<int, 15>()); break;
+        }
     }
-    store_field<double, 72>(out, (uint32_t)i, pk);
 }
 
 // Gauss-Jordan inversion of a 6x6 complex block with partial pivoting (pivot row chosen by
@@ -317,14 +393,13 @@ void clover_apply_t(dirac_ctx *c, void *out, const void *in, int parity, int inv
 
 }  // namespace
 
-void clover_build(dirac_ctx *c, hipStream_t s) {
+void clover_build(dirac_ctx *c, const void *planes, const double *theta, hipStream_t s) {
     PrecFields &f = c->f[DIRAC_F64];
     const double diag = 1.0 / (2.0 * c->p.kappa);
     for (int p = 0; p < 2; ++p) {
-        f.clov[p].alloc((size_t)72 * sizeof(double) * c->g.vhp);
-        k_clover_build<<<grid_for(c->vh), kBlock, 0, s>>>(c->g, p, (const double *)c->U_lex.p,
-                                                          (const double *)c->theta_lex.p, c->p.csw,
-                                                          c->p.csw_qed * c->p.qhat, diag, (double2 *)f.clov[p].p);
+        f.clov[p].alloc_field((size_t)72 * sizeof(double) * c->g.vhp);
+        k_clover_build<<<c->g.vhp / kSB, 384, 0, s>>>(c->g, p, (const double2 *)planes, theta, c->p.csw,
+                                                      c->p.csw_qed * c->p.qhat, diag, (double2 *)f.clov[p].p);
     }
     HIP_CHECK(hipGetLastError());
     c->sap_ready = false;
@@ -337,7 +412,7 @@ void clover_build(dirac_ctx *c, hipStream_t s) {
 int64_t clover_invert_parity(dirac_ctx *c, int p, hipStream_t s) {
     PrecFields &f = c->f[DIRAC_F64];
     require(f.clover_ready, "no clover field");
-    f.clinv[p].alloc((size_t)72 * sizeof(double) * c->g.vhp);
+    f.clinv[p].alloc_field((size_t)72 * sizeof(double) * c->g.vhp);
     c->flags.alloc(256);
     int *bad = (int *)c->flags.p + 8;
     const int big = 0x7fffffff;

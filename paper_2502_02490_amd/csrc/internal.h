@@ -33,20 +33,52 @@ inline void require(bool ok, const std::string &msg, dirac_status s = DIRAC_EINV
     if (!ok) throw Error(s, msg);
 }
 
+// pool.hip: device memory kept for the next context.  pool_take: a block of at least n bytes (*got) on
+// the current device (*dev); pool_give: back to the pool, when no work can touch the block any more;
+// pool_trim: free what the pool holds of a device.
+void *pool_take(size_t n, size_t *got, int *dev);
+void pool_give(void *p, size_t bytes, int dev);
+void pool_trim(int dev);
+
 // Device allocation owned by the context (freed in dirac_destroy).
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
+    int dev = -1;  // its device when it came from the pool
     void alloc(size_t n) {
         if (p && bytes >= n) return;
         release();
-        HIP_CHECK(hipMalloc(&p, n));
+        hipError_t e = hipMalloc(&p, n);
+        if (e == hipErrorOutOfMemory) {  // the pool may hold the memory that is missing
+            (void)hipGetLastError();
+            int d = -1;
+            HIP_CHECK(hipGetDevice(&d));
+            pool_trim(d);
+            e = hipMalloc(&p, n);
+        }
+        if (e != hipSuccess) p = nullptr;
+        HIP_CHECK(e);
         bytes = n;
+    }
+    // the same from the pool, for fields that are written before they are read
+    void alloc_field(size_t n) {
+        if (p && bytes >= n) return;
+        release();
+        p = pool_take(n, &bytes, &dev);
     }
     void release() {
         if (p) (void)hipFree(p);
         p = nullptr;
         bytes = 0;
+        dev = -1;
+    }
+    // back to the pool (if it came from there): only when no work can touch the block any more
+    void retire() {
+        if (p && dev >= 0) pool_give(p, bytes, dev);
+        else if (p) (void)hipFree(p);
+        p = nullptr;
+        bytes = 0;
+        dev = -1;
     }
 };
 
@@ -79,7 +111,6 @@ struct dirac_ctx {
     dirac_params p;
     Geom g;
     int64_t V, vh;
-    dl::DevBuf U_lex, theta_lex;   // FP64 copies of the gauge input (clover rebuild, precision copies)
     dl::PrecFields f[4];           // indexed by dirac_prec
     dl::DevBuf ptc_links[2];       // full FP32 links with phases for the PTC network (built on first use)
     dl::DevBuf sap_rho;            // Schwarz preconditioner: residual, solution, corrections (block order)
@@ -102,7 +133,10 @@ inline int grid_xcd(int64_t n) { return (grid_for(n) + 7) & ~7; }
 size_t link_plane_bytes(dirac_prec pr);  // bytes of one 12-real link plane set, per site and direction
 
 // fields.hip
-void import_links(dirac_ctx *c, hipStream_t s);
+// the LEX gauge field as per-parity planes of complex numbers (link_planes_bytes of scratch)
+void links_to_planes(const dirac_ctx *c, const void *su3_links, void *planes, hipStream_t s);
+inline size_t link_planes_bytes(const Geom &g) { return (size_t)2 * 4 * 9 * 16 * g.vhp; }
+void import_links(dirac_ctx *c, const void *planes, const double *theta, hipStream_t s);
 // openQxD odd-point gauge storage (u_odd [V/2][8][3][3], a_odd [V/2][8] or NULL) to LEX [V][4] arrays
 void openqxd_links_to_lex(const Geom &g, const double *u_odd, const double *a_odd, double *U, double *th,
                           hipStream_t s);
@@ -120,7 +154,7 @@ void clover_import(dirac_ctx *c, const double *user, dirac_layout lay, hipStream
 void clover_export(dirac_ctx *c, double *user, int inverse, dirac_layout lay, hipStream_t s);
 
 // clover.hip
-void clover_build(dirac_ctx *c, hipStream_t s);
+void clover_build(dirac_ctx *c, const void *planes, const double *theta, hipStream_t s);
 int64_t clover_invert_parity(dirac_ctx *c, int parity, hipStream_t s);  // returns first singular Lambda or -1
 void clover_apply(dirac_ctx *c, void *out, const void *in, int parity, int inverse, dirac_prec pr, hipStream_t s,
                   int nrhs = 1);
