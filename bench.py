@@ -38,7 +38,7 @@ HOP_SHAPES = ["k_hop_p bs256 1/CU 2 neighbours/iteration streaming hints (persis
               "k_hop bs256 xcd-order", "k_hop bs256", "k_hop bs128 xcd-order", "k_hop bs64 xcd-order",
               "k_hop_t tt4 (time-tiled LDS)", "k_hop_t tt8 (time-tiled LDS)", "k_hop_p bs512 1/CU (persistent)",
               "k_hop_p bs256 2/CU (persistent)", "k_hop_p bs256 1/CU xcd-regions (persistent)",
-              "k_hop_tp tt4 1/CU (persistent time-tiled)", "k_hop_tp tt8 1/CU (persistent time-tiled)",
+              "k_hop_d (direction-parallel)", "k_hop_p bs512 2/CU streaming hints (persistent)",
               "k_hop_ps bs256 1/CU (XCD slab sweep)", "k_hop_ps bs256 2/CU (XCD slab sweep)",
               "k_hop_ps bs128 2/CU (XCD slab sweep)", "k_hop_p bs256 2/CU 2 neighbours/iteration (persistent)",
               "k_hop_mr 2 RHS/work-item 1/CU streaming hints", "k_hop_mr 4 RHS/work-item 1/CU streaming hints",
@@ -74,7 +74,7 @@ HOP_CLOV_KERNEL_32C64 = {
     2: ("k_hop_p<double, 0, 2, 256, 0, 1, true>", 131072), 3: ("k_hop_p<double, 0, 2, 256, 0, 1, false>", 65536),
     4: ("k_hop_p<double, 0, 2, 256, 0, 2, false>", 65536), 11: ("k_hop_p<double, 0, 2, 512, 0, 1, false>", 131072),
     12: ("k_hop_p<double, 0, 2, 256, 0, 1, false>", 131072), 13: ("k_hop_p<double, 0, 2, 256, 1, 1, false>", 65536),
-    14: ("k_hop_tp<double, 0, 2, 4>", 65536), 15: ("k_hop_tp<double, 0, 2, 8>", 131072),
+    15: ("k_hop_p<double, 0, 2, 512, 0, 1, true>", 262144),
     16: ("k_hop_ps<double, 0, 2, 256, 1, false>", 65536), 17: ("k_hop_ps<double, 0, 2, 256, 1, false>", 131072),
     18: ("k_hop_ps<double, 0, 2, 128, 1, false>", 65536), 19: ("k_hop_p<double, 0, 2, 256, 0, 2, false>", 131072),
     28: ("k_hop_p<double, 0, 2, 256, 0, 4, true>", 65536), 29: ("k_hop_p<double, 0, 2, 256, 0, 4, true>", 131072),
@@ -791,10 +791,10 @@ def main():
     try:
         with open(os.environ["DIRAC_TUNE_CACHE"]) as fh:
             choices = json.load(fh)
-        key = "hop-v2|f64|dag0|mode2|" + "x".join(map(str, DIMS)) + "|nrhs1|gfx950"
+        key = "hop-v3|f64|dag0|mode2|" + "x".join(map(str, DIMS)) + "|nrhs1|gfx950"
         chosen = int(choices[key])
         extra["tuned_hop_shapes"] = {k.split("|", 1)[1].rsplit("|", 1)[0]: HOP_SHAPES[v] for k, v in choices.items()
-                                     if k.startswith("hop-v2|") and "x".join(map(str, DIMS)) in k}
+                                     if k.startswith("hop-v3|") and "x".join(map(str, DIMS)) in k}
     except (OSError, KeyError, ValueError) as e:
         log(f"[bench] tuner choice not readable: {e}")
     # every launch shape of the hop kernel, FP64 Schur (the tuner's choice is what the timed loop used)

@@ -342,6 +342,8 @@ dirac_status dirac_apply(dirac_ctx *c, void *out, const void *in, dirac_prec pr,
     check_no_alias(out, nb, in, nb);
     if (lay == DIRAC_LAYOUT_NATIVE) {
         dl::full_apply(c, out, in, dagger != 0, pr, s);
+    } else if (dl::direct_layout(c, out, in)) {
+        dl::full_apply_direct(c, out, in, lay, dagger != 0, pr, s);
     } else {
         dl::PrecFields &f = c->f[pr];
         f.user_in.alloc(native_bytes(c, pr, 0));
@@ -367,6 +369,8 @@ dirac_status dirac_apply_eo(dirac_ctx *c, void *out, const void *in, dirac_prec 
     check_no_alias(out, nb, in, nb);
     if (lay == DIRAC_LAYOUT_NATIVE) {
         dl::schur_apply(c, out, in, dagger != 0, pr, s);
+    } else if (dl::direct_layout(c, out, in)) {
+        dl::schur_apply_direct(c, out, in, lay, dagger != 0, pr, s);
     } else {
         dl::PrecFields &f = c->f[pr];
         f.user_in.alloc(native_bytes(c, pr, 0));

@@ -241,6 +241,18 @@ DEV void lex_coords(const Geom &g, int lam, int x[4]) {
     x[1] = r % g.L[1];
     x[0] = r / g.L[1];
 }
+// Offset, in 16-byte vectors, of the first of the NP vectors of site (par, i) with coordinates x of a spinor in
+// layout lay (dirac_layout; half: a vector of one parity, the base of a NATIVE vector being its parity's),
+// and the distance of consecutive vectors of a site.
+template <int NP>
+DEV size_t spinor_offset(const Geom &g, int lay, int half, int par, int i, const int x[4]) {
+    if (lay == 2) return (size_t)(half ? 0 : par) * NP * g.vhp + (size_t)(i >> 6) * NP * kSB + (i & (kSB - 1));  // NATIVE
+    if (lay == 0) return (size_t)lex_index(g, x) * NP;                   // LEX
+    if (lay == 1) return (size_t)(i + (half ? 0 : par * g.vh)) * NP;     // EO
+    return (size_t)(ipt_index(g, x) - (half ? (int64_t)par * g.vh : 0)) * NP;  // OPENQXD
+}
+DEV int spinor_stride(int lay) { return lay == 2 ? kSB : 1; }
+
 DEV int wrap_up(int v, int L) { return v + 1 == L ? 0 : v + 1; }
 DEV int wrap_dn(int v, int L) { return v == 0 ? L - 1 : v - 1; }
 

@@ -8,4 +8,5 @@ void hop_prec_bf16(dirac_ctx *c, void *out, const void *in, const void *chi, int
     hop_t<__hip_bfloat16>(c, out, in, chi, p, mode, coef, dagger, DIRAC_BF16, s, nrhs, active, no_tune);
 }
 
+void hop_dir_bf16(dirac_ctx *c, const HopDirCall &k, hipStream_t s) { hop_dir_t<__hip_bfloat16>(c, k, s); }
 }  // namespace dl

@@ -115,25 +115,38 @@ DEV void project_dir_n(const C<T> psi[12], C<T> h[6]) {
     }
 }
 
-template <typename T, int DAG, int N>
-DEV void apply_dir_n(const C<T> h[6], const C<T> u[6], const C<T> r2[3], T co, T si, C<T> acc[12]) {
+// link_dir_n: the link product w of the half-spinor h.  add_dir_row: component K = 3 spin + colour of the
+// reconstruction of w added to acc (w may be any indexable container of the six components).
+template <typename T, int N>
+DEV void link_dir_n(const C<T> h[6], const C<T> u[6], const C<T> r2[3], T co, T si, C<T> w[6]) {
+    if constexpr (N & 1) link_adj_mul_r2(u, r2, co, si, h, w);
+    else link_mul_r2(u, r2, co, si, h, w);
+}
+
+template <typename T, int DAG, int N, int K, typename W>
+DEV void add_dir_row(const W &w, C<T> &acc) {
     constexpr int mu = N >> 1, back = N & 1;
     constexpr int SG = (DAG ? 1 : -1) * (back ? -1 : 1);
     constexpr bool SW = (mu == 1 || mu == 2);
     constexpr int C0R = (mu == 0 || mu == 2) ? -1 : 0, C0I = (mu == 1 || mu == 3) ? -1 : 0;
     constexpr int C1R = mu == 0 ? -1 : mu == 2 ? 1 : 0, C1I = mu == 1 ? -1 : mu == 3 ? 1 : 0;
-    C<T> w[6];
-    if constexpr (back) link_adj_mul_r2(u, r2, co, si, h, w);
-    else link_mul_r2(u, r2, co, si, h, w);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        acc[c] = acc[c] + w[c];
-        acc[3 + c] = acc[3 + c] + w[3 + c];
-        const C<T> t0 = unit_mul<C0R, -C0I>(w[c]);      // conj(c_0) w_0 -> lower spin p_0
-        const C<T> t1 = unit_mul<C1R, -C1I>(w[3 + c]);  // conj(c_1) w_1 -> lower spin p_1
-        acc[6 + c] = add_signed<SG>(acc[6 + c], SW ? t1 : t0);
-        acc[9 + c] = add_signed<SG>(acc[9 + c], SW ? t0 : t1);
+    if constexpr (K < 6) {
+        acc = acc + w[K];
+    } else {
+        constexpr int c = K % 3;
+        if constexpr ((K < 9) != SW) acc = add_signed<SG>(acc, unit_mul<C0R, -C0I>(w[c]));  // conj(c_0) w_0 -> lower spin p_0
+        else acc = add_signed<SG>(acc, unit_mul<C1R, -C1I>(w[3 + c]));                      // conj(c_1) w_1 -> lower spin p_1
     }
+}
+
+template <typename T, int DAG, int N>
+DEV void apply_dir_n(const C<T> h[6], const C<T> u[6], const C<T> r2[3], T co, T si, C<T> acc[12]) {
+    C<T> w[6];
+    link_dir_n<T, N>(h, u, r2, co, si, w);
+    add_dir_row<T, DAG, N, 0>(w, acc[0]); add_dir_row<T, DAG, N, 1>(w, acc[1]); add_dir_row<T, DAG, N, 2>(w, acc[2]);
+    add_dir_row<T, DAG, N, 3>(w, acc[3]); add_dir_row<T, DAG, N, 4>(w, acc[4]); add_dir_row<T, DAG, N, 5>(w, acc[5]);
+    add_dir_row<T, DAG, N, 6>(w, acc[6]); add_dir_row<T, DAG, N, 7>(w, acc[7]); add_dir_row<T, DAG, N, 8>(w, acc[8]);
+    add_dir_row<T, DAG, N, 9>(w, acc[9]); add_dir_row<T, DAG, N, 10>(w, acc[10]); add_dir_row<T, DAG, N, 11>(w, acc[11]);
 }
 
 template <typename T, int DAG, int N>

@@ -8,4 +8,5 @@ void hop_prec_f32(dirac_ctx *c, void *out, const void *in, const void *chi, int 
     hop_t<float>(c, out, in, chi, p, mode, coef, dagger, DIRAC_F32, s, nrhs, active, no_tune);
 }
 
+void hop_dir_f32(dirac_ctx *c, const HopDirCall &k, hipStream_t s) { hop_dir_t<float>(c, k, s); }
 }  // namespace dl

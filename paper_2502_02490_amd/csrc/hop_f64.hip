@@ -8,4 +8,5 @@ void hop_prec_f64(dirac_ctx *c, void *out, const void *in, const void *chi, int 
     hop_t<double>(c, out, in, chi, p, mode, coef, dagger, DIRAC_F64, s, nrhs, active, no_tune);
 }
 
+void hop_dir_f64(dirac_ctx *c, const HopDirCall &k, hipStream_t s) { hop_dir_t<double>(c, k, s); }
 }  // namespace dl

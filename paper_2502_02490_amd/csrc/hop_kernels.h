@@ -17,6 +17,7 @@
 
 #include "dirac_ops.h"
 #include "hop_core.h"
+#include "hop_launch.h"
 #include "internal.h"
 
 namespace dl {
@@ -746,43 +747,222 @@ __global__ __launch_bounds__(64 * TT) void k_hop_t(HopArgs<S> a) {
     hop_site<S, DAG, MODE>(a, ii, tile, w + 1);
 }
 
-// Persistent form of the time-tiled kernel: the grid sweeps the tiles in order, spatial block
-// fastest, so one band of TT time slices is in flight at a time.
-template <typename S, int DAG, int MODE, int TT>
-__global__ __launch_bounds__(64 * TT) void k_hop_tp(HopArgs<S> a, int nwg) {
+// Direction-parallel kernel for lattices too small to fill the card: a work-group of eight wavefronts
+// takes 64 sites, one neighbour direction per wavefront, so a site's eight neighbours are fetched and
+// multiplied at once instead of one after the other.  The link products meet in LDS; each wavefront
+// then sums one or two of the twelve spin-colour components over the directions in the order of the
+// other kernels, and applies one row of the clover block in the order of block_mul, so the results are
+// bitwise theirs.  The rows' clover entries and chi are loaded before the neighbours.
+// Spinors are read and written in the layout of the caller's vectors (lin for in and chi, lout for out;
+// a NATIVE intermediate keeps `in` NATIVE with chi_lay for chi), so a call on a small lattice needs no
+// conversion passes; with np = 2 one launch computes both parities of a full vector.
+// Bound by latency (two dependent memory accesses and two barriers, 6 us a launch).  At 8^4 in FP64 the
+// Schur operator on an EO vector takes 14.8 us, against 27.8 us for the best other shape between
+// conversion passes, D on a LEX vector 13 against 36 us; on NATIVE vectors it is the faster shape up to
+// about 10,000 sites per parity (12^4: 21 against 23 us in FP64, 16^4: 44 against 31 us).
+template <typename S>
+struct HopDirArgs {
+    Geom g;
+    int p, np;                     // first output parity, parities computed
+    int nrhs;
+    size_t vs;                     // 16-byte vectors between right-hand sides (NATIVE)
+    const int *active;
+    int in_lay, chi_lay, out_lay;  // dirac_layout of in, chi, out
+    int half;                      // vectors of one parity (else full vectors)
+    const typename St<S>::vec *in, *chi;
+    typename St<S>::vec *out;
+    const typename Lk<S>::vec *links[2];
+    const typename Lk<S>::om *omega[2];
+    const typename St<S>::vec *clov[2];
+    typename St<S>::acc coef;
+};
+
+// reals 2 k, 2 k + 1 of a site whose vectors start at q, `ps` apart
+template <typename S>
+DEV C<typename St<S>::acc> ld_pair(const typename St<S>::vec *q, int ps, int k) {
+    using T = typename St<S>::acc;
+    constexpr int W = St<S>::W;
+    const S *r = reinterpret_cast<const S *>(q + (size_t)(2 * k / W) * ps) + (2 * k) % W;
+    if constexpr (W == 2) {
+        const double2 v = *reinterpret_cast<const double2 *>(r);
+        return mk(v.x, v.y);
+    } else if constexpr (W == 4) {
+        const float2 v = *reinterpret_cast<const float2 *>(r);
+        return mk(v.x, v.y);
+    } else {
+        uint4 v = make_uint4(*reinterpret_cast<const uint32_t *>(r), 0u, 0u, 0u);
+        T o[8];
+        St<S>::unpack(v, o);
+        return mk(o[0], o[1]);
+    }
+}
+template <typename S>
+DEV void st_pair(typename St<S>::vec *q, int ps, int k, C<typename St<S>::acc> v) {
+    using T = typename St<S>::acc;
+    constexpr int W = St<S>::W;
+    S *r = reinterpret_cast<S *>(q + (size_t)(2 * k / W) * ps) + (2 * k) % W;
+    if constexpr (W == 2) *reinterpret_cast<double2 *>(r) = make_double2(v.r, v.i);
+    else if constexpr (W == 4) *reinterpret_cast<float2 *>(r) = make_float2(v.r, v.i);
+    else {
+        const T o[8] = {v.r, v.i, T(0), T(0), T(0), T(0), T(0), T(0)};
+        *reinterpret_cast<uint32_t *>(r) = St<S>::pack(o).x;
+    }
+}
+
+template <typename S, int DAG, int MODE>
+__global__ __launch_bounds__(512, 2) void k_hop_d(HopDirArgs<S> a) {
+    using T = typename St<S>::acc;
     using V = typename St<S>::vec;
-    constexpr int NP = 24 / St<S>::W;
-    __shared__ V tile[(TT + 2) * NP * kSB];
-    const int nsb = a.g.vh / (a.g.L[0] * kSB);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & (kSB - 1);
-#pragma nounroll
-    for (int lb = blockIdx.x; lb < nwg; lb += gridDim.x) {
-        const int rhs = lb % a.nrhs, wg = lb / a.nrhs;
-        if (a.active && !a.active[rhs]) continue;  // uniform over the work-group
-        const int sb = wg % nsb, t0 = (wg / nsb) * TT;
-        HopArgs<S> b = a;
-        if (rhs) {
-            b.in += rhs * a.vs;
-            b.out += rhs * a.vs;
-            if (b.chi) b.chi += rhs * a.vs;
-        }
-        auto stage = [&](int slot, int t) {
-            const V *src = b.in + ((size_t)(t * nsb + sb) * NP) * kSB + lane;
-            V *dst = tile + (size_t)slot * NP * kSB + lane;
+    constexpr int NP = 24 / St<S>::W, CP = 72 / St<S>::W;
+    __shared__ C<T> s_w[8][6][kSB];
+    __shared__ C<T> s_y[MODE == HOP_INV ? 12 : 1][kSB];
+    const int lane = threadIdx.x & (kSB - 1), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int rhs = (int)blockIdx.x % a.nrhs, b = (int)blockIdx.x / a.nrhs;
+    if (a.active && !a.active[rhs]) return;
+    const int nb = a.g.vhp / kSB;
+    const int p = a.np == 2 ? b >= nb : a.p, blk = a.np == 2 ? b % nb : b;
+    const int i = min(blk * kSB + lane, a.g.vh - 1);  // lanes past the end repeat the last site; not stored
+    int x[4];
+    site_coords(a.g, i, p, x);
+    const V *in = a.in + rhs * a.vs;
+    const size_t own = spinor_offset<NP>(a.g, a.out_lay, a.half, p, i, x);
+    // row K of a clover block (diagonal d, the other entries e in the order block_mul uses them) and chi, for
+    // component K of the site
+    const V *cl = MODE != HOP_PLAIN ? site_ptr(p ? a.clov[1] : a.clov[0], (uint32_t)i, CP) : nullptr;
+    auto load_row = [&](auto kc, T &d, C<T> (&e)[5], C<T> (&chi)[6]) {
+        constexpr int K = decltype(kc)::value, R = K % 6, O = 18 * (K / 6);  // row, first pair of the block
+        if constexpr (MODE != HOP_PLAIN) {
+            const C<T> dd = ld_pair<S>(cl, kSB, O + R / 2);
+            d = R % 2 ? dd.i : dd.r;
+            int n = 0;
 #pragma unroll
-            for (int k = 0; k < NP; ++k) dst[k * kSB] = src[k * kSB];
+            for (int c = 0; c < 6; ++c) {
+                if (c == R) continue;
+                const int lo = c < R ? c : R, hi = c < R ? R : c;
+                e[n++] = ld_pair<S>(cl, kSB, O + 3 + lo * (11 - lo) / 2 + hi - lo - 1);
+            }
+            if constexpr (MODE == HOP_CLOV) {
+                const V *q = a.chi + rhs * a.vs + spinor_offset<NP>(a.g, a.chi_lay, a.half, p, i, x);
+#pragma unroll
+                for (int c = 0; c < 6; ++c) chi[c] = ld_pair<S>(q, spinor_stride(a.chi_lay), 6 * (K / 6) + c);
+            }
+        }
+    };
+    auto dir = [&](auto nc) {
+        constexpr int N = decltype(nc)::value, mu = N >> 1, back = N & 1;
+        int y[4] = {x[0], x[1], x[2], x[3]};
+        const bool cross = back ? y[mu] == 0 : y[mu] + 1 == a.g.L[mu];
+        y[mu] = back ? wrap_dn(y[mu], a.g.L[mu]) : wrap_up(y[mu], a.g.L[mu]);
+        y[1] = cstar_x1(a.g, mu, cross, y[1]);
+        const V *q = in + spinor_offset<NP>(a.g, a.in_lay, a.half, 1 - p, half_index(a.g, y), y);
+        const int ps = spinor_stride(a.in_lay);
+        V raw[NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) raw[k] = q[(size_t)k * ps];
+        HopArgs<S> l;
+        l.g = a.g;
+        l.links = p ? a.links[1] : a.links[0];
+        l.omega = p ? a.omega[1] : a.omega[0];
+        C<T> u[6], r2[3], psi[12], h[6], o[6];
+        T co, si;
+        load_link<S, false>(l, N, (uint32_t)i, u, co, si);
+        third_row(u, r2);
+        T r[24];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) St<S>::unpack(raw[k], r + k * St<S>::W);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) psi[k] = mk(r[2 * k], r[2 * k + 1]);
+        project_dir_n<T, DAG, N>(psi, h);
+        link_dir_n<T, N>(h, u, r2, co, si, o);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) s_w[N][k][lane] = o[k];
+    };
+    // the hopping sum of component K, scaled
+    auto sum = [&](auto kc) -> C<T> {
+        constexpr int K = decltype(kc)::value;
+        struct At {
+            const C<T> (*q)[kSB];
+            int lane;
+            DEV C<T> operator[](int k) const { return q[k][lane]; }
         };
-        __syncthreads();  // the previous tile has been consumed
-        stage(w + 1, t0 + w);
-        if (w == 0) stage(0, t0 == 0 ? a.g.L[0] - 1 : t0 - 1);
-        if (w == TT - 1) stage(TT + 1, t0 + TT == a.g.L[0] ? 0 : t0 + TT);
+        C<T> acc = mk(T(0), T(0));
+        add_dir_row<T, DAG, 0, K>(At{s_w[0], lane}, acc);
+        add_dir_row<T, DAG, 1, K>(At{s_w[1], lane}, acc);
+        add_dir_row<T, DAG, 2, K>(At{s_w[2], lane}, acc);
+        add_dir_row<T, DAG, 3, K>(At{s_w[3], lane}, acc);
+        add_dir_row<T, DAG, 4, K>(At{s_w[4], lane}, acc);
+        add_dir_row<T, DAG, 5, K>(At{s_w[5], lane}, acc);
+        add_dir_row<T, DAG, 6, K>(At{s_w[6], lane}, acc);
+        add_dir_row<T, DAG, 7, K>(At{s_w[7], lane}, acc);
+        return a.coef * acc;
+    };
+    // row K of the clover block times v (six components)
+    auto row_mul = [&](auto kc, T d, const C<T> (&e)[5], const C<T> (&v)[6]) -> C<T> {
+        constexpr int R = decltype(kc)::value % 6;
+        C<T> o = d * v[R];
+        int n = 0;
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            if (c == R) continue;
+            if (c < R) cmadd(o, e[n], v[c]);  // B_Rc = conj(B_cR)
+            else madd(o, e[n], v[c]);
+            ++n;
+        }
+        return o;
+    };
+    auto put = [&](auto kc, C<T> v) {
+        if (blk * kSB + lane < a.g.vh)
+            st_pair<S>(a.out + rhs * a.vs + own, spinor_stride(a.out_lay), decltype(kc)::value, v);
+    };
+    // wavefront w: direction w, then component w and, for w < 4, component w + 8
+    auto work = [&](auto wc) {
+        constexpr int Wv = decltype(wc)::value;
+        constexpr bool two = Wv < 4;
+        using K0 = std::integral_constant<int, Wv>;
+        using K1 = std::integral_constant<int, two ? Wv + 8 : Wv>;
+        T d0 = T(0), d1 = T(0);
+        C<T> e0[5], e1[5], c0[6], c1[6];
+        load_row(K0(), d0, e0, c0);
+        if constexpr (two) load_row(K1(), d1, e1, c1);
+        dir(wc);
         __syncthreads();
-        hop_site<S, DAG, MODE>(b, ((t0 + w) * nsb + sb) * kSB + lane, tile, w + 1);
+        const C<T> y0 = sum(K0());
+        C<T> y1 = y0;
+        if constexpr (two) y1 = sum(K1());
+        if constexpr (MODE == HOP_PLAIN) {
+            put(K0(), y0);
+            if constexpr (two) put(K1(), y1);
+        } else if constexpr (MODE == HOP_CLOV) {
+            put(K0(), y0 + row_mul(K0(), d0, e0, c0));
+            if constexpr (two) put(K1(), y1 + row_mul(K1(), d1, e1, c1));
+        } else {
+            s_y[K0::value][lane] = y0;
+            if constexpr (two) s_y[K1::value][lane] = y1;
+            __syncthreads();
+            auto finish = [&](auto kc, T d, const C<T> (&e)[5]) {
+                C<T> v[6];
+#pragma unroll
+                for (int c = 0; c < 6; ++c) v[c] = s_y[6 * (decltype(kc)::value / 6) + c][lane];
+                put(kc, row_mul(kc, d, e, v));
+            };
+            finish(K0(), d0, e0);
+            if constexpr (two) finish(K1(), d1, e1);
+        }
+    };
+    switch (w) {
+        case 0: work(std::integral_constant<int, 0>()); break;
+        case 1: work(std::integral_constant<int, 1>()); break;
+        case 2: work(std::integral_constant<int, 2>()); break;
+        case 3: work(std::integral_constant<int, 3>()); break;
+        case 4: work(std::integral_constant<int, 4>()); break;
+        case 5: work(std::integral_constant<int, 5>()); break;
+        case 6: work(std::integral_constant<int, 6>()); break;
+        default: work(std::integral_constant<int, 7>()); break;
     }
 }
 
 struct HopShape {
-    int bs, xcd, tt, pers, slab, npi, nt, mr, rb, pf, x1s, cw, cr, db;
+    int bs, xcd, tt, pers, slab, npi, nt, mr, rb, pf, x1s, cw, cr, db, dir;
 };
 // Shape 0 is the default (used when tuning is off, and inside a graph capture before the key
 // was tuned): the persistent sweep, one 256-wide work-group per compute unit, two neighbours per
@@ -794,12 +974,12 @@ struct HopShape {
 // its next-direction prefetch; x1s: the x1-split sweep (or block order); cw: the right-hand-side
 // blocked column walk with cw wavefronts per work-group and at most cr right-hand sides each,
 // pers work-groups per compute unit wanted (16-bit and FP32 storage only), db: its LDS staging
-// double-buffered.
+// double-buffered; dir: the direction-parallel kernel.
 const HopShape kShapes[] = {
     {256, 0, 0, 1, 0, 2, 1, 1}, {256, 0, 0, 1, 0, 1, 1, 1}, {256, 0, 0, 2, 0, 1, 1, 1}, {256, 0, 0, 1, 0, 1, 0, 1},
     {256, 0, 0, 1, 0, 2, 0, 1}, {256, 1, 0, 0, 0, 1, 0, 1}, {256, 0, 0, 0, 0, 1, 0, 1}, {128, 1, 0, 0, 0, 1, 0, 1},
     {64, 1, 0, 0, 0, 1, 0, 1},  {256, 1, 4, 0, 0, 1, 0, 1}, {512, 1, 8, 0, 0, 1, 0, 1}, {512, 0, 0, 1, 0, 1, 0, 1},
-    {256, 0, 0, 2, 0, 1, 0, 1}, {256, 1, 0, 1, 0, 1, 0, 1}, {256, 0, 4, 1, 0, 1, 0, 1}, {512, 0, 8, 1, 0, 1, 0, 1},
+    {256, 0, 0, 2, 0, 1, 0, 1}, {256, 1, 0, 1, 0, 1, 0, 1}, {512, 0, 0, 0, 0, 1, 0, 1, 0, 0, 0, 0, 0, 0, 1}, {512, 0, 0, 2, 0, 1, 1, 1},
     {256, 0, 0, 1, 1, 1, 0, 1}, {256, 0, 0, 2, 1, 1, 0, 1}, {128, 0, 0, 2, 1, 1, 0, 1}, {256, 0, 0, 2, 0, 2, 0, 1},
     {256, 0, 0, 1, 0, 1, 1, 2}, {256, 0, 0, 1, 0, 1, 1, 4}, {256, 0, 0, 2, 0, 1, 1, 2},
     {256, 0, 0, 0, 0, 1, 1, 1, 4, 0}, {512, 0, 0, 0, 0, 1, 1, 1, 8, 0}, {256, 0, 0, 0, 0, 1, 1, 1, 4, 1},
@@ -892,13 +1072,30 @@ void launch_multi(HopArgs<S> a, int per_cu, hipStream_t s) {
     k_hop_mr<S, DAG, MODE, 256, NR, true><<<grid, 256, 0, s>>>(a, nlog);
 }
 
-template <typename S, int DAG, int MODE, int TT>
-void launch_tiled_persistent(HopArgs<S> a, int per_cu, hipStream_t s) {
-    const int nwg = (a.g.L[0] / TT) * (a.g.vh / (a.g.L[0] * kSB)) * a.nrhs;
-    const int grid = std::min(nwg, per_cu * compute_units());
-    a.xcd = 0;
-    a.nb8 = grid;
-    k_hop_tp<S, DAG, MODE, TT><<<grid, 64 * TT, 0, s>>>(a, nwg);
+// The direction-parallel kernel on NATIVE half vectors (the arguments of the other shapes).
+template <typename S>
+HopDirArgs<S> dir_args(const HopArgs<S> &a) {
+    HopDirArgs<S> d{};
+    d.g = a.g;
+    d.p = a.p;
+    d.np = 1;
+    d.nrhs = a.nrhs;
+    d.vs = a.vs;
+    d.active = a.active;
+    d.in_lay = d.chi_lay = d.out_lay = DIRAC_LAYOUT_NATIVE;
+    d.half = 1;
+    d.in = a.in;
+    d.chi = a.chi;
+    d.out = a.out;
+    d.links[a.p] = a.links;
+    d.omega[a.p] = a.omega;
+    d.clov[a.p] = a.clov;
+    d.coef = a.coef;
+    return d;
+}
+template <typename S, int DAG, int MODE>
+void launch_dir(const HopDirArgs<S> &d, hipStream_t s) {
+    k_hop_d<S, DAG, MODE><<<d.g.vhp / kSB * d.np * d.nrhs, 512, 0, s>>>(d);
 }
 
 template <typename S, int DAG, int MODE, int TT>
@@ -955,7 +1152,9 @@ void launch_hop(const HopArgs<S> &a, int shape, hipStream_t s) {
         (h.x1s && !h.cw && !x1split_ok(a.g, h.rb != 0)) ||
         (h.cw && (std::is_same<S, double>::value || !column_ok(a.g) || a.nrhs > h.cw * h.cr)))
         h = kShapes[0];  // does not fit
-    if (h.cw) {
+    if (h.dir) {
+        launch_dir<S, DAG, MODE>(dir_args(a), s);
+    } else if (h.cw) {
         if constexpr (!std::is_same<S, double>::value) {
             if (h.cw == 12 && h.db) launch_rbc<S, DAG, MODE, 12, 1, true>(a, h.pers, h.x1s != 0, s);
             else if (h.cw == 8 && h.db) launch_rbc<S, DAG, MODE, 8, 2, true>(a, h.pers, h.x1s != 0, s);
@@ -975,13 +1174,8 @@ void launch_hop(const HopArgs<S> &a, int shape, hipStream_t s) {
             else launch_multi<S, DAG, MODE, 4>(a, h.pers, s);
         }
     } else if (h.tt) {
-        if (h.pers) {
-            if (h.tt == 4) launch_tiled_persistent<S, DAG, MODE, 4>(a, h.pers, s);
-            else launch_tiled_persistent<S, DAG, MODE, 8>(a, h.pers, s);
-        } else {
-            if (h.tt == 4) launch_tiled<S, DAG, MODE, 4>(a, s);
-            else launch_tiled<S, DAG, MODE, 8>(a, s);
-        }
+        if (h.tt == 4) launch_tiled<S, DAG, MODE, 4>(a, s);
+        else launch_tiled<S, DAG, MODE, 8>(a, s);
     } else if (h.x1s) {
         if (h.npi == 4) launch_x1split<S, DAG, MODE, 256, 4>(a, h.pers, s);
         else if (h.bs == 256) launch_x1split<S, DAG, MODE, 256, 2>(a, h.pers, s);
@@ -992,7 +1186,8 @@ void launch_hop(const HopArgs<S> &a, int shape, hipStream_t s) {
         else if (h.bs == 256) launch_slab<S, DAG, MODE, 256>(a, h.pers, s);
         else launch_slab<S, DAG, MODE, 128>(a, h.pers, s);
     } else if (h.pers) {
-        if (h.bs == 512) launch_persistent<S, DAG, MODE, 512>(a, h.pers, h.xcd, s);
+        if (h.bs == 512 && h.nt) launch_persistent<S, DAG, MODE, 512, 1, true>(a, h.pers, 0, s);
+        else if (h.bs == 512) launch_persistent<S, DAG, MODE, 512>(a, h.pers, h.xcd, s);
         else if (h.nt && h.npi == 4) launch_persistent<S, DAG, MODE, 256, 4, true>(a, h.pers, 0, s);
         else if (h.nt && h.npi == 2) launch_persistent<S, DAG, MODE, 256, 2, true>(a, h.pers, 0, s);
         else if (h.nt) launch_persistent<S, DAG, MODE, 256, 1, true>(a, h.pers, 0, s);
@@ -1037,7 +1232,7 @@ void hop_t(dirac_ctx *c, void *out, const void *in, const void *chi, int p, HopM
         HIP_CHECK(hipGetLastError());
     };
     char key[160];
-    snprintf(key, sizeof key, "hop-v2|%s|dag%d|mode%d|%dx%dx%dx%d|nrhs%d", prec_name(pr), dagger, (int)mode,
+    snprintf(key, sizeof key, "hop-v3|%s|dag%d|mode%d|%dx%dx%dx%d|nrhs%d", prec_name(pr), dagger, (int)mode,
              c->g.L[0], c->g.L[1], c->g.L[2], c->g.L[3], nrhs);
     if (no_tune) {
         // no timing runs (they create events): the shape tuned earlier for this key, else shape 0
@@ -1046,6 +1241,33 @@ void hop_t(dirac_ctx *c, void *out, const void *in, const void *chi, int p, HopM
     } else {
         launch(tuned_choice(key, num_shapes<S>(), launch, s));
     }
+}
+
+// The direction-parallel kernel on vectors in the caller's layouts.
+template <typename S>
+void hop_dir_t(dirac_ctx *c, const HopDirCall &k, hipStream_t s) {
+    PrecFields &f = c->f[k.pr];
+    HopDirArgs<S> d{};
+    d.g = c->g;
+    d.p = k.p;
+    d.np = k.np;
+    d.nrhs = 1;
+    d.in_lay = k.in_lay;
+    d.chi_lay = k.chi_lay;
+    d.out_lay = k.out_lay;
+    d.half = k.half;
+    d.in = (const typename St<S>::vec *)k.in;
+    d.chi = (const typename St<S>::vec *)k.chi;
+    d.out = (typename St<S>::vec *)k.out;
+    for (int p = 0; p < 2; ++p) {
+        d.links[p] = (const typename Lk<S>::vec *)f.links[p].p;
+        d.omega[p] = (const typename Lk<S>::om *)f.omega[p].p;
+        d.clov[p] = (const typename St<S>::vec *)(k.mode == HOP_INV ? f.clinv[p].p : f.clov[p].p);
+    }
+    d.coef = (typename St<S>::acc)k.coef;
+    if (k.mode == HOP_INV) k.dagger ? launch_dir<S, 1, HOP_INV>(d, s) : launch_dir<S, 0, HOP_INV>(d, s);
+    else k.dagger ? launch_dir<S, 1, HOP_CLOV>(d, s) : launch_dir<S, 0, HOP_CLOV>(d, s);
+    HIP_CHECK(hipGetLastError());
 }
 
 }  // namespace

@@ -174,6 +174,12 @@ void schur_apply(dirac_ctx *c, void *out_e, const void *in_e, int dagger, dirac_
 void schur_apply_into(dirac_ctx *c, void *out_e, const void *in_e, void *tmp, int dagger, dirac_prec pr,
                       hipStream_t s, int nrhs, const int *active, bool no_alloc);
 void full_apply(dirac_ctx *c, void *out, const void *in, int dagger, dirac_prec pr, hipStream_t s);
+// the same on vectors in any layout without conversion passes, for lattices and vectors that direct_layout accepts
+bool direct_layout(const dirac_ctx *c, const void *out, const void *in);
+void schur_apply_direct(dirac_ctx *c, void *out_e, const void *in_e, dirac_layout lay, int dagger, dirac_prec pr,
+                        hipStream_t s);
+void full_apply_direct(dirac_ctx *c, void *out, const void *in, dirac_layout lay, int dagger, dirac_prec pr,
+                       hipStream_t s);
 
 // noalloc.hip: D-hat with the intermediate in the library's static device buffer (allocates nothing)
 void schur_apply_noalloc(dirac_ctx *c, void *out_e, const void *in_e, int dagger, dirac_prec pr, hipStream_t s);
