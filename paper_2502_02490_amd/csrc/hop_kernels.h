@@ -449,8 +449,8 @@ __global__ __launch_bounds__(64 * NW) void k_hop_rb(HopArgs<S> a) {
 // All waves of an XCD work on neighbouring columns at the same slice, so the spatial neighbours of
 // slice t + 1 are read one slice after their +t loads.  Work-groups: spatial block fastest, then
 // chunk; with X1S the spatial blocks of XCD k (work-group index = k mod 8) are the k-th eighth of
-// a slice (its x1 range), so the x2 and x3 neighbours are on the same XCD.  Needs whole blocks per
-// time slice; the host checks the fit.
+// a slice (rounded up to blocks: its x1 range), so the x2 and x3 neighbours are on the same XCD.
+// Needs whole blocks per time slice; the host checks the fit.
 template <typename T, int DAG, int N>
 DEV void apply_lds(const T *lk, int lane, const C<T> h[6], C<T> acc[12]) {
     constexpr int NL = 20;
@@ -473,7 +473,7 @@ DEV void dir_lds(const T *lk, int lane, const C<T> psi[12], C<T> acc[12]) {
 // DB: the staging data is double-buffered in LDS, so a slice's data is written while the previous
 // slice is still being computed from the other buffer (one barrier per slice instead of two).
 template <typename S, int DAG, int MODE, int NW, int R, bool X1S, bool DB>
-__global__ __launch_bounds__(64 * NW) void k_hop_rbc(HopArgs<S> a, int tc) {
+__global__ __launch_bounds__(64 * NW) void k_hop_rbc(HopArgs<S> a, int tcmax) {
     using T = typename St<S>::acc;
     using V = typename St<S>::vec;
     using LV = typename Lk<S>::vec;
@@ -491,14 +491,15 @@ __global__ __launch_bounds__(64 * NW) void k_hop_rbc(HopArgs<S> a, int tc) {
     const int nsb = a.g.vh / (a.g.L[0] * kSB);  // spatial blocks per time slice
     int sb, ch;
     if constexpr (X1S) {
-        const int per = nsb >> 3, j = (int)blockIdx.x >> 3;
+        const int per = (nsb + 7) >> 3, j = (int)blockIdx.x >> 3;
         sb = ((int)blockIdx.x & 7) * per + j % per;
         ch = j / per;
+        if (sb >= nsb) return;  // the last XCD's part may be shorter; uniform over the work-group
     } else {
         sb = (int)blockIdx.x % nsb;
         ch = (int)blockIdx.x / nsb;
     }
-    const int t0 = ch * tc;
+    const int t0 = ch * tcmax, tc = min(tcmax, a.g.L[0] - t0);  // the last chunk may be shorter
     const int tid = (int)threadIdx.x, w = tid >> 6, lane = tid & (kSB - 1);
     const size_t vhp = (size_t)a.g.vhp;
     LV lraw[LI][12 / LW];
@@ -1106,25 +1107,33 @@ void launch_tiled(HopArgs<S> a, hipStream_t s) {
     k_hop_t<S, DAG, MODE, TT><<<a.nb8, 64 * TT, 0, s>>>(a);
 }
 
-// Column walk: chunks of tc time slices, tc the largest divisor of L0 of at least 4 slices (or
-// L0 itself) that still gives per_cu work-groups per compute unit where the lattice allows.
+// Column walk: nch chunks of tc time slices (the last may be shorter).  A chunk costs its slices and about
+// one more (the first slice's staging is exposed, and its first two slices load the -t neighbour),
+// and the work-groups run in rounds of per_cu per compute unit of each XCD, so nch is the count with
+// the least rounds x (tc + 1), of at least 3 slices.  At 24^3 x 48 (108 spatial blocks) two chunks of 24
+// slices run in one round of 216 work-groups, where the former rule (whole divisors of L0, at least
+// one work-group per compute unit) took three chunks and two rounds, the second of them a quarter full.
 template <typename S, int DAG, int MODE, int NW, int R, bool DB = false>
 void launch_rbc(HopArgs<S> a, int per_cu, bool x1s, hipStream_t s) {
     const int L0 = a.g.L[0];
     const int nsb = a.g.vh / (L0 * kSB);
-    const int want = per_cu * compute_units();
-    int nch = 1;
-    while ((int64_t)nsb * nch < want) {
-        int nx = nch + 1;
-        while (nx <= L0 && L0 % nx) ++nx;
-        if (nx > L0 || L0 / nx < 4) break;
-        nch = nx;
+    const int lanes = x1s ? (nsb + 7) / 8 : nsb;                                  // columns sharing the slots
+    const int slots = per_cu * compute_units() / (x1s ? 8 : 1);
+    int tc = L0;
+    int64_t best = 0;
+    for (int n = 1; n == 1 || (L0 + n - 1) / n >= 3; ++n) {
+        const int t = (L0 + n - 1) / n, nc = (L0 + t - 1) / t;
+        const int64_t cost = ((int64_t)lanes * nc + slots - 1) / slots * (t + 1);
+        if (n == 1 || cost < best) {
+            best = cost;
+            tc = t;
+        }
     }
-    const int tc = L0 / nch;
-    const int grid = nsb * nch;
+    const int nch = (L0 + tc - 1) / tc;
+    const int grid = (x1s ? 8 * lanes : nsb) * nch;
     a.xcd = 0;
     a.nb8 = grid;
-    if (x1s && nsb % 8 == 0) k_hop_rbc<S, DAG, MODE, NW, R, true, DB><<<grid, 64 * NW, 0, s>>>(a, tc);
+    if (x1s) k_hop_rbc<S, DAG, MODE, NW, R, true, DB><<<grid, 64 * NW, 0, s>>>(a, tc);
     else k_hop_rbc<S, DAG, MODE, NW, R, false, DB><<<grid, 64 * NW, 0, s>>>(a, tc);
 }
 
