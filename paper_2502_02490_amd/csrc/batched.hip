@@ -30,7 +30,7 @@ std::atomic<unsigned long long> g_bwork_ids{1};
 struct BWork {
     unsigned long long id = g_bwork_ids++;  // identifies this work space in graph keys
     hipStream_t s = nullptr;                // the lattice's stream (set-up and per-lattice steps)
-    DevBuf P, Q, r, e, b, act, cyc, cnt;
+    DevBuf P, Q, e, b, act, cyc, cnt;
     DevBuf stage;                   // device staging of per-system values (contiguous)
     unsigned char *pin = nullptr;   // pinned host staging (kPinBytes): every host <-> device value copy
     DevBuf h64[4];  // FP64 half vectors x nrhs: eta-hat, x_e, r, tmp
@@ -64,7 +64,7 @@ struct BWork {
         for (auto e : ev) (void)hipEventDestroy(e);
         if (host_nact) (void)hipHostFree(host_nact);
         if (pin) (void)hipHostFree(pin);
-        for (DevBuf *d : {&P, &Q, &r, &e, &b, &act, &cyc, &cnt, &table, &nact, &stage}) d->release();
+        for (DevBuf *d : {&P, &Q, &e, &b, &act, &cyc, &cnt, &table, &nact, &stage}) d->release();
         for (auto &d : h64) d.release();
         for (auto &d : f64) d.release();
     }
@@ -72,7 +72,6 @@ struct BWork {
 
 namespace {
 
-constexpr int S_RED = 0, S_SC = 8, S_MISC = 16, S_GAM = 64, S_ALP = 192, S_C = 320, S_BETA = 512;
 constexpr int S_ALPHA = kSysScal - 64, S_XS = kSysScal - 62, S_ONE = kSysScal - 60;  // per-system free slots
 constexpr int S_TGT = kSysScal - 56;  // per-system target of the current GCR (normalised norm)
 constexpr int kMaxM = 64;
@@ -133,31 +132,6 @@ __global__ void k_bat_cycle_start(int R, const int *act, int *cyc, int *cnt) {
     if (q >= R) return;
     cyc[q] = act[q];
     cnt[2 * R + q] = 0;
-}
-
-// GCR back-substitution per system of the cycle over its own cycle length n:
-// alpha_j = c_j gamma_j + sum_{k > j} c_k beta_jk, solved for c_{n-1} .. c_0; c_j = 0 for n <= j < kmax.
-__global__ void k_bat_backsub(int R, const int *cyc, const int *cnt, double *scal, int kmax) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= R || !cyc[q]) return;
-    double *b = scal + (size_t)q * kSysScal;
-    const int n = cnt[2 * R + q];
-    for (int j = kmax - 1; j >= n; --j) {
-        b[S_C + 2 * j] = 0.0;
-        b[S_C + 2 * j + 1] = 0.0;
-    }
-    for (int j = n - 1; j >= 0; --j) {
-        double ar = b[S_ALP + 2 * j], ai = b[S_ALP + 2 * j + 1];
-        for (int k = j + 1; k < n; ++k) {
-            const double br = b[S_BETA + 2 * kMaxM * k + 2 * j], bi = b[S_BETA + 2 * kMaxM * k + 2 * j + 1];
-            const double cr = b[S_C + 2 * k], ci = b[S_C + 2 * k + 1];
-            ar -= br * cr - bi * ci;
-            ai -= br * ci + bi * cr;
-        }
-        const double g = b[S_GAM + j];
-        b[S_C + 2 * j] = ar / g;
-        b[S_C + 2 * j + 1] = ai / g;
-    }
 }
 
 // dst[r] = src[r * stride] and back: per-system scalars to and from a contiguous staging array.
@@ -332,7 +306,7 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
               (unsigned long long)(uintptr_t)b[l], (unsigned long long)(uintptr_t)c->work->blas.part.p,
               (unsigned long long)(uintptr_t)c->work->blas.scal.p,
               (unsigned long long)(uintptr_t)c->f[pr[l]].tmp_half.p, (unsigned long long)(uintptr_t)L.w->P.p,
-              (unsigned long long)(uintptr_t)L.w->Q.p, (unsigned long long)(uintptr_t)L.w->r.p,
+              (unsigned long long)(uintptr_t)L.w->Q.p,
               (unsigned long long)(uintptr_t)L.w->act.p, (unsigned long long)(uintptr_t)L.w->cyc.p,
               (unsigned long long)(uintptr_t)L.w->cnt.p})
             key.push_back(v);
@@ -353,7 +327,7 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
         const int R = L.nrhs;
         blas(l).lincomb(pr[l], pr[l], pr[l], 1, x[l], nullptr, 0.0, b[l], 0.0, nullptr, nullptr, 1.0, ms,
                         L.spec(L.act()));
-        blas(l).lincomb(pr[l], pr[l], pr[l], 1, L.w->r.p, nullptr, 1.0, b[l], 0.0, nullptr, L.sp(S_RED + 4),
+        blas(l).lincomb(pr[l], pr[l], pr[l], 1, L.w->P.p, nullptr, 1.0, b[l], 0.0, nullptr, L.sp(S_RED + 4),
                         scale(l), ms, L.spec(L.act()));
         k_bat_status<<<1, 64, 0, ms>>>(R, 1, 0, L.act(), L.cyc(), L.cnt(), L.scal());
         HIP_CHECK(hipGetLastError());
@@ -365,7 +339,7 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
     // lets it choose before the graphs are recorded
     if (use_graph && !lw.it_graphs[0])
         for (int l = 0; l < nl; ++l)
-            schur_apply(B.lats[l].c, B.lats[l].w->Q.p, B.lats[l].w->r.p, 0, pr[l], ms, B.lats[l].nrhs,
+            schur_apply(B.lats[l].c, B.lats[l].w->Q.p, B.lats[l].w->P.p, 0, pr[l], ms, B.lats[l].nrhs,
                         B.lats[l].act());
     auto iteration = [&](int l, int k, hipStream_t s) {
         Lat &L = B.lats[l];
@@ -375,12 +349,9 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
         Blas &Bl = blas(l);
         const double sc = scale(l);
         schur_apply(L.c, qk, P + k * kb, 0, pr[l], s, L.nrhs, L.act());
-        double *bcol = L.sp(S_BETA + 2 * kMaxM * k);
-        if (k > 0) Bl.mdot(pr[l], 1, Q, k, qk, bcol, sc, s, L.spec(L.act()));
-        Bl.maxpy_dot(pr[l], 1, Q, k, bcol, qk, L.w->r.p, L.sp(S_RED), sc, s, L.spec(L.act()));
-        Bl.gcr_scalars(L.sp(S_RED), L.sp(S_SC), L.sp(S_GAM), L.sp(S_ALP), k, s, L.spec(L.act()));
-        Bl.gcr_update(pr[l], 1, L.sp(S_SC), qk, L.w->r.p, P + (k + 1) * kb, L.sp(S_RED + 4), sc, s,
-                      L.spec(L.act()));
+        // the residual of iteration k is its direction, slot k of P
+        Bl.gcr_dots(pr[l], 1, Q, k, qk, P + k * kb, sc, s, L.spec(L.act()));
+        Bl.gcr_step(pr[l], 1, Q, k, qk, P + k * kb, P + (k + 1) * kb, sc, s, L.spec(L.act()));
         k_bat_status<<<1, 64, 0, s>>>(L.nrhs, 0, k, L.act(), L.cyc(), L.cnt(), L.scal());
         HIP_CHECK(hipGetLastError());
     };
@@ -388,20 +359,17 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
         Lat &L = B.lats[l];
         k_bat_cycle_start<<<1, 64, 0, s>>>(L.nrhs, L.act(), L.cyc(), L.cnt());
         HIP_CHECK(hipGetLastError());
-        blas(l).lincomb(pr[l], pr[l], pr[l], 1, L.w->P.p, nullptr, 1.0, L.w->r.p, 0.0, nullptr, nullptr, 1.0, s,
-                        L.spec(L.act()));
     };
     auto cycle_end = [&](int l, int kmax, hipStream_t s) {
         Lat &L = B.lats[l];
-        k_bat_backsub<<<1, 64, 0, s>>>(L.nrhs, L.cyc(), L.cnt(), L.scal(), kmax);
-        HIP_CHECK(hipGetLastError());
+        blas(l).gcr_backsub(L.cnt() + 2 * L.nrhs, 0, kmax, s, L.spec(L.cyc()));
         // each system sums its own cycle's basis vectors (with a shorter cycle than the batch's,
         // the later slots hold vectors of earlier cycles or calls)
         blas(l).axpy_multi(pr[l], pr[l], 1, x[l], L.w->P.p, kmax, L.sp(S_C), 1.0, s, L.spec(L.cyc()), nullptr,
                            L.cnt() + 2 * L.nrhs);
         // true residuals of the systems that took part in the cycle
         schur_apply(L.c, L.w->Q.p, x[l], 0, pr[l], s, L.nrhs, L.cyc());
-        blas(l).lincomb(pr[l], pr[l], pr[l], 1, L.w->r.p, nullptr, 1.0, b[l], -1.0, L.w->Q.p, L.sp(S_RED + 4),
+        blas(l).lincomb(pr[l], pr[l], pr[l], 1, L.w->P.p, nullptr, 1.0, b[l], -1.0, L.w->Q.p, L.sp(S_RED + 4),
                         scale(l), s, L.spec(L.cyc()));
         k_bat_status<<<1, 64, 0, s>>>(L.nrhs, 2, 0, L.act(), L.cyc(), L.cnt(), L.scal());
         HIP_CHECK(hipGetLastError());
@@ -461,7 +429,6 @@ void ensure_bwork(dirac_ctx *c, int m, int nrhs) {
     const size_t hb = (size_t)nrhs * 24 * 8 * c->g.vhp;  // FP64 (the largest) sizing: fallback needs it
     w.P.alloc(hb * (m + 1));
     w.Q.alloc(hb * m);
-    w.r.alloc(hb);
     w.e.alloc(hb);
     w.b.alloc(hb);
     w.act.alloc(nrhs * sizeof(int));

@@ -21,24 +21,29 @@ struct BatchSpec {
     int sstride = 0;
 };
 
+// device scalar slots (doubles) of a system: residual norm^2 at S_RED + 4, {1 / gamma, alpha}, free slots, per
+// iteration gamma_k, alpha_k, the solution's coefficients c_k, |Q_k|^2 and the beta_kj
+constexpr int kGcrMax = 64;  // longest cycle
+constexpr int S_RED = 0, S_SC = 8, S_MISC = 16, S_GAM = 64, S_ALP = 192, S_C = 320, S_N2 = 448, S_BETA = 512;
 constexpr int kSysScal = 8768;  // device scalar doubles per system: GCR(64) coefficients and 64 free slots
 
 struct Blas {
     dirac_ctx *c = nullptr;
-    DevBuf part, scal;
+    DevBuf part, scal, count;  // partial sums, scalars, work-groups finished per system (zero between launches)
 
     void reserve(int64_t nsites_max, int kmax, int nrhs = 1);
     // out[j] = scale <Q_j, q>, j < k (complex, 2 doubles each)
     void mdot(dirac_prec pr, int nh, const void *Q, int k, const void *q, double *out_dev, double scale, hipStream_t s,
               const BatchSpec &bs = BatchSpec());
-    // q -= sum_j coef_j Q_j; out = scale {|q|^2, <q, r>}
-    void maxpy_dot(dirac_prec pr, int nh, const void *Q, int k, const double *coef_dev, void *q, const void *r,
-                   double *out_dev, double scale, hipStream_t s, const BatchSpec &bs = BatchSpec());
-    void gcr_scalars(const double *red, double *sc, double *gam, double *alp, int k, hipStream_t s,
-                     const BatchSpec &bs = BatchSpec());
-    // q /= gamma; r -= alpha q; pnext = r; out = scale |r|^2
-    void gcr_update(dirac_prec pr, int nh, const double *sc, void *q, void *r, void *pnext, double *out_dev,
-                    double scale, hipStream_t s, const BatchSpec &bs = BatchSpec());
+    // Step k of a GCR cycle (basis vectors Q_0 .. Q_{k-1}, q = A p_k): the scalars beta_k, gamma_k, alpha_k, then
+    // q <- the new basis vector, rnew = r - alpha q (rnew may be r), |rnew|^2 in S_RED + 4; with ctl (one system) the
+    // iteration control of the cycle is advanced against `target`.
+    void gcr_dots(dirac_prec pr, int nh, const void *Q, int k, const void *q, const void *r, double scale, hipStream_t s,
+                  const BatchSpec &bs = BatchSpec());
+    void gcr_step(dirac_prec pr, int nh, const void *Q, int k, void *q, const void *r, void *rnew, double scale,
+                  hipStream_t s, const BatchSpec &bs = BatchSpec(), int *ctl = nullptr, double target = 0.0);
+    // the coefficients S_C of x += sum_j c_j p_j after a cycle of n steps (counts[sys] when given), zero up to kmax
+    void gcr_backsub(const int *counts, int n, int kmax, hipStream_t s, const BatchSpec &bs = BatchSpec());
     // x += xscale sum_j coef_j P_j, j < k (xscale_r = xscales[r * sstride] when given; system r sums
     // only j < kcount[r] when kcount is given)
     void axpy_multi(dirac_prec px, dirac_prec pp, int nh, void *x, const void *P, int k, const double *coef_dev,
@@ -66,6 +71,7 @@ struct SolverWork {
     DevBuf f64[3];          // FP64 full vectors: b, x, r
     int m = 0;
     dirac_prec pr = DIRAC_F64;
+    double *pin = nullptr;  // pinned host memory for the values a solve waits for (8 doubles)
     long syncs = 0;  // host waits on the device (value reads) since the current solve began
 };
 

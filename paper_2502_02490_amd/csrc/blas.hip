@@ -149,83 +149,356 @@ __global__ __launch_bounds__(kRed) void k_reduce(int nblk, int nent, int nc, con
         for (int c = 0; c < nc; ++c) out[(size_t)r * sstride + j * nc + c] = scale * v[c];
 }
 
-// q -= sum_j coef_j Q_j (coef complex double in device memory); partials: |q|^2, <q, r>
-template <typename S>
-__global__ __launch_bounds__(kRed) void k_maxpy_dot(Bat B, const typename St<S>::vec *Q, int k, const double *coef,
-                                                    typename St<S>::vec *q, const typename St<S>::vec *rv,
-                                                    double *partials) {
-    __shared__ double lds[3 * kRed / 64];
-    int r, t;
-    if (!sys_of(B, r, t)) return;
-    const size_t vs = vstride<S>(B);
-    q += r * vs;
-    rv += r * vs;
-    const double2 *cf = reinterpret_cast<const double2 *>(coef + (size_t)r * B.sstride);
-    double v[3] = {0.0, 0.0, 0.0};
-    if (t < B.n) {
-        double a[24], b[24];
-        ld<S>(q, t, B.vh, a);
-        for (int j = 0; j < k; ++j) {
-            const double2 cj = cf[j];
-            ld_basis<S>(Q + ((size_t)j * B.nrhs + r) * vs, t, B.vh, b);
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                a[2 * c] -= cj.x * b[2 * c] - cj.y * b[2 * c + 1];
-                a[2 * c + 1] -= cj.x * b[2 * c + 1] + cj.y * b[2 * c];
-            }
-        }
-        st<S>(q, t, B.vh, a);
-        ld<S>(q, t, B.vh, a);  // the stored (rounded) q is what the recurrence uses
-        ld<S>(rv, t, B.vh, b);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            v[0] += a[2 * c] * a[2 * c] + a[2 * c + 1] * a[2 * c + 1];
-            v[1] += a[2 * c] * b[2 * c] + a[2 * c + 1] * b[2 * c + 1];
-            v[2] += a[2 * c] * b[2 * c + 1] - a[2 * c + 1] * b[2 * c];
-        }
-    }
-    group_sum<3>(v, lds);
-    if (threadIdx.x == 0)
-        for (int c = 0; c < 3; ++c) partials[(size_t)blockIdx.x * 3 + c] = v[c];
+// ------------------------------------------------------------------ one GCR orthogonalisation step
+// Two kernels per iteration, each finished by its last work-group per system, instead of a kernel and a
+// reduction for each of the dots, the subtraction and the update, and one for the scalars:
+//   k_gcr_dots: <Q_j, q> (j < k), |q|^2 and <q, r> in one pass over Q, q and r; then
+//     beta_j = <Q_j, q> / |Q_j|^2,  gamma^2 = |q|^2 - sum_j |<Q_j, q>|^2 / |Q_j|^2,  alpha = <q, r> / gamma
+//     (r is orthogonal to the Q_j, so <q - sum beta_j Q_j, r> = <q, r>);
+//   k_gcr_step: q <- (q - sum_j beta_j Q_j) / gamma, r_new = r - alpha q, |q|^2 (kept as |Q_k|^2) and |r_new|^2.
+// gamma from the difference is as accurate as FP64 sums of the stored vectors make it; what is left of
+// an inexact gamma is in the kept |Q_k|^2, by which the later beta are divided.  A q that lies in the
+// span of the Q_j up to the rounding of the stored vectors (gamma^2 <= eps |q|^2) gives Q_k = 0 and no step.
+// r_new goes to the next direction's slot (or over r): r is not stored a second time.  Passes over
+// vectors per iteration: 2 k + 6, against 2 k + 9.
+// Work-groups take chunks of BS sites in turn, one site per thread; BS = 512, or 256 where 512 would leave compute
+// units without a work-group.  On the smallest lattices (kWideSites) a thread would still wait for one basis
+// vector after the other (1.6 us each in FP64), so there (WIDE) a chunk is 64 sites and wavefront w of eight
+// takes the basis vectors w, w + 8, ...: at 8^4 a kernel of an FP64 GCR(32) step falls from 34 to 10 us on
+// average; at 16^3 x 32 one right-hand side is slower that way (92 against 78 us per iteration).  The partial sums and the finishing work-group's reads of
+// them are agent-scope accesses (the XCDs' L2s are not coherent with each other), summed in a fixed order.
+constexpr int kGcr = 512;
+constexpr int kGcrBlocks = 512;  // work-groups per system at most: two per compute unit
+constexpr int kGcrEnt = 2 * (64 + 2);
+constexpr int kWideSites = 1 << 15;  // sites times systems
+
+template <int CTRL, int ROWS>
+DEV double dpp_part(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+// sum over the wavefront in lane 63 (row shifts, then the rows in order)
+DEV double wave_sum63(double v) {
+    v += dpp_part<0x111, 0xf>(v);
+    v += dpp_part<0x112, 0xf>(v);
+    v += dpp_part<0x114, 0xf>(v);
+    v += dpp_part<0x118, 0xf>(v);
+    v += dpp_part<0x142, 0xa>(v);
+    v += dpp_part<0x143, 0xc>(v);
+    return v;
 }
 
-// q_hat = q / gamma -> q; r -= alpha q_hat; pnext = r (if given); partial |r|^2.
-// sc = {1/gamma, alpha.re, alpha.im} in device memory.
-template <typename S>
-__global__ __launch_bounds__(kRed) void k_gcr_update(Bat B, const double *sc, typename St<S>::vec *q,
-                                                     typename St<S>::vec *rv, typename St<S>::vec *pnext,
-                                                     double *partials) {
-    __shared__ double lds[kRed / 64];
-    int r, t;
-    if (!sys_of(B, r, t)) return;
-    const size_t vs = vstride<S>(B);
-    q += r * vs;
-    rv += r * vs;
-    if (pnext) pnext += r * vs;
-    sc += (size_t)r * B.sstride;
-    double v[1] = {0.0};
-    if (t < B.n) {
-        const double ig = sc[0], ar = sc[1], ai = sc[2];
-        double a[24], b[24];
-        ld<S>(q, t, B.vh, a);
+// Partial sums of a work-group, acc[wave][e] for e < ne, to part; true in every thread of the work-group that
+// finishes last of the system's nblk, with tot[e] (in acc[0]) the sums over all of them.
+template <int BS>
+DEV bool gcr_finish(double (*acc)[kGcrEnt], int ne, int nblk, int sys, int blk, double *part, unsigned *ctr) {
+    __shared__ bool last;
+    constexpr int NW = BS / 64;
+    const int tid = threadIdx.x;
+    __syncthreads();
+    part += (size_t)sys * nblk * ne;
+    if (tid < ne) {
+        double s = acc[0][tid];
 #pragma unroll
-        for (int c = 0; c < 24; ++c) a[c] *= ig;
-        st<S>(q, t, B.vh, a);
-        ld<S>(q, t, B.vh, a);
-        ld<S>(rv, t, B.vh, b);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            b[2 * c] -= ar * a[2 * c] - ai * a[2 * c + 1];
-            b[2 * c + 1] -= ar * a[2 * c + 1] + ai * a[2 * c];
-        }
-        st<S>(rv, t, B.vh, b);
-        if (pnext) st<S>(pnext, t, B.vh, b);
-        ld<S>(rv, t, B.vh, b);
-#pragma unroll
-        for (int c = 0; c < 24; ++c) v[0] += b[c] * b[c];
+        for (int w = 1; w < NW; ++w) s += acc[w][tid];
+        __hip_atomic_store(part + (size_t)blk * ne + tid, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    group_sum<1>(v, lds);
-    if (threadIdx.x == 0) partials[blockIdx.x] = v[0];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the partial sums have arrived before the count goes up
+    __syncthreads();
+    if (tid == 0)
+        last = __hip_atomic_fetch_add(ctr + sys, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nblk - 1;
+    __syncthreads();
+    if (!last) return false;
+    if (tid == 0) __hip_atomic_store(ctr + sys, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    double *flat = &acc[0][0];
+    const int groups = BS / ne, g = tid / ne, e = tid - g * ne;
+    double s = 0.0;
+    if (g < groups) {
+#pragma unroll 8
+        for (int b = g; b < nblk; b += groups)
+            s += __hip_atomic_load(part + (size_t)b * ne + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (g < groups) flat[g * ne + e] = s;
+    __syncthreads();
+    if (tid < ne) {
+        for (int q = 1; q < groups; ++q) s += flat[q * ne + tid];
+        flat[tid] = s;
+    }
+    __syncthreads();
+    return true;
+}
+
+// Back-substitution at the end of a cycle, one work-group per system: alpha_j = c_j gamma_j + sum_{k > j} c_k beta_kj,
+// solved for c_{n-1} .. c_0 with one wavefront (lane j holds what is left of alpha_j), the beta in LDS.
+// n = counts[sys], or n_all; c_j = 0 for n <= j < kmax.
+__global__ __launch_bounds__(256) void k_gcr_backsub(const int *active, const int *counts, int n_all, int kmax,
+                                                     int sstride, double *scal) {
+    __shared__ double2 beta[kGcrMax * kGcrMax];
+    const int sys = (int)blockIdx.x;
+    if (active && !active[sys]) return;
+    scal += (size_t)sys * sstride;
+    const int n = counts ? counts[sys] : n_all;
+    const double2 *bg = reinterpret_cast<const double2 *>(scal + S_BETA);
+    for (int e = threadIdx.x; e < n * kGcrMax; e += 256) beta[e] = bg[e];  // entries j >= k are not used
+    __syncthreads();
+    const int lane = threadIdx.x;
+    if (lane >= 64) return;
+    double ar = 0.0, ai = 0.0, ig = 0.0;
+    if (lane < n) {
+        ar = scal[S_ALP + 2 * lane];
+        ai = scal[S_ALP + 2 * lane + 1];
+        ig = 1.0 / scal[S_GAM + lane];
+    }
+    for (int k = n - 1; k >= 0; --k) {
+        const double cr = __shfl(ar * ig, k, 64), ci = __shfl(ai * ig, k, 64);
+        if (lane < k) {
+            const double2 b = beta[k * kGcrMax + lane];
+            ar -= b.x * cr - b.y * ci;
+            ai -= b.x * ci + b.y * cr;
+        }
+    }
+    if (lane < kmax) {
+        scal[S_C + 2 * lane] = lane < n ? ar * ig : 0.0;
+        scal[S_C + 2 * lane + 1] = lane < n ? ai * ig : 0.0;
+    }
+}
+
+template <typename S, bool WIDE, int BS>
+__global__ __launch_bounds__(BS) void k_gcr_dots(Bat B, int nblk, const typename St<S>::vec *Q, int k,
+                                                   const typename St<S>::vec *q, const typename St<S>::vec *rv,
+                                                   double *part, unsigned *ctr, double scale, double eps, double *scal) {
+    __shared__ double acc[BS / 64][kGcrEnt];
+    const int sys = (int)blockIdx.x / nblk, blk = (int)blockIdx.x - sys * nblk;
+    if (B.active && !B.active[sys]) return;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, ne = 2 * (k + 2);
+    for (int e = lane; e < ne; e += 64) acc[w][e] = 0.0;
+    const size_t vs = vstride<S>(B);
+    q += sys * vs;
+    rv += sys * vs;
+    constexpr int CH = WIDE ? 64 : BS;
+    const int nch = (B.n + CH - 1) / CH;
+    for (int c = blk; c < nch; c += nblk) {
+        const int t = c * CH + (WIDE ? lane : (int)threadIdx.x);
+        const bool on = t < B.n;
+        double a[24];
+        if (on) ld<S>(q, t, B.vh, a);
+        if (!WIDE || w == 0) {
+            double v[3] = {0.0, 0.0, 0.0};
+            if (on) {
+                double b[24];
+                ld<S>(rv, t, B.vh, b);
+#pragma unroll
+                for (int m = 0; m < 12; ++m) {
+                    v[0] = fma(a[2 * m], a[2 * m], fma(a[2 * m + 1], a[2 * m + 1], v[0]));
+                    v[1] = fma(a[2 * m], b[2 * m], fma(a[2 * m + 1], b[2 * m + 1], v[1]));
+                    v[2] = fma(a[2 * m], b[2 * m + 1], fma(-a[2 * m + 1], b[2 * m], v[2]));
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < 3; ++m) v[m] = wave_sum63(v[m]);
+            if (lane == 63) {
+                acc[w][2 * k] += v[0];
+                acc[w][2 * k + 2] += v[1];
+                acc[w][2 * k + 3] += v[2];
+            }
+        }
+        for (int j = WIDE ? w : 0; j < k; j += WIDE ? (BS / 64) : 1) {
+            double u[2] = {0.0, 0.0};
+            if (on) {
+                double b[24];
+                ld_basis<S>(Q + ((size_t)j * B.nrhs + sys) * vs, t, B.vh, b);
+#pragma unroll
+                for (int m = 0; m < 12; ++m) {
+                    u[0] = fma(b[2 * m], a[2 * m], fma(b[2 * m + 1], a[2 * m + 1], u[0]));
+                    u[1] = fma(b[2 * m], a[2 * m + 1], fma(-b[2 * m + 1], a[2 * m], u[1]));
+                }
+            }
+            u[0] = wave_sum63(u[0]);
+            u[1] = wave_sum63(u[1]);
+            if (lane == 63) {
+                acc[w][2 * j] += u[0];
+                acc[w][2 * j + 1] += u[1];
+            }
+        }
+    }
+    if (!gcr_finish<BS>(acc, ne, nblk, sys, blk, part, ctr)) return;
+    if (w) return;
+    // one wavefront: lane j forms beta_j
+    const double *tot = acc[0];
+    scal += (size_t)sys * B.sstride;
+    double sub = 0.0;
+    if (lane < k) {
+        const double n2 = scal[S_N2 + lane], inv = n2 > 0.0 ? 1.0 / n2 : 0.0;
+        const double dr = scale * tot[2 * lane], di = scale * tot[2 * lane + 1];
+        double *beta = scal + S_BETA + 2 * kGcrMax * k + 2 * lane;
+        beta[0] = dr * inv;
+        beta[1] = di * inv;
+        sub = (dr * dr + di * di) * inv;
+    }
+    sub = wave_sum63(sub);
+    if (lane == 63) {
+        const double qq = scale * tot[2 * k], g2 = qq - sub;
+        const bool in_span = g2 <= eps * qq;  // false for NaN, which goes on into the step
+        const double g = in_span ? 1.0 : sqrt(g2), ig = in_span ? 0.0 : 1.0 / g;
+        const double ar = scale * tot[2 * k + 2] * ig, ai = scale * tot[2 * k + 3] * ig;
+        scal[S_SC] = ig;
+        scal[S_SC + 1] = ar;
+        scal[S_SC + 2] = ai;
+        scal[S_GAM + k] = g;
+        scal[S_ALP + 2 * k] = ar;
+        scal[S_ALP + 2 * k + 1] = ai;
+    }
+}
+
+// o rounded to the storage precision, stored, and returned as stored
+template <typename S>
+DEV void st_rounded(typename St<S>::vec *p, int t, int vh, double *o) {
+    constexpr int W = St<S>::W;
+    uint32_t i;
+    typename St<S>::vec *q = site_ptr(blk_base<S>(p, t, vh, i), i, 24 / W);
+#pragma unroll
+    for (int m = 0; m < 24 / W; ++m) {
+        typename St<S>::acc r[W];
+#pragma unroll
+        for (int e = 0; e < W; ++e) r[e] = (typename St<S>::acc)o[m * W + e];
+        const typename St<S>::vec v = St<S>::pack(r);
+        q[m * kSB] = v;
+        St<S>::unpack(v, r);
+#pragma unroll
+        for (int e = 0; e < W; ++e) o[m * W + e] = (double)r[e];
+    }
+}
+
+// ctl (one system): after the sums, ++ctl[1]; ctl[0] = 0 when the new residual norm is at most target or not
+// finite (then ctl[2] = 1).  WIDE: the wavefronts' parts of sum_j beta_j Q_j meet in LDS, and wavefront w then
+// takes the storage planes w, w + 8 of the chunk's sites.
+template <typename S, bool WIDE, int BS>
+__global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename St<S>::vec *Q, int k,
+                                                   typename St<S>::vec *q, const typename St<S>::vec *rv,
+                                                   typename St<S>::vec *rnew, double *part, unsigned *ctr, double scale,
+                                                   double *scal, int *ctl, double target) {
+    __shared__ double acc[BS / 64][kGcrEnt];
+    __shared__ double sub[WIDE ? (BS / 64) : 1][WIDE ? 24 : 1][64];
+    const int sys = (int)blockIdx.x / nblk, blk = (int)blockIdx.x - sys * nblk;
+    if (B.active && !B.active[sys]) return;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const size_t vs = vstride<S>(B);
+    q += sys * vs;
+    rv += sys * vs;
+    rnew += sys * vs;
+    scal += (size_t)sys * B.sstride;
+    const double2 *cf = reinterpret_cast<const double2 *>(scal + S_BETA + 2 * kGcrMax * k);
+    const double ig = scal[S_SC], ar = scal[S_SC + 1], ai = scal[S_SC + 2];
+    double v[2] = {0.0, 0.0};
+    constexpr int CH = WIDE ? 64 : BS;
+    const int nch = (B.n + CH - 1) / CH;
+    for (int c = blk; c < nch; c += nblk) {
+        const int t = c * CH + (WIDE ? lane : (int)threadIdx.x);
+        double a[24], b[24];
+        auto take = [&](int j) {  // a -= beta_j Q_j
+            const double2 cj = cf[j];
+            ld_basis<S>(Q + ((size_t)j * B.nrhs + sys) * vs, t, B.vh, b);
+#pragma unroll
+            for (int m = 0; m < 12; ++m) {
+                a[2 * m] -= cj.x * b[2 * m] - cj.y * b[2 * m + 1];
+                a[2 * m + 1] -= cj.x * b[2 * m + 1] + cj.y * b[2 * m];
+            }
+        };
+        if constexpr (!WIDE) {
+            if (t >= B.n) continue;
+            ld<S>(q, t, B.vh, a);
+            for (int j = 0; j < k; ++j) take(j);
+#pragma unroll
+            for (int m = 0; m < 24; ++m) a[m] *= ig;
+            st_rounded<S>(q, t, B.vh, a);  // the stored (rounded) q is what the recurrence uses
+            ld<S>(rv, t, B.vh, b);
+#pragma unroll
+            for (int m = 0; m < 12; ++m) {
+                b[2 * m] -= ar * a[2 * m] - ai * a[2 * m + 1];
+                b[2 * m + 1] -= ar * a[2 * m + 1] + ai * a[2 * m];
+            }
+            st_rounded<S>(rnew, t, B.vh, b);
+#pragma unroll
+            for (int m = 0; m < 24; ++m) {
+                v[0] = fma(a[m], a[m], v[0]);
+                v[1] = fma(b[m], b[m], v[1]);
+            }
+        } else {
+            constexpr int W = St<S>::W, NP = 24 / W;
+            const int nw = min(k, (BS / 64));  // wavefronts with a basis vector
+            if (w < nw) {
+#pragma unroll
+                for (int m = 0; m < 24; ++m) a[m] = 0.0;
+                if (t < B.n)
+                    for (int j = w; j < k; j += (BS / 64)) take(j);
+#pragma unroll
+                for (int m = 0; m < 24; ++m) sub[w][m][lane] = a[m];
+            }
+            __syncthreads();
+            if (t < B.n) {
+                uint32_t i;
+                const size_t off = (size_t)(blk_base<S>(q, t, B.vh, i) - q);
+                auto site = [&](auto *p) { return site_ptr(p + off, i, NP); };
+                for (int pl = w; pl < NP; pl += (BS / 64)) {
+                    typename St<S>::vec vq = site(q)[pl * kSB];
+                    typename St<S>::acc f[W];
+                    double y[W];
+                    St<S>::unpack(vq, f);
+#pragma unroll
+                    for (int e = 0; e < W; ++e) {
+                        double z = (double)f[e];
+                        for (int u = 0; u < nw; ++u) z += sub[u][pl * W + e][lane];
+                        f[e] = (typename St<S>::acc)(z * ig);
+                    }
+                    vq = St<S>::pack(f);
+                    site(q)[pl * kSB] = vq;
+                    St<S>::unpack(vq, f);  // the stored (rounded) q is what the recurrence uses
+#pragma unroll
+                    for (int e = 0; e < W; ++e) y[e] = (double)f[e];
+                    typename St<S>::vec vr = site(rv)[pl * kSB];
+                    St<S>::unpack(vr, f);
+#pragma unroll
+                    for (int e = 0; e < W; e += 2) {
+                        const double re = (double)f[e] - (ar * y[e] - ai * y[e + 1]);
+                        const double im = (double)f[e + 1] - (ar * y[e + 1] + ai * y[e]);
+                        f[e] = (typename St<S>::acc)re;
+                        f[e + 1] = (typename St<S>::acc)im;
+                    }
+                    vr = St<S>::pack(f);
+                    site(rnew)[pl * kSB] = vr;
+                    St<S>::unpack(vr, f);
+#pragma unroll
+                    for (int e = 0; e < W; ++e) {
+                        v[0] = fma(y[e], y[e], v[0]);
+                        v[1] = fma((double)f[e], (double)f[e], v[1]);
+                    }
+                }
+            }
+            __syncthreads();  // sub is read before the next chunk overwrites it
+        }
+    }
+    v[0] = wave_sum63(v[0]);
+    v[1] = wave_sum63(v[1]);
+    if (lane == 63) {
+        acc[w][0] = v[0];
+        acc[w][1] = v[1];
+    }
+    if (!gcr_finish<BS>(acc, 2, nblk, sys, blk, part, ctr)) return;
+    if (threadIdx.x) return;
+    const double rn2 = scale * acc[0][1];
+    scal[S_N2 + k] = scale * acc[0][0];
+    scal[S_RED + 4] = rn2;
+    if (ctl) {
+        ++ctl[1];
+        if (!isfinite(rn2)) {
+            ctl[2] = 1;
+            ctl[0] = 0;
+        } else if (sqrt(rn2) <= target) {
+            ctl[0] = 0;
+        }
+    }
 }
 
 // x += xscale_r sum_j coef_j P_j (x and P may have different precisions)
@@ -345,25 +618,6 @@ __global__ __launch_bounds__(kRed) void k_cgls_p(int n, int vh, const double *rh
     st<S>(p, t, vh, a);
 }
 
-// GCR scalars after k_maxpy_dot, per system r (thread r): red = {|q|^2, re <q,r>, im <q,r>};
-// out: sc = {1/gamma, alpha}, gamma_k and alpha_k stored at slot k
-__global__ void k_gcr_scalars(int nrhs, int sstride, const int *active, const double *red, double *sc, double *gam,
-                              double *alp, int k) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nrhs || (active && !active[r])) return;
-    const size_t o = (size_t)r * sstride;
-    const double n2 = red[o];
-    const double g = sqrt(n2);
-    const double ig = g > 0.0 ? 1.0 / g : 0.0;
-    const double ar = red[o + 1] * ig, ai = red[o + 2] * ig;  // <q_hat, r>
-    sc[o] = ig;
-    sc[o + 1] = ar;
-    sc[o + 2] = ai;
-    gam[o + k] = g;
-    alp[o + 2 * k] = ar;
-    alp[o + 2 * k + 1] = ai;
-}
-
 __global__ void k_set(double *p, double v) {
     if (threadIdx.x == 0 && blockIdx.x == 0) p[0] = v;
 }
@@ -387,8 +641,14 @@ int blas_grid(int64_t nsites) { return (int)((nsites + kRed - 1) / kRed); }
 
 void Blas::reserve(int64_t nsites_max, int kmax, int nrhs) {
     const size_t nb = (size_t)blas_grid(nsites_max);
-    part.alloc(nb * (size_t)nrhs * (size_t)std::max(kmax, 4) * 2 * sizeof(double) + 64);
-    scal.alloc((size_t)std::max(nrhs, 1) * kSysScal * sizeof(double));
+    nrhs = std::max(nrhs, 1);
+    part.alloc(std::max(nb * (size_t)nrhs * (size_t)std::max(kmax, 4) * 2 * sizeof(double) + 64,
+                        (size_t)nrhs * kGcrBlocks * kGcrEnt * sizeof(double)));
+    scal.alloc((size_t)nrhs * kSysScal * sizeof(double));
+    if (count.bytes < (size_t)nrhs * sizeof(unsigned)) {  // zero between launches
+        count.alloc((size_t)nrhs * sizeof(unsigned));
+        HIP_CHECK(hipMemset(count.p, 0, count.bytes));
+    }
 }
 
 namespace {
@@ -417,36 +677,51 @@ void Blas::mdot(dirac_prec pr, int nh, const void *Q, int k, const void *q, doub
     HIP_CHECK(hipGetLastError());
 }
 
-void Blas::maxpy_dot(dirac_prec pr, int nh, const void *Q, int k, const double *coef_dev, void *q, const void *r,
-                     double *out_dev, double scale, hipStream_t s, const BatchSpec &bs) {
+namespace {
+// rounding of the stored vectors, squared and summed incoherently, leaves gamma^2 / |q|^2 uncertain by about this
+double span_eps(dirac_prec pr) { return pr == DIRAC_F64 ? 1e-14 : pr == DIRAC_F32 ? 1e-9 : 1e-6; }
+bool gcr_wide(const Bat &b) { return (int64_t)b.n * b.nrhs <= kWideSites; }
+int gcr_block_size(const Bat &b) { return gcr_wide(b) || (int64_t)b.n * b.nrhs >= 256 * kGcr ? kGcr : kGcr / 2; }
+int gcr_blocks(const Bat &b) {
+    const int ch = gcr_wide(b) ? 64 : gcr_block_size(b);
+    return std::min((b.n + ch - 1) / ch, kGcrBlocks);
+}
+}  // namespace
+
+void Blas::gcr_dots(dirac_prec pr, int nh, const void *Q, int k, const void *q, const void *r, double scale,
+                    hipStream_t s, const BatchSpec &bs) {
     const Bat b = make_bat(c, nh, bs);
-#define FN(S)                                                                                            \
-    k_maxpy_dot<S><<<b.nb * b.nrhs, kRed, 0, s>>>(b, (const typename St<S>::vec *)Q, k, coef_dev,         \
-                                                  (typename St<S>::vec *)q, (const typename St<S>::vec *)r, \
-                                                  (double *)part.p);
+    const int nblk = gcr_blocks(b);
+#define FNW(S, WIDE, BS)                                                                                                  \
+    k_gcr_dots<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,                     \
+                                                       (const typename St<S>::vec *)q, (const typename St<S>::vec *)r, \
+                                                       (double *)part.p, (unsigned *)count.p, scale, span_eps(pr),     \
+                                                       (double *)scal.p);
+#define FN(S) if (gcr_wide(b)) { FNW(S, true, kGcr) } else if (gcr_block_size(b) == kGcr) { FNW(S, false, kGcr) } else { FNW(S, false, kGcr / 2) }
     DISPATCH_PREC(pr, FN)
 #undef FN
-    k_reduce<<<dim3(1, b.nrhs), kRed, 0, s>>>(b.nb, 1, 3, (const double *)part.p, scale, out_dev, b.sstride,
-                                              b.active);
+#undef FNW
     HIP_CHECK(hipGetLastError());
 }
 
-void Blas::gcr_scalars(const double *red, double *sc, double *gam, double *alp, int k, hipStream_t s,
-                       const BatchSpec &bs) {
-    k_gcr_scalars<<<(bs.nrhs + 63) / 64, 64, 0, s>>>(bs.nrhs, bs.sstride, bs.active, red, sc, gam, alp, k);
+void Blas::gcr_backsub(const int *counts, int n, int kmax, hipStream_t s, const BatchSpec &bs) {
+    k_gcr_backsub<<<bs.nrhs, 256, 0, s>>>(bs.active, counts, n, kmax, bs.sstride, (double *)scal.p);
     HIP_CHECK(hipGetLastError());
 }
 
-void Blas::gcr_update(dirac_prec pr, int nh, const double *sc, void *q, void *r, void *pnext, double *out_dev,
-                      double scale, hipStream_t s, const BatchSpec &bs) {
+void Blas::gcr_step(dirac_prec pr, int nh, const void *Q, int k, void *q, const void *r, void *rnew, double scale,
+                    hipStream_t s, const BatchSpec &bs, int *ctl, double target) {
     const Bat b = make_bat(c, nh, bs);
-#define FN(S)                                                                                                   \
-    k_gcr_update<S><<<b.nb * b.nrhs, kRed, 0, s>>>(b, sc, (typename St<S>::vec *)q, (typename St<S>::vec *)r,    \
-                                                   (typename St<S>::vec *)pnext, (double *)part.p);
+    const int nblk = gcr_blocks(b);
+#define FNW(S, WIDE, BS)                                                                                            \
+    k_gcr_step<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,               \
+                                                       (typename St<S>::vec *)q, (const typename St<S>::vec *)r, \
+                                                       (typename St<S>::vec *)rnew, (double *)part.p,            \
+                                                       (unsigned *)count.p, scale, (double *)scal.p, ctl, target);
+#define FN(S) if (gcr_wide(b)) { FNW(S, true, kGcr) } else if (gcr_block_size(b) == kGcr) { FNW(S, false, kGcr) } else { FNW(S, false, kGcr / 2) }
     DISPATCH_PREC(pr, FN)
 #undef FN
-    k_reduce<<<dim3(1, b.nrhs), kRed, 0, s>>>(b.nb, 1, 1, (const double *)part.p, scale, out_dev, b.sstride,
-                                              b.active);
+#undef FNW
     HIP_CHECK(hipGetLastError());
 }
 

@@ -25,9 +25,7 @@ namespace dl {
 
 namespace {
 
-// device scalar slots (doubles) inside Blas::scal
-constexpr int S_RED = 0, S_SC = 8, S_MISC = 16, S_GAM = 64, S_ALP = 192, S_C = 320, S_BETA = 512;
-constexpr int kMaxRestart = 64;
+constexpr int kMaxRestart = kGcrMax;
 
 struct GcrOut {
     int iters = 0, restarts = 0;
@@ -42,7 +40,7 @@ double *sc_ptr(SolverWork &w, int slot) { return (double *)w.blas.scal.p + slot;
 
 // Device-side iteration control of one GCR cycle without a preconditioner: ctl[0] = 1 while the
 // system is active, ctl[1] = iterations done in the cycle, ctl[2] = 1 after a non-finite residual.
-// After each iteration k_gcr_poll compares the updated residual norm with the target and clears
+// The last work-group of each iteration compares the updated residual norm with the target and clears
 // ctl[0]; every kernel of a later iteration of the cycle takes ctl as its active mask and does
 // nothing, so the host only reads ctl every kPoll iterations and at the end of the cycle.
 constexpr int kPoll = 4;
@@ -55,24 +53,20 @@ __global__ void k_gcr_ctl_start(int *ctl) {
     }
 }
 
-__global__ void k_gcr_poll(const double *rn2p, double target, int *ctl) {
-    if (threadIdx.x != 0 || blockIdx.x != 0 || !ctl[0]) return;
-    ++ctl[1];
-    const double rn2 = *rn2p;
-    if (!isfinite(rn2)) {
-        ctl[2] = 1;
-        ctl[0] = 0;
-    } else if (sqrt(rn2) <= target) {
-        ctl[0] = 0;
-    }
-}
-
-double read_scalar(SolverWork &w, int slot, hipStream_t s) {
-    double h = 0.0;
-    HIP_CHECK(hipMemcpyAsync(&h, sc_ptr(w, slot), sizeof(double), hipMemcpyDeviceToHost, s));
+// n device values at p to the pinned memory, waited for
+void read_pinned(SolverWork &w, const void *p, size_t bytes, hipStream_t s) {
+    HIP_CHECK(hipMemcpyAsync(w.pin, p, bytes, hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
     ++w.syncs;
-    return h;
+}
+double read_scalar(SolverWork &w, int slot, hipStream_t s) {
+    read_pinned(w, sc_ptr(w, slot), sizeof(double), s);
+    return w.pin[0];
+}
+// a norm and its non-finite flag (lincomb): NaN when the flag is set
+double read_norm2(SolverWork &w, int slot, hipStream_t s) {
+    read_pinned(w, sc_ptr(w, slot), 2 * sizeof(double), s);
+    return w.pin[1] != 0.0 ? std::nan("") : w.pin[0];
 }
 
 }  // namespace
@@ -85,15 +79,12 @@ void ensure_blas(dirac_ctx *c) {
         c->work->blas.c = c;
     }
     c->work->blas.reserve(c->V, kMaxRestart);
+    if (!c->work->pin) HIP_CHECK(hipHostMalloc((void **)&c->work->pin, 8 * sizeof(double), hipHostMallocDefault));
 }
 
 void ensure_work(dirac_ctx *c, int m, dirac_prec inner, int nh) {
-    if (!c->work) {
-        c->work = new SolverWork();
-        c->work->blas.c = c;
-    }
+    ensure_blas(c);
     SolverWork &w = *c->work;
-    w.blas.reserve(c->V, kMaxRestart);
     const size_t half64 = (size_t)24 * 8 * c->g.vhp;
     for (auto &b : w.h64) b.alloc(half64);
     for (auto &b : w.f64) b.alloc(2 * half64);
@@ -125,7 +116,8 @@ GcrOut gcr(dirac_ctx *c, SolverWork &w, dirac_prec pr, void *x, const void *b, b
         else schur_apply(c, out, in, 0, pr, s);
     };
     char *P = (char *)w.P.p, *Q = (char *)w.Q.p;
-    void *r = w.r.p;
+    // the residual: the next direction itself (slot k of P), or apart from the preconditioned directions
+    void *r = M ? w.r.p : P;
     GcrOut out;
     if (x0) {
         apply(Q, x);
@@ -134,8 +126,8 @@ GcrOut gcr(dirac_ctx *c, SolverWork &w, dirac_prec pr, void *x, const void *b, b
         B.lincomb(pr, pr, pr, nh, x, nullptr, 0.0, b, 0.0, nullptr, nullptr, 1.0, s);
         B.lincomb(pr, pr, pr, nh, r, nullptr, 1.0, b, 0.0, nullptr, sc_ptr(w, S_RED + 4), scale, s);
     }
-    double rn2 = read_scalar(w, S_RED + 4, s);
-    if (read_scalar(w, S_RED + 5, s) != 0.0 || !std::isfinite(rn2)) {
+    double rn2 = read_norm2(w, S_RED + 4, s);
+    if (!std::isfinite(rn2)) {
         out.nonfinite = true;
         return out;
     }
@@ -144,11 +136,9 @@ GcrOut gcr(dirac_ctx *c, SolverWork &w, dirac_prec pr, void *x, const void *b, b
         out.converged = true;
         return out;
     }
-    std::vector<double> gam(m), alp(2 * m), beta(2 * m * m), cc(2 * m);
     while (out.iters < max_iter) {
         const double cycle_start = out.rnorm;
         if (M) (*M)(P, r);
-        else B.lincomb(pr, pr, pr, nh, P, nullptr, 1.0, r, 0.0, nullptr, nullptr, 1.0, s);
         int n = 0;
         if (!M && !full) {
             // iterations decided on the device: the host queues up to kPoll iterations ahead
@@ -156,21 +146,15 @@ GcrOut gcr(dirac_ctx *c, SolverWork &w, dirac_prec pr, void *x, const void *b, b
             const BatchSpec bs{1, ctl, 0};
             k_gcr_ctl_start<<<1, 64, 0, s>>>(ctl);
             const int kmax = std::min(m, max_iter - out.iters);
-            int h[3] = {1, 0, 0};
+            int *h = reinterpret_cast<int *>(w.pin);
+            h[1] = h[2] = 0;
             for (int k = 0; k < kmax; ++k) {
                 char *qk = Q + k * hb;
                 schur_apply(c, qk, P + k * hb, 0, pr, s, 1, ctl);
-                double *bcol = sc_ptr(w, S_BETA + 2 * kMaxRestart * k);
-                if (k > 0) B.mdot(pr, nh, Q, k, qk, bcol, scale, s, bs);
-                B.maxpy_dot(pr, nh, Q, k, bcol, qk, r, sc_ptr(w, S_RED), scale, s, bs);
-                B.gcr_scalars(sc_ptr(w, S_RED), sc_ptr(w, S_SC), sc_ptr(w, S_GAM), sc_ptr(w, S_ALP), k, s, bs);
-                B.gcr_update(pr, nh, sc_ptr(w, S_SC), qk, r, P + (k + 1) * hb, sc_ptr(w, S_RED + 4), scale, s, bs);
-                k_gcr_poll<<<1, 64, 0, s>>>(sc_ptr(w, S_RED + 4), target, ctl);
-                HIP_CHECK(hipGetLastError());
+                B.gcr_dots(pr, nh, Q, k, qk, P + k * hb, scale, s, bs);
+                B.gcr_step(pr, nh, Q, k, qk, P + k * hb, P + (k + 1) * hb, scale, s, bs, ctl, target);
                 if ((k + 1) % kPoll == 0 || k + 1 == kmax) {
-                    HIP_CHECK(hipMemcpyAsync(h, ctl, sizeof h, hipMemcpyDeviceToHost, s));
-                    HIP_CHECK(hipStreamSynchronize(s));
-                    ++w.syncs;
+                    read_pinned(w, ctl, 3 * sizeof(int), s);
                     if (!h[0]) break;
                 }
             }
@@ -184,13 +168,10 @@ GcrOut gcr(dirac_ctx *c, SolverWork &w, dirac_prec pr, void *x, const void *b, b
             for (int k = 0; k < m; ++k) {
                 char *qk = Q + k * hb;
                 apply(qk, P + k * hb);
-                double *bcol = sc_ptr(w, S_BETA + 2 * kMaxRestart * k);
-                if (k > 0) B.mdot(pr, nh, Q, k, qk, bcol, scale, s);
-                B.maxpy_dot(pr, nh, Q, k, bcol, qk, r, sc_ptr(w, S_RED), scale, s);
-                B.gcr_scalars(sc_ptr(w, S_RED), sc_ptr(w, S_SC), sc_ptr(w, S_GAM), sc_ptr(w, S_ALP), k, s);
-                // the next direction is r itself (copied by the update) or M(r)
-                B.gcr_update(pr, nh, sc_ptr(w, S_SC), qk, r, M ? nullptr : P + (k + 1) * hb, sc_ptr(w, S_RED + 4),
-                             scale, s);
+                // the next direction is r itself (slot k + 1) or M(r)
+                void *rk = M ? r : P + k * hb, *rn = M ? r : P + (k + 1) * hb;
+                B.gcr_dots(pr, nh, Q, k, qk, rk, scale, s);
+                B.gcr_step(pr, nh, Q, k, qk, rk, rn, scale, s);
                 rn2 = read_scalar(w, S_RED + 4, s);
                 ++out.iters;
                 n = k + 1;
@@ -202,30 +183,13 @@ GcrOut gcr(dirac_ctx *c, SolverWork &w, dirac_prec pr, void *x, const void *b, b
                 if (M) (*M)(P + (k + 1) * hb, r);
             }
         }
-        // back-substitution: alpha_j = c_j gamma_j + sum_{k > j} c_k beta_jk
-        HIP_CHECK(hipMemcpyAsync(gam.data(), sc_ptr(w, S_GAM), n * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipMemcpyAsync(alp.data(), sc_ptr(w, S_ALP), 2 * n * sizeof(double), hipMemcpyDeviceToHost, s));
-        for (int k = 1; k < n; ++k)
-            HIP_CHECK(hipMemcpyAsync(beta.data() + 2 * m * k, sc_ptr(w, S_BETA + 2 * kMaxRestart * k),
-                                     2 * k * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipStreamSynchronize(s));
-        ++w.syncs;
-        for (int j = n - 1; j >= 0; --j) {
-            std::complex<double> acc(alp[2 * j], alp[2 * j + 1]);
-            for (int k = j + 1; k < n; ++k)
-                acc -= std::complex<double>(beta[2 * m * k + 2 * j], beta[2 * m * k + 2 * j + 1]) *
-                       std::complex<double>(cc[2 * k], cc[2 * k + 1]);
-            acc /= gam[j];
-            cc[2 * j] = acc.real();
-            cc[2 * j + 1] = acc.imag();
-        }
-        HIP_CHECK(hipMemcpyAsync(sc_ptr(w, S_C), cc.data(), 2 * n * sizeof(double), hipMemcpyHostToDevice, s));
+        B.gcr_backsub(nullptr, n, n, s);
         B.axpy_multi(pr, pr, nh, x, P, n, sc_ptr(w, S_C), 1.0, s);
         // true residual of the updated iterate
         apply(Q, x);
         B.lincomb(pr, pr, pr, nh, r, nullptr, 1.0, b, -1.0, Q, sc_ptr(w, S_RED + 4), scale, s);
-        rn2 = read_scalar(w, S_RED + 4, s);
-        if (!std::isfinite(rn2) || read_scalar(w, S_RED + 5, s) != 0.0) {
+        rn2 = read_norm2(w, S_RED + 4, s);
+        if (!std::isfinite(rn2)) {
             out.nonfinite = true;
             return out;
         }
@@ -276,6 +240,9 @@ void free_solver_work(dirac_ctx *c) {
     SolverWork &w = *c->work;
     w.blas.part.release();
     w.blas.scal.release();
+    w.blas.count.release();
+    if (w.pin) (void)hipHostFree(w.pin);
+    w.ctl.release();
     w.P.release(); w.Q.release(); w.r.release(); w.e.release(); w.b.release();
     for (auto &b : w.h64) b.release();
     for (auto &b : w.f64) b.release();
