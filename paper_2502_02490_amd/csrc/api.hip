@@ -1,5 +1,6 @@
 // C ABI entry points (include/dirac.h): argument validation, context lifetime,
 // staging between the user layouts and the NATIVE layout, status codes.
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -608,6 +609,13 @@ dirac_status dirac_dot(dirac_ctx *c, const void *a, const void *b, dirac_prec pr
 }
 
 // ---------------------------------------------------------------- learned preconditioner
+// The network's input: the caller's vector itself, or a copy in acts[0] (NULL) when it is not 16-byte aligned.
+static const void *ptc_input(dirac_ctx *c, dirac_ptc *n, const void *in, hipStream_t s) {
+    if (dl::ptc_in_place(in)) return in;
+    HIP_CHECK(hipMemcpyAsync(dl::ptc_act(c, n, 0), in, native_bytes(c, DIRAC_F32, 0), hipMemcpyDeviceToDevice, s));
+    return nullptr;
+}
+
 dirac_status ptc_create(const int *channels, int nlayers, dirac_ptc **out) {
     API_BEGIN
     require(channels != nullptr && out != nullptr, "channels and out must not be NULL");
@@ -715,9 +723,10 @@ dirac_status ptc_forward(dirac_ctx *c, dirac_ptc *n, void *out, const void *in, 
     check_dev(out, nb, "out");
     check_no_alias(out, nb, in, nb);
     dl::ptc_ensure_acts(c, n);
-    HIP_CHECK(hipMemcpyAsync(dl::ptc_act(c, n, 0), in, nb, hipMemcpyDeviceToDevice, s));
-    dl::ptc_forward_acts(c, n, s, false);
-    HIP_CHECK(hipMemcpyAsync(out, dl::ptc_act(c, n, n->nlayers), nb, hipMemcpyDeviceToDevice, s));
+    const void *x = ptc_input(c, n, in, s);
+    void *y = dl::ptc_in_place(out) ? out : nullptr;
+    dl::ptc_forward_acts(c, n, s, false, false, x, y);
+    if (!y) HIP_CHECK(hipMemcpyAsync(out, dl::ptc_act(c, n, n->nlayers), nb, hipMemcpyDeviceToDevice, s));
     API_END
 }
 
@@ -754,9 +763,15 @@ dirac_status ptc_backward(dirac_ctx *c, dirac_ptc *n, void *grad_in, const void 
         check_no_alias(grad_in, nb, grad_out, nb);
     }
     dl::ptc_ensure_acts(c, n);
-    HIP_CHECK(hipMemcpyAsync(dl::ptc_act(c, n, 0), in, nb, hipMemcpyDeviceToDevice, s));
-    dl::ptc_forward_acts(c, n, s);
-    dl::ptc_backward_acts(c, n, grad_out, grad_in, s);
+    const void *x = ptc_input(c, n, in, s);
+    dl::ptc_forward_acts(c, n, s, true, false, x);
+    if (grad_in && !dl::ptc_in_place(grad_in)) {
+        // the kernels' stores need 16-byte alignment: through acts[nlayers], which the gradients do not read
+        dl::ptc_backward_acts(c, n, grad_out, dl::ptc_act(c, n, n->nlayers), s, x);
+        HIP_CHECK(hipMemcpyAsync(grad_in, dl::ptc_act(c, n, n->nlayers), nb, hipMemcpyDeviceToDevice, s));
+    } else {
+        dl::ptc_backward_acts(c, n, grad_out, grad_in, s, x);
+    }
     API_END
 }
 
@@ -785,27 +800,35 @@ dirac_status ptc_train_step(dirac_ctx *c, dirac_ptc *n, const void *const *r, co
     dl::ensure_work(c, 1, DIRAC_F32, 2);
     n->grad_zero(s);
     dl::Blas &B = c->work->blas;
-    double *sc = (double *)B.scal.p + dl::kSysScal - 16;  // free slots at the end of the scalar block
+    // device slots of the pairs' norms: the beta block, free outside a solve.  The norms of the targets of up to
+    // kGroup pairs are read together before their passes and the residuals' after them: two waits per
+    // group of pairs instead of two per pair.
+    constexpr int kGroup = 1024;
+    double *sc = (double *)B.scal.p + dl::S_BETA;
     const double scale = 1.0 / (24.0 * (double)c->vh);
     double total = 0.0;
     void *g = c->work->P.p;  // dL/dy* of the current pair (F32 full)
-    for (int i = 0; i < nbatch; ++i) {
-        HIP_CHECK(hipMemcpyAsync(dl::ptc_act(c, n, 0), r[i], nb, hipMemcpyDeviceToDevice, s));
-        dl::ptc_forward_acts(c, n, s);
-        const void *y = dl::ptc_act(c, n, n->nlayers);
-        B.mdot(DIRAC_F32, 2, e[i], 1, e[i], sc, scale, s);
-        double ne2 = 0.0;
-        HIP_CHECK(hipMemcpyAsync(&ne2, sc, sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipStreamSynchronize(s));
-        require(std::isfinite(ne2) && ne2 > 0.0, "target e is zero or not finite", DIRAC_ENONFINITE);
-        // g = (y - e) / (|e|^2 nbatch), with |.|^2 in the normalised norm (the factor cancels in L)
-        const double f = 1.0 / (ne2 / scale * nbatch);
-        B.lincomb(DIRAC_F32, DIRAC_F32, DIRAC_F32, 2, g, nullptr, f, y, -f, e[i], sc + 2, 1.0, s);
-        double gn = 0.0;
-        HIP_CHECK(hipMemcpyAsync(&gn, sc + 2, sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipStreamSynchronize(s));
-        total += gn / (f * f) / (ne2 / scale) / nbatch;  // |y - e|^2 / |e|^2 / nbatch
-        dl::ptc_backward_acts(c, n, g, nullptr, s);
+    std::vector<double> h(2 * (size_t)std::min(nbatch, kGroup)), f(std::min(nbatch, kGroup));
+    for (int i0 = 0; i0 < nbatch; i0 += kGroup) {
+        const int ng = std::min(kGroup, nbatch - i0);
+        for (int i = 0; i < ng; ++i) B.mdot(DIRAC_F32, 2, e[i0 + i], 1, e[i0 + i], sc + 2 * i, scale, s);
+        read_slots(h.data(), sc, 2 * ng, s);
+        for (int i = 0; i < ng; ++i) {
+            const double ne2 = h[2 * i];
+            require(std::isfinite(ne2) && ne2 > 0.0, "target e is zero or not finite", DIRAC_ENONFINITE);
+            f[i] = 1.0 / (ne2 / scale * nbatch);
+        }
+        for (int i = 0; i < ng; ++i) {
+            const void *x = ptc_input(c, n, r[i0 + i], s);
+            dl::ptc_forward_acts(c, n, s, true, false, x);
+            // g = (y - e) / (|e|^2 nbatch), with |.|^2 in the normalised norm (the factor cancels in L)
+            B.lincomb(DIRAC_F32, DIRAC_F32, DIRAC_F32, 2, g, nullptr, f[i], dl::ptc_act(c, n, n->nlayers), -f[i],
+                      e[i0 + i], sc + 2 * i, 1.0, s);
+            dl::ptc_backward_acts(c, n, g, nullptr, s, x);
+        }
+        read_slots(h.data(), sc, 2 * ng, s);
+        // |y - e|^2 / |e|^2 / nbatch = |g|^2 / f, as f = 1 / (|e|^2 nbatch)
+        for (int i = 0; i < ng; ++i) total += h[2 * i] / f[i];
     }
     *loss = total;
     // the weights and Adam moments change only when the loss and every gradient entry are finite
@@ -840,8 +863,7 @@ dirac_status ptc_loss(dirac_ctx *c, dirac_ptc *n, const void *const *r, const vo
     void *d = c->work->P.p;  // N(r_i) - e_i
     double total = 0.0;
     for (int i = 0; i < nbatch; ++i) {
-        HIP_CHECK(hipMemcpyAsync(dl::ptc_act(c, n, 0), r[i], nb, hipMemcpyDeviceToDevice, s));
-        dl::ptc_forward_acts(c, n, s, false);
+        dl::ptc_forward_acts(c, n, s, false, false, ptc_input(c, n, r[i], s));
         B.mdot(DIRAC_F32, 2, e[i], 1, e[i], sc, 1.0, s);
         B.lincomb(DIRAC_F32, DIRAC_F32, DIRAC_F32, 2, d, nullptr, 1.0, dl::ptc_act(c, n, n->nlayers), -1.0, e[i],
                   sc + 2, 1.0, s);

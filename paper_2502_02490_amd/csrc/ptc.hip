@@ -484,7 +484,7 @@ __global__ __launch_bounds__(256) void k_ptc_tsum(PtcGeom a, int nparity, const 
 // tiles drifted to 2.4e-6 of the result at 32^3 x 64).  The running sums are added to the work-group's
 // slice every kFlush tiles; one lane owns each entry of a slice (no atomics, deterministic).
 // Measured at 32^3 x 64 (FP32 vector contraction with the transports of x before -> now): 8 -> 8
-// channels 9.5 -> 3.65 ms, 8 -> 1 3.3 -> 0.77 ms, 1 -> 8 1.65 -> 1.33 ms; errors against 64 bits
+// channels 9.5 -> 3.65 ms, 8 -> 1 3.3 -> 0.76 ms, 1 -> 8 1.65 -> 1.10 ms; errors against 64 bits
 // 1.2-2.9e-7 -> 1.2-1.4e-7.  The 8 -> 8 kernel is bound by none of its parts alone: vector ALU 55 %
 // busy (about 400 instructions per transport), matrix cores 18 %, 10 GB fetched; without cache
 // misses it takes 10 % less, without the matrix instructions 15 %, without the link products 5 %.
@@ -579,6 +579,28 @@ __global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *_
     // factor is zero there) and the raw data of its next transport.
     int i = 0, x[4], lp = 0, lbase = 0;
     TRaw<float> raw;
+    // With few groups per tile the near factor's loads would stall every tile: its raw data is loaded one tile
+    // ahead as well (two neighbouring sites per thread of the first 32 NL threads).
+    constexpr bool AHEAD = W::NG <= 2;
+    using NV = typename Act<std::conditional_t<NEARBF, bf16s, float>>::vec;
+    constexpr int NNP = NEARBF ? 3 : 6;
+    const int nc = tid >> 5, sp = tid & 31;
+    NV n0[AHEAD ? NNP : 1], n1[AHEAD ? NNP : 1];
+    auto near_at = [&](int p, int base) {
+        using A = std::conditional_t<NEARBF, bf16s, float>;
+        return site_ptr((const NV *)near_ + nc * chan_vecs<A>(a.g.vhp) + p * half_vecs<A>(a.g.vhp),
+                        (uint32_t)(base + 2 * sp), NNP);
+    };
+    auto load_near = [&]() {
+        if (nc < NL) {
+            const NV *q = near_at(lp, lbase);
+#pragma unroll
+            for (int k = 0; k < NNP; ++k) {
+                n0[k] = q[k * kSB];
+                n1[k] = q[k * kSB + 1];
+            }
+        }
+    };
     auto next_tile = [&](int j) {  // the first step at or after j with a block of the lattice
         for (; j < 2 * per; j += nwg) {
             lp = j >= per;
@@ -606,6 +628,9 @@ __global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *_
     };
     int j = next_tile((int)blockIdx.x >> 3);
     if (j < 2 * per) load(0);
+    if constexpr (AHEAD) {
+        if (j < 2 * per) load_near();
+    }
 #pragma nounroll
     while (j < 2 * per) {
         const int p = lp, base = lbase;
@@ -616,9 +641,10 @@ __global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *_
         const uint32_t flip = negate ? 0x80008000u : 0u;
         negate = !negate;
         // the near factor, two neighbouring sites per thread: [part][column][k]; sites past the end are zero
-        const int nc = tid >> 5, sp = tid & 31, s0 = base + 2 * sp;
+        const int s0 = base + 2 * sp;
         if (nc < NL) {
             const bool on0 = s0 < a.g.vh, on1 = s0 + 1 < a.g.vh;
+            const NV *q = near_at(p, base);
             unsigned char *dst = sm + buf * kWBuf + 4 * (sp & 3);
             // real r = 6 t + 2 colour + ri of the spinor is column 2 t + ri, depth 64 colour + site
             auto put = [&](int part_, int r, uint32_t w) {
@@ -626,11 +652,9 @@ __global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *_
                     dst + part_ * 64 * kWRow + wgrad_at(8 * nc + 2 * (r / 6) + (r & 1), (r % 6) >> 1, sp >> 2)) = w ^ flip;
             };
             if constexpr (NEARBF) {
-                const uint4 *q = site_ptr((const uint4 *)near_ + nc * chan_vecs<bf16s>(a.g.vhp) +
-                                              p * half_vecs<bf16s>(a.g.vhp), (uint32_t)s0, 3);
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
-                    const uint4 u0 = q[k * kSB], u1 = q[k * kSB + 1];
+                    const uint4 u0 = AHEAD ? n0[AHEAD ? k : 0] : q[k * kSB], u1 = AHEAD ? n1[AHEAD ? k : 0] : q[k * kSB + 1];
                     const uint32_t w0[4] = {u0.x, u0.y, u0.z, u0.w}, w1[4] = {u1.x, u1.y, u1.z, u1.w};
 #pragma unroll
                     for (int m = 0; m < 4; ++m) {
@@ -640,11 +664,9 @@ __global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *_
                     }
                 }
             } else {
-                const float4 *q = site_ptr((const float4 *)near_ + nc * chf + p * half_vecs<float>(a.g.vhp),
-                                           (uint32_t)s0, 6);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) {
-                    const float4 u0 = q[k * kSB], u1 = q[k * kSB + 1];
+                    const float4 u0 = AHEAD ? n0[AHEAD ? k : 0] : q[k * kSB], u1 = AHEAD ? n1[AHEAD ? k : 0] : q[k * kSB + 1];
                     const float f0[4] = {u0.x, u0.y, u0.z, u0.w}, f1[4] = {u1.x, u1.y, u1.z, u1.w};
 #pragma unroll
                     for (int m = 0; m < 4; ++m) {
@@ -696,7 +718,10 @@ __global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *_
                 load(grp + 1);
             } else {
                 jn = next_tile(j + nwg);
-                if (jn < 2 * per) load(0);
+                if (jn < 2 * per) {
+                    load(0);
+                    if constexpr (AHEAD) load_near();
+                }
             }
             __syncthreads();
             // row tiles holding no pair of the last group are skipped (their rows were not written)
@@ -1078,12 +1103,21 @@ float *ptc_act(dirac_ctx *c, dirac_ptc *n, int l) {
     return (float *)((char *)n->acts.p + off);
 }
 
-// forward: acts[0] must hold the input; leaves the output in acts[nlayers] and, with keep_all,
-// every layer's output in acts[l + 1] (the backward pass needs them).  With eo the input's odd
-// half must be zero, and only the even half of the output is formed (a network of one layer
-// forms both).
-void ptc_forward_acts(dirac_ctx *c, dirac_ptc *n, hipStream_t s, bool keep_all, bool eo) {
+// Input and output vectors a caller hands to the network are read and written in place when the kernels'
+// 16-byte accesses allow (in: acts[0] otherwise, copied by the caller of these functions).
+bool ptc_in_place(const void *p) { return ((uintptr_t)p & 15) == 0; }
+
+// forward: the input is `in`, or acts[0] when that is NULL; leaves the output in `out`, or acts[nlayers], and,
+// with keep_all, every hidden layer's output in acts[l + 1] (the backward pass needs them).  With eo
+// the input's odd half must be zero, and only the even half of the output is formed (a network of
+// one layer forms both).
+void ptc_forward_acts(dirac_ctx *c, dirac_ptc *n, hipStream_t s, bool keep_all, bool eo, const void *in, void *out) {
     PtcGeom a = geom_of(c, s);
+    auto act = [&](int l) -> void * {
+        if (l == 0 && in) return const_cast<void *>(in);
+        if (l == n->nlayers && out) return out;
+        return ptc_act(c, n, l);
+    };
     const int L = n->nlayers;
     const bool cf = n->contract_last();
     for (int l = 0; l < (cf ? L - 1 : L); ++l) {
@@ -1096,30 +1130,34 @@ void ptc_forward_acts(dirac_ctx *c, dirac_ptc *n, hipStream_t s, bool keep_all, 
         }
         if (eo && l == 0) zo.eo |= kEoIn;
         const Io io = act_bf16(n, l + 1) ? (act_bf16(n, l) ? Io::Mid : Io::In) : Io::F32;
-        layer_dispatch(a, n->ch[l], n->ch[l + 1], ptc_act(c, n, l), (const uint4 *)n->afw.p + n->afw_off[l],
-                       ptc_act(c, n, l + 1), io, s, zo);
+        layer_dispatch(a, n->ch[l], n->ch[l + 1], act(l), (const uint4 *)n->afw.p + n->afw_off[l], act(l + 1), io, s, zo);
     }
     if (cf) {
         const int npar = eo ? 1 : 2;
         k_ptc_tsum<<<(int)((npar * c->vh + 255) / 256), 256, 0, s>>>(a, npar, (const float4 *)n->zbuf.p,
-                                                                     (float4 *)ptc_act(c, n, L));
+                                                                     (float4 *)act(L));
         HIP_CHECK(hipGetLastError());
     }
 }
 
 // backward from g (dL/dy*, FP32 NATIVE full, 1 channel) at the output: accumulates dL/dW* into
-// n->grad and, when gin is given, writes dL/dx* of the input.
-void ptc_backward_acts(dirac_ctx *c, dirac_ptc *n, const void *g_out, void *gin, hipStream_t s) {
+// n->grad and, when gin is given, writes dL/dx* of the input (`in`, or acts[0] when that is NULL).
+void ptc_backward_acts(dirac_ctx *c, dirac_ptc *n, const void *g_out, void *gin, hipStream_t s, const void *in) {
     PtcGeom a = geom_of(c, s);
     const size_t chanb = chan_vecs<float>(c->g.vhp) * sizeof(float4);
     int maxc = 0;
     for (int l = 0; l <= n->nlayers; ++l) maxc = std::max(maxc, n->ch[l]);
     char *gA = (char *)n->gbuf.p, *gB = gA + (size_t)maxc * chanb;
-    HIP_CHECK(hipMemcpyAsync(gA, g_out, (size_t)n->ch[n->nlayers] * chanb, hipMemcpyDeviceToDevice, s));
+    const void *g = g_out;  // the gradient at the current layer's output
+    if (!ptc_in_place(g_out)) {
+        HIP_CHECK(hipMemcpyAsync(gA, g_out, (size_t)n->ch[n->nlayers] * chanb, hipMemcpyDeviceToDevice, s));
+        g = gA;
+    }
     for (int l = n->nlayers - 1; l >= 0; --l) {
         const int nin = n->ch[l], nout = n->ch[l + 1];
         const int nw = (int)ptc_nweights(n, l);
-        wgrad_dispatch(a, nin, nout, ptc_act(c, n, l), act_bf16(n, l), gA, n->part.p, (float2 *)n->grad.p + n->off[l], s);
+        wgrad_dispatch(a, nin, nout, l == 0 && in ? in : ptc_act(c, n, l), act_bf16(n, l), g, n->part.p,
+                       (float2 *)n->grad.p + n->off[l], s);
         if (l == 0 && !gin) break;
         k_adjoint_weights<<<(nw + 255) / 256, 256, 0, s>>>(nout, nin, (const uint32_t *)n->wbf.p + n->off[l],
                                                            (uint32_t *)n->wt.p + n->off[l]);
@@ -1127,8 +1165,9 @@ void ptc_backward_acts(dirac_ctx *c, dirac_ptc *n, const void *g_out, void *gin,
         uint4 *afb = (uint4 *)n->afb.p + n->afb_off[l];
         build_afrags(nout, nin, (const uint32_t *)n->wt.p + n->off[l], afb, s);
         void *dst = l == 0 ? gin : (void *)gB;
-        layer_dispatch(a, nout, nin, gA, afb, dst, Io::F32, s);
+        layer_dispatch(a, nout, nin, g, afb, dst, Io::F32, s);
         std::swap(gA, gB);
+        g = gA;
     }
 }
 

@@ -63,3 +63,49 @@ def test_weight_gradients_exact_activations(dims, channels):
     finally:
         net.close()
         c.D.close()
+
+
+def test_unaligned_vectors_and_batches():
+    """Vectors that are not 16-byte aligned go through copies: the same bits as aligned ones; a minibatch's loss and
+    gradient are those of its pairs."""
+    import torch
+
+    need_gpu()
+    dims, channels = (4, 4, 6, 8), (1, 4, 8, 1)
+    flush("[gpu] unaligned network vectors")
+    c = Case(dims, seed=18)
+    net = P.PTC(channels)
+    try:
+        net.set_weights(optc.init_weights(channels, seed=2, scale=1.0))
+        n = c.D.native_empty("f32").numel()
+
+        def vec(seed, off):
+            buf = torch.zeros(n + 4, device="cuda")
+            buf[off:off + n] = torch.randn(n, generator=torch.Generator(device="cuda").manual_seed(seed), device="cuda")
+            return buf[off:off + n]
+
+        got = []
+        for off in (0, 1):
+            x, g, y, gi = vec(1, off), vec(2, off), vec(3, off), vec(4, off)
+            net.forward(c.D, y, x)
+            net.zero_grad()
+            net.backward(c.D, gi, x, g)
+            got.append([y.cpu(), gi.cpu()] + [torch.from_numpy(w) for w in net.get_grad()])
+        assert all(torch.equal(a, b) for a, b in zip(*got))
+        rs, es = [vec(10 + k, k % 2) for k in range(3)], [vec(20 + k, 0) for k in range(3)]
+        losses = [net.loss(c.D, [r], [e]) for r, e in zip(rs, es)]
+        ws = net.get_weights()
+        loss = net.train_step(c.D, rs, es, 1e-3)
+        # the loss of a pair is a sum of FP32 squares accumulated in FP64: the two entry points differ by the FP32
+        # rounding of y - e and of its scaled copy, 2^-23 relative each
+        assert abs(loss - sum(losses) / 3) <= 2 ** -21 * loss
+        grad = net.get_grad()
+        net.set_weights(ws)
+        with pytest.raises(P.DiracError):  # a zero target: refused, weights unchanged
+            net.train_step(c.D, rs, [es[0], torch.zeros_like(es[1]), es[2]], 1e-3)
+        assert all(np.array_equal(a, b) for a, b in zip(net.get_weights(), ws))
+        net.train_step(c.D, rs, es, 1e-3)
+        assert all(np.array_equal(a, b) for a, b in zip(net.get_grad(), grad))
+    finally:
+        net.close()
+        c.D.close()
