@@ -157,57 +157,55 @@ DEV int64_t user_site(const Geom &g, int p, int i, int lay, int half) {
     return half ? (int64_t)i : (int64_t)i + (int64_t)p * g.vh;
 }
 
-__global__ __launch_bounds__(kBlock) void k_clover_in(Geom g, int p, int lay, const double *__restrict__ user,
-                                                       double2 *__restrict__ dst) {
-    int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= g.vh) return;
-    const double *u = user + user_site(g, p, i, lay, 0) * 72;
-    double r[72];
-#pragma unroll
-    for (int k = 0; k < 72; ++k) r[k] = u[k];
-    store_field<double, 72>(dst, i, r);
-}
-
-__global__ __launch_bounds__(kBlock) void k_clover_out(Geom g, int p, int lay, const double2 *__restrict__ src,
-                                                        double *__restrict__ user) {
-    int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= g.vh) return;
-    double *u = user + user_site(g, p, i, lay, 0) * 72;
-    double r[72];
-    if (src) {
-        load_field<double, 72>(src, i, r);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 72; ++k) r[k] = 0.0;
+// Site fields of NR reals between the caller's order (NR consecutive reals per site) and the planes.  A work-group
+// takes one 64-site block, both parities one after the other (in LEX order their sites alternate, so the
+// cache lines of one are still in L2 for the other): the caller's side is accessed with consecutive lanes on
+// consecutive reals of a site, the planes 1 KB at a time, and the block goes through LDS in between (an odd
+// row length in reals: no bank conflicts either way).  Bandwidth-bound; one thread per site on both sides
+// left the caller's side with 192 or 576 bytes between lanes.  A LEX vector of
+// 40 x 18 x 22 x 26 in FP64: in 38 -> 33 us, out 48 -> 28 us; a clover field of 24^3 x 48 out 200 -> 144 us
+// (764 MB: the rate of a copy).
+template <typename U, typename S, int NR>
+__global__ __launch_bounds__(kBlock) void k_site_in(Geom g, int p0, int np, int lay, int half, const U *__restrict__ user,
+                                                     typename St<S>::vec *__restrict__ dst, size_t parity_vecs) {
+    using T = typename St<S>::acc;
+    constexpr int W = St<S>::W, NP = NR / W;
+    __shared__ T t[kSB * (NR + 1)];
+    __shared__ int64_t us[kSB];
+    const int i0 = (int)blockIdx.x * kSB, ns = min(kSB, g.vh - i0), lane = threadIdx.x & (kSB - 1);
+    for (int p = p0; p < p0 + np; ++p) {
+        if (threadIdx.x < ns) us[threadIdx.x] = user_site(g, p, i0 + (int)threadIdx.x, lay, half) * NR;
+        __syncthreads();
+        for (int k = threadIdx.x; k < ns * NR; k += kBlock) t[k + k / NR] = (T)user[us[k / NR] + k % NR];
+        __syncthreads();
+        if (lane < ns) {
+            typename St<S>::vec *q = site_ptr(dst + (size_t)(p - p0) * parity_vecs, (uint32_t)(i0 + lane), NP);
+            for (int m = threadIdx.x >> 6; m < NP; m += kBlock / kSB) q[m * kSB] = St<S>::pack(t + lane * (NR + 1) + m * W);
+        }
     }
-#pragma unroll
-    for (int k = 0; k < 72; ++k) u[k] = r[k];
 }
 
-// ------------------------------------------------------------------ spinors (24 reals per site)
-template <typename U, typename S>
-__global__ __launch_bounds__(kBlock) void k_spinor_in(Geom g, int p, int lay, int half, const U *__restrict__ user,
-                                                       typename St<S>::vec *__restrict__ dst) {
-    int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= g.vh) return;
-    const U *u = user + user_site(g, p, i, lay, half) * 24;
-    typename St<S>::acc r[24];
-#pragma unroll
-    for (int k = 0; k < 24; ++k) r[k] = (typename St<S>::acc)u[k];
-    store_field<S, 24>(dst, i, r);
-}
-
-template <typename U, typename S>
-__global__ __launch_bounds__(kBlock) void k_spinor_out(Geom g, int p, int lay, int half,
-                                                        const typename St<S>::vec *__restrict__ src,
-                                                        U *__restrict__ user) {
-    int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= g.vh) return;
-    U *u = user + user_site(g, p, i, lay, half) * 24;
-    typename St<S>::acc r[24];
-    load_field<S, 24>(src, i, r);
-#pragma unroll
-    for (int k = 0; k < 24; ++k) u[k] = (U)r[k];
+template <typename U, typename S, int NR>
+__global__ __launch_bounds__(kBlock) void k_site_out(Geom g, int p0, int np, int lay, int half,
+                                                      const typename St<S>::vec *__restrict__ src0,
+                                                      const typename St<S>::vec *__restrict__ src1, U *__restrict__ user) {
+    using T = typename St<S>::acc;
+    constexpr int W = St<S>::W, NP = NR / W;
+    __shared__ T t[kSB * (NR + 1)];
+    __shared__ int64_t us[kSB];
+    const int i0 = (int)blockIdx.x * kSB, ns = min(kSB, g.vh - i0), lane = threadIdx.x & (kSB - 1);
+    for (int p = p0; p < p0 + np; ++p) {
+        const typename St<S>::vec *src = p == p0 ? src0 : src1;  // NULL: zeros
+        if (threadIdx.x < ns) us[threadIdx.x] = user_site(g, p, i0 + (int)threadIdx.x, lay, half) * NR;
+        if (lane < ns && src) {
+            const typename St<S>::vec *q = site_ptr(src, (uint32_t)(i0 + lane), NP);
+            for (int m = threadIdx.x >> 6; m < NP; m += kBlock / kSB)
+                St<S>::unpack(q[m * kSB], t + lane * (NR + 1) + m * W);
+        }
+        __syncthreads();
+        for (int k = threadIdx.x; k < ns * NR; k += kBlock) user[us[k / NR] + k % NR] = src ? (U)t[k + k / NR] : U(0);
+        __syncthreads();
+    }
 }
 
 template <typename S>
@@ -249,20 +247,13 @@ void convert_fields(dirac_ctx *c, dirac_prec pr, hipStream_t s) {
 
 template <typename U, typename S>
 void spinor_io(dirac_ctx *c, void *native, const void *user, bool in, int sites, dirac_layout lay, hipStream_t s) {
-    const int vh = (int)c->vh;
-    const size_t half_bytes = (size_t)24 * sizeof(S) * c->g.vhp;
-    for (int p = 0; p < 2; ++p) {
-        if (sites == 1 && p == 1) continue;
-        if (sites == 2 && p == 0) continue;
-        char *nat = (char *)native + (sites == 0 ? p * half_bytes : 0);
-        const int half = sites != 0;
-        if (in)
-            k_spinor_in<U, S><<<grid_for(vh), kBlock, 0, s>>>(c->g, p, lay, half, (const U *)user,
-                                                              (typename St<S>::vec *)nat);
-        else
-            k_spinor_out<U, S><<<grid_for(vh), kBlock, 0, s>>>(c->g, p, lay, half, (const typename St<S>::vec *)nat,
-                                                               (U *)user);
-    }
+    using V = typename St<S>::vec;
+    const size_t pv = (size_t)(24 / St<S>::W) * c->g.vhp;  // vectors of a parity
+    const int nb = c->g.vhp / kSB, p0 = sites == 2, np = sites == 0 ? 2 : 1, half = sites != 0;
+    if (in)
+        k_site_in<U, S, 24><<<nb, kBlock, 0, s>>>(c->g, p0, np, lay, half, (const U *)user, (V *)native, pv);
+    else
+        k_site_out<U, S, 24><<<nb, kBlock, 0, s>>>(c->g, p0, np, lay, half, (const V *)native, (const V *)native + pv, (U *)user);
     HIP_CHECK(hipGetLastError());
 }
 
@@ -397,7 +388,7 @@ void clover_import(dirac_ctx *c, const double *user, dirac_layout lay, hipStream
     PrecFields &f = c->f[DIRAC_F64];
     for (int p = 0; p < 2; ++p) {
         f.clov[p].alloc_field((size_t)72 * sizeof(double) * c->g.vhp);
-        k_clover_in<<<grid_for(c->vh), kBlock, 0, s>>>(c->g, p, lay, user, (double2 *)f.clov[p].p);
+        k_site_in<double, double, 72><<<c->g.vhp / kSB, kBlock, 0, s>>>(c->g, p, 1, lay, 0, user, (double2 *)f.clov[p].p, 0);
     }
     HIP_CHECK(hipGetLastError());
     c->sap_ready = false;
@@ -411,11 +402,10 @@ void clover_export(dirac_ctx *c, double *user, int inverse, dirac_layout lay, hi
     require(lay == DIRAC_LAYOUT_LEX || lay == DIRAC_LAYOUT_EO || lay == DIRAC_LAYOUT_OPENQXD,
             "clover layout must be LEX, EO or OPENQXD");
     PrecFields &f = c->f[DIRAC_F64];
-    for (int p = 0; p < 2; ++p) {
-        const double2 *src = inverse ? (f.inv_ready[p] ? (const double2 *)f.clinv[p].p : nullptr)
-                                     : (const double2 *)f.clov[p].p;
-        k_clover_out<<<grid_for(c->vh), kBlock, 0, s>>>(c->g, p, lay, src, user);
-    }
+    const double2 *src[2];
+    for (int p = 0; p < 2; ++p)
+        src[p] = inverse ? (f.inv_ready[p] ? (const double2 *)f.clinv[p].p : nullptr) : (const double2 *)f.clov[p].p;
+    k_site_out<double, double, 72><<<c->g.vhp / kSB, kBlock, 0, s>>>(c->g, 0, 2, lay, 0, src[0], src[1], user);
     HIP_CHECK(hipGetLastError());
 }
 
