@@ -140,13 +140,18 @@ DEV void add_dir_row(const W &w, C<T> &acc) {
 }
 
 template <typename T, int DAG, int N>
-DEV void apply_dir_n(const C<T> h[6], const C<T> u[6], const C<T> r2[3], T co, T si, C<T> acc[12]) {
-    C<T> w[6];
-    link_dir_n<T, N>(h, u, r2, co, si, w);
+DEV void add_rows_n(const C<T> w[6], C<T> acc[12]) {
     add_dir_row<T, DAG, N, 0>(w, acc[0]); add_dir_row<T, DAG, N, 1>(w, acc[1]); add_dir_row<T, DAG, N, 2>(w, acc[2]);
     add_dir_row<T, DAG, N, 3>(w, acc[3]); add_dir_row<T, DAG, N, 4>(w, acc[4]); add_dir_row<T, DAG, N, 5>(w, acc[5]);
     add_dir_row<T, DAG, N, 6>(w, acc[6]); add_dir_row<T, DAG, N, 7>(w, acc[7]); add_dir_row<T, DAG, N, 8>(w, acc[8]);
     add_dir_row<T, DAG, N, 9>(w, acc[9]); add_dir_row<T, DAG, N, 10>(w, acc[10]); add_dir_row<T, DAG, N, 11>(w, acc[11]);
+}
+
+template <typename T, int DAG, int N>
+DEV void apply_dir_n(const C<T> h[6], const C<T> u[6], const C<T> r2[3], T co, T si, C<T> acc[12]) {
+    C<T> w[6];
+    link_dir_n<T, N>(h, u, r2, co, si, w);
+    add_rows_n<T, DAG, N>(w, acc);
 }
 
 template <typename T, int DAG, int N>

@@ -10,7 +10,7 @@
 // shuffle trees and a fixed-order sum over the four wavefronts (deterministic).  The residual
 // update after a colour's solves changes rho only on the faces of the other colour's blocks
 // (D delta = -1/2 H delta there); it is done by the next step's work-groups on entry, from the
-// corrections delta of the previous step, so a step is one launch.  FP32 throughout (the
+// corrections delta of the previous step, kept projected on the faces, so a step is one launch.  FP32 throughout (the
 // arithmetic of a preconditioner), on block-ordered copies of the F32 links and clover field.
 #include "dirac_ops.h"
 #include "hop_core.h"
@@ -21,13 +21,18 @@ namespace {
 
 constexpr int kSapB = 4;                                  // block extent in every direction
 constexpr int kSapSites = kSapB * kSapB * kSapB * kSapB;  // 256: one work-group
-constexpr int kSapLinkPlanes = 4;  // a link in block order: 12 reals of rows 0, 1, then cos, sin of its phase
 constexpr int kSapInner = kSapSites / kSapB * (kSapB - 1);  // 192 sites of a block with a neighbour inside it in +mu
+constexpr int kSapFace = kSapSites / kSapB;                 // 64 sites of a face
+// Links of a block: the 4 x 192 of hops inside it, then the 8 x 64 of hops into it across its faces; of each
+// list three planes (rows 0 and 1 of the SU(3) matrix), then (cos, sin) of the phase; in float4:
+constexpr int kSapInnerPh = 4 * 3 * kSapInner, kSapFaces = kSapInnerPh + 4 * kSapInner / 2;
+constexpr int kSapFacePh = kSapFaces + 8 * 3 * kSapFace, kSapLinks = kSapFacePh + 8 * kSapFace / 2;
 
 // Block order: the fields of the Schwarz blocks are kept block by block (block k lexicographic in
 // the block coordinates, site t = 64 b0 + 16 b1 + 4 b2 + b3 inside it), plane-major within a
 // block, so that a work-group reads one contiguous chunk and every wavefront load is 1 KB of
-// consecutive 16-byte vectors:  spinor [k][6][256], clover [k][18][256], links [k][8][4][256].
+// consecutive 16-byte vectors:  spinor [k][6][256], clover [k][18][256], links as above, 70 KB a block, and
+// the corrections on the faces [k][8][3][64].
 // (The sites of a 4^4 block lie in 2-site pieces of the x3-fastest NATIVE order: read from there,
 // every wavefront load touches 32 cache lines for 32 bytes each.  The first cycle reads the
 // residual from there all the same, which costs less than a separate reordering pass; the
@@ -37,11 +42,14 @@ struct SapArgs {
     Geom g;
     const float4 *links;  // block order
     const float4 *clov;   // block order
-    float4 *rho, *psi, *dlt;  // block order, all blocks
+    float4 *rho, *psi;    // block order, all blocks
+    float4 *faces;        // block k, direction d: delta on the face that is the source of its neighbour's hops d, projected
     const float4 *rin;    // NATIVE input residual, read instead of rho when set (the first cycle)
     int nb[4];            // blocks per direction
     int colour, nmr, update;
     int first;            // the first cycle: psi is zero, so psi = delta
+    int keep;             // rho is read again (not in the last cycle)
+    int send;             // the faces are read by a further step
 };
 
 DEV int block_of(const SapArgs &a, const int n[4]) { return ((n[0] * a.nb[1] + n[1]) * a.nb[2] + n[2]) * a.nb[3] + n[3]; }
@@ -76,17 +84,6 @@ DEV void store_sp(float4 *base, const C<float> r[12]) {
 #pragma unroll
     for (int k = 0; k < 6; ++k) base[k * kSapSites] = make_float4(r[2 * k].r, r[2 * k].i, r[2 * k + 1].r, r[2 * k + 1].i);
 }
-// link of direction d at site t of block k (block order)
-DEV void load_blink(const SapArgs &a, int k, int d, int t, C<float> u[6], float &co, float &si) {
-    const float4 *q = a.links + ((size_t)(k * 8 + d) * kSapLinkPlanes) * kSapSites + t;
-    const float4 l0 = q[0], l1 = q[kSapSites], l2 = q[2 * kSapSites], l3 = q[3 * kSapSites];
-    u[0] = mk(l0.x, l0.y); u[1] = mk(l0.z, l0.w);
-    u[2] = mk(l1.x, l1.y); u[3] = mk(l1.z, l1.w);
-    u[4] = mk(l2.x, l2.y); u[5] = mk(l2.z, l2.w);
-    co = l3.x;
-    si = l3.y;
-}
-
 // Forward link of direction mu at block site t (b_mu < 3, the links of the hops inside the block),
 // in the LDS tile of the block: the 192 such sites of a direction, in site order.
 DEV int inner_link(int mu, int t) {
@@ -94,29 +91,119 @@ DEV int inner_link(int mu, int t) {
     return t - ((t >> (sh + 2)) << sh);
 }
 
+// The other three coordinates of a block site, x3 fastest: its place on a face of direction mu.
+DEV int face_site(int mu, const int b[4]) {
+    int f = 0, o = 0;
+#pragma unroll
+    for (int m = 3; m >= 0; --m) {
+        if (m == mu) continue;
+        f |= b[m] << (2 * o);
+        ++o;
+    }
+    return f;
+}
+
+template <int N = 0, typename F>
+DEV void each_dir(const F &f) {
+    f(std::integral_constant<int, N>());
+    if constexpr (N < 7) each_dir<N + 1>(f);
+}
+
+DEV void cplx3(float4 p, float4 q, float4 r, C<float> o[6]) {
+    o[0] = mk(p.x, p.y); o[1] = mk(p.z, p.w);
+    o[2] = mk(q.x, q.y); o[3] = mk(q.z, q.w);
+    o[4] = mk(r.x, r.y); o[5] = mk(r.z, r.w);
+}
+DEV float4 pair4(C<float> p, C<float> q) { return make_float4(p.r, p.i, q.r, q.i); }
+
+// w = M h (forward) or M^dag h (backward) for both spin rows; M, the link times its phase, in full.
+template <int BACK>
+DEV void full_mul(const C<float> M[9], const C<float> h[6], C<float> w[6]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            C<float> t = BACK ? conj_mul(M[r], h[3 * s]) : M[3 * r] * h[3 * s];
+#pragma unroll
+            for (int c = 1; c < 3; ++c) {
+                if constexpr (BACK) cmadd(t, M[3 * c + r], h[3 * s + c]);
+                else madd(t, M[3 * r + c], h[3 * s + c]);
+            }
+            w[3 * s + r] = t;
+        }
+}
+
+// One step: the face terms of the other colour's last corrections, nmr minimal-residual steps, the results.
+// At 4 minimal-residual steps it moves 1.1 KB a site (0.85 KB of it read) and issues 6,600 VALU instructions a
+// wavefront, and two work-groups fit on a CU (80 KB of LDS and 239 registers each), which overlap only in part.  So
+//  - the block's inner links are kept in LDS as full matrices with their phase: third row and phase
+//    product are formed once a step, not in each of the 4 x 7.5 hops of a site (8,150 instructions before);
+//  - only the projected faces of the corrections travel between blocks, 48 of 96 bytes a site, in whole
+//    cache lines (a face of direction 3 is every fourth site of the block), and only the links that are
+//    used (1.36 GB read a step before on 64 x 32^3, 0.92 GB now);
+//  - all loads of the entry are issued together, before the first is waited for.
+// On 64 x 32^3 with 4 cycles of 4 steps: 343 -> 276 us a step, 71 % of the SIMD cycles issue VALU instructions.
+// -1/2 folded into the links, hops added to A r directly: 272 us, but the rounding error grows by 5 %.
 __global__ __launch_bounds__(kSapSites) void k_sap_step(SapArgs a) {
-    __shared__ float4 rs[6][kSapSites];  // the block's residual, plane-major
+    // the face terms [8][3][64], then the block's residual [6][256]
+    __shared__ float4 rs[6 * kSapSites];
     __shared__ float red[3][4];
-    // the block's forward links of in-block hops (a backward hop from t takes the forward link of
-    // t - stride): rows 0, 1 of the SU(3) matrix in three planes, (cos, sin) of the phase
-    __shared__ float4 lq[4][3][kSapInner];
-    __shared__ float2 lp[4][kSapInner];
+    // links of the hops inside the block, phase included (a backward hop from t takes the forward link of
+    // t - stride): 18 reals as four planes of float4 and one of float2
+    __shared__ float4 lq[4][4][kSapInner];
+    __shared__ float2 lr[4][kSapInner];
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
     const int b[4] = {t >> 6, (t >> 4) & 3, (t >> 2) & 3, t & 3};
     int n[4];
     sap_block(a, blockIdx.x, n);
     const int k = block_of(a, n);
+    const float4 *lk = a.links + (size_t)k * kSapLinks;
 
-    // the site's position in the NATIVE full vectors (parity-major, 6 planes per site)
-    int xs[4];
+    // face terms: wavefront w takes the faces of directions w and w + 4, a lane a site
+    float4 fh[2][3], fu[2][3];
+    float2 fp[2];
+    if (a.update) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) xs[m] = kSapB * n[m] + b[m];
-    const int par = (xs[0] + xs[1] + xs[2] + xs[3]) & 1;
-    const int hi = half_index(a.g, xs);
-    const size_t nat = (size_t)par * 6 * a.g.vhp + (size_t)(hi >> 6) * 6 * kSB + (hi & (kSB - 1));
-
+        for (int j = 0; j < 2; ++j) {
+            const int d = 4 * j + wave, mu = d >> 1, back = d & 1;
+            // the neighbouring block, with the lattice wrap and the C* mirror shift
+            int nn[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) nn[m] = n[m];
+            const int nm = mu == 0 ? n[0] : mu == 1 ? n[1] : mu == 2 ? n[2] : n[3];
+            const int Nm = mu == 0 ? a.nb[0] : mu == 1 ? a.nb[1] : mu == 2 ? a.nb[2] : a.nb[3];
+            const bool cross = back ? nm == 0 : nm == Nm - 1;
+            const int nx = back ? (cross ? Nm - 1 : nm - 1) : (cross ? 0 : nm + 1);
+            if (mu == 0) nn[0] = nx; else if (mu == 1) nn[1] = nx; else if (mu == 2) nn[2] = nx; else nn[3] = nx;
+            nn[1] = cstar_x1(a.g, mu, cross, kSapB * nn[1]) / kSapB;
+            const float4 *src = a.faces + ((size_t)block_of(a, nn) * 8 + d) * 3 * kSapFace + lane;
+            const float4 *ul = lk + kSapFaces + d * 3 * kSapFace + lane;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                fh[j][q] = src[q * kSapFace];
+                fu[j][q] = ul[q * kSapFace];
+            }
+            fp[j] = reinterpret_cast<const float2 *>(lk + kSapFacePh)[d * kSapFace + lane];
+        }
+    }
+    float4 iu[3][3];
+    float2 ip[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int e = t + j * kSapSites, mu = e / kSapInner, ci = e % kSapInner;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) iu[j][q] = lk[(mu * 3 + q) * kSapInner + ci];
+        ip[j] = reinterpret_cast<const float2 *>(lk + kSapInnerPh)[e];
+    }
     C<float> r[12];
     if (a.rin) {
+        // the site's position in the NATIVE full vectors (parity-major, 6 planes per site)
+        int xs[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) xs[m] = kSapB * n[m] + b[m];
+        const int par = (xs[0] + xs[1] + xs[2] + xs[3]) & 1;
+        const int hi = half_index(a.g, xs);
+        const size_t nat = (size_t)par * 6 * a.g.vhp + (size_t)(hi >> 6) * 6 * kSB + (hi & (kSB - 1));
 #pragma unroll
         for (int q = 0; q < 6; ++q) {
             const float4 v = a.rin[nat + q * kSB];
@@ -125,99 +212,6 @@ __global__ __launch_bounds__(kSapSites) void k_sap_step(SapArgs a) {
         }
     } else {
         load_sp(a.rho + spinor_at(k, t), r);
-    }
-    if (a.update) {
-        // rho += 1/2 H delta over the faces of the block: the previous step's corrections live on
-        // the neighbouring blocks (the other colour).  The 8 faces of 64 sites are taken face by
-        // face, wavefront w the faces of directions w (first pass) and w + 4 (second pass), so no
-        // lane idles; each face term, formed from zero, goes through LDS (the residual tile, free
-        // until the minimal-residual steps) to its site, which adds its terms in direction order.
-        float *fb = reinterpret_cast<float *>(&rs[0][0]);  // [4 directions][24 reals][64 face sites]
-        C<float> acc[12];
-#pragma unroll
-        for (int q = 0; q < 12; ++q) acc[q] = mk(0.f, 0.f);
-#pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            {
-                // face site `lane` of direction d: b_mu on the face, the other coordinates from lane
-                const int d = 4 * pass + wave, mu = d >> 1, back = d & 1;
-                int bf[4], o = 0;
-#pragma unroll
-                for (int m = 3; m >= 0; --m) {
-                    if (m == mu) {
-                        bf[m] = back ? 0 : kSapB - 1;
-                    } else {
-                        bf[m] = (lane >> (2 * o)) & 3;
-                        ++o;
-                    }
-                }
-                const int tf = ((bf[0] * kSapB + bf[1]) * kSapB + bf[2]) * kSapB + bf[3];
-                int y[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) y[m] = kSapB * n[m] + bf[m];
-                // the neighbour across the face, with the lattice wrap and the C* mirror shift
-                const int Lm = a.g.L[mu];
-                const int ym = y[mu];
-                const bool cross = back ? ym == 0 : ym == Lm - 1;
-                const int yn = back ? (ym == 0 ? Lm - 1 : ym - 1) : (ym == Lm - 1 ? 0 : ym + 1);
-                if (mu == 0) y[0] = yn; else if (mu == 1) y[1] = yn; else if (mu == 2) y[2] = yn; else y[3] = yn;
-                y[1] = cstar_x1(a.g, mu, cross, y[1]);
-                int nn[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) nn[m] = y[m] / kSapB;
-                const int tn = ((y[0] % kSapB) * kSapB + (y[1] % kSapB)) * kSapB * kSapB + (y[2] % kSapB) * kSapB + (y[3] % kSapB);
-                C<float> nb[12], u[6], v[12];
-                float co, si;
-                load_sp(a.dlt + spinor_at(block_of(a, nn), tn), nb);
-                load_blink(a, k, d, tf, u, co, si);
-#pragma unroll
-                for (int q = 0; q < 12; ++q) v[q] = mk(0.f, 0.f);
-                accumulate_dir<float, 0>(d, nb, u, co, si, v);
-                float *dst = fb + (size_t)wave * 24 * 64 + lane;
-#pragma unroll
-                for (int q = 0; q < 12; ++q) {
-                    dst[(2 * q) * 64] = v[q].r;
-                    dst[(2 * q + 1) * 64] = v[q].i;
-                }
-            }
-            __syncthreads();
-            // this site's terms of the pass's four directions, in direction order
-#pragma unroll
-            for (int dd = 0; dd < 4; ++dd) {
-                const int d = 4 * pass + dd, mu = d >> 1, back = d & 1;
-                const int bm = mu == 0 ? b[0] : mu == 1 ? b[1] : mu == 2 ? b[2] : b[3];
-                if (back ? bm != 0 : bm != kSapB - 1) continue;  // not on this face
-                int f = 0, o = 0;
-#pragma unroll
-                for (int m = 3; m >= 0; --m) {
-                    if (m == mu) continue;
-                    f |= b[m] << (2 * o);
-                    ++o;
-                }
-                const float *src = fb + (size_t)dd * 24 * 64 + f;
-#pragma unroll
-                for (int q = 0; q < 12; ++q) acc[q] = mk(acc[q].r + src[(2 * q) * 64], acc[q].i + src[(2 * q + 1) * 64]);
-            }
-            __syncthreads();  // the pass's terms are read before the next pass (or the residual tile) overwrites them
-        }
-#pragma unroll
-        for (int q = 0; q < 12; ++q) r[q] = mk(fmaf(0.5f, acc[q].r, r[q].r), fmaf(0.5f, acc[q].i, r[q].i));
-    }
-    C<float> dl_[12];
-#pragma unroll
-    for (int q = 0; q < 12; ++q) dl_[q] = mk(0.f, 0.f);
-    // the block's inner links, read once for all minimal-residual steps (the first step's barrier
-    // orders these writes before any read)
-#pragma unroll
-    for (int mu = 0; mu < 4; ++mu) {
-        if (b[mu] == kSapB - 1) continue;
-        const int ci = inner_link(mu, t);
-        const float4 *q = a.links + ((size_t)(k * 8 + 2 * mu) * kSapLinkPlanes) * kSapSites + t;
-        lq[mu][0][ci] = q[0];
-        lq[mu][1][ci] = q[kSapSites];
-        lq[mu][2][ci] = q[2 * kSapSites];
-        const float4 ph = q[3 * kSapSites];
-        lp[mu][ci] = make_float2(ph.x, ph.y);
     }
     // the site's clover block, read once for all minimal-residual steps
     float pk[72];
@@ -233,38 +227,83 @@ __global__ __launch_bounds__(kSapSites) void k_sap_step(SapArgs a) {
         }
     }
 
+    if (a.update) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int d = 4 * j + wave;
+            C<float> h[6], u[6], w[6];
+            cplx3(fh[j][0], fh[j][1], fh[j][2], h);
+            cplx3(fu[j][0], fu[j][1], fu[j][2], u);
+            if (d & 1) link_adj_mul(u, fp[j].x, fp[j].y, h, w);
+            else link_mul(u, fp[j].x, fp[j].y, h, w);
+            float4 *dst = rs + d * 3 * kSapFace + lane;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) dst[q * kSapFace] = pair4(w[2 * q], w[2 * q + 1]);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int e = t + j * kSapSites, mu = e / kSapInner, ci = e % kSapInner;
+        C<float> u[6], M[9];
+        cplx3(iu[j][0], iu[j][1], iu[j][2], u);
+        third_row(u, M + 6);
+        const C<float> ph = mk(ip[j].x, ip[j].y);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) M[q] = ph * (q < 6 ? u[q < 6 ? q : 0] : M[q]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) lq[mu][q][ci] = pair4(M[2 * q], M[2 * q + 1]);
+        lr[mu][ci] = make_float2(M[8].r, M[8].i);
+    }
+    if (a.update) {
+        // rho += 1/2 H delta: a site adds the terms of the faces it is on, in direction order
+        __syncthreads();
+        C<float> acc[12];
+#pragma unroll
+        for (int q = 0; q < 12; ++q) acc[q] = mk(0.f, 0.f);
+        each_dir([&](auto dn) {
+            constexpr int N = dn, mu = N >> 1, back = N & 1;
+            if (b[mu] != (back ? 0 : kSapB - 1)) return;  // not on this face
+            const float4 *src = rs + N * 3 * kSapFace + face_site(mu, b);
+            C<float> w[6];
+            cplx3(src[0], src[kSapFace], src[2 * kSapFace], w);
+            add_rows_n<float, 0, N>(w, acc);
+        });
+#pragma unroll
+        for (int q = 0; q < 12; ++q) r[q] = mk(fmaf(0.5f, acc[q].r, r[q].r), fmaf(0.5f, acc[q].i, r[q].i));
+        __syncthreads();  // the terms are read before the residual takes their place
+    }
+    C<float> dl_[12];
+#pragma unroll
+    for (int q = 0; q < 12; ++q) dl_[q] = mk(0.f, 0.f);
+
+    // Two barriers a step: the second orders this step's reads of rs before the next step's writes, the first the
+    // reads of red before the next writes of it (and the links before their first use).
 #pragma nounroll
     for (int it = 0; it < a.nmr; ++it) {
-        __syncthreads();  // the previous step's reads of rs are done
 #pragma unroll
-        for (int q = 0; q < 6; ++q) rs[q][t] = make_float4(r[2 * q].r, r[2 * q].i, r[2 * q + 1].r, r[2 * q + 1].i);
+        for (int q = 0; q < 6; ++q) rs[q * kSapSites + t] = pair4(r[2 * q], r[2 * q + 1]);
         __syncthreads();
         // v = D_blk r = A r - 1/2 sum over the neighbours inside the block
         C<float> v[12], hs[12];
 #pragma unroll
         for (int q = 0; q < 12; ++q) hs[q] = mk(0.f, 0.f);
-#pragma unroll
-        for (int d = 0; d < 8; ++d) {
-            const int mu = d >> 1, back = d & 1;
-            const int bm = mu == 0 ? b[0] : mu == 1 ? b[1] : mu == 2 ? b[2] : b[3];
-            if (back ? bm == 0 : bm == kSapB - 1) continue;  // that neighbour is outside the block
-            const int stride = mu == 0 ? 64 : mu == 1 ? 16 : mu == 2 ? 4 : 1;
+        each_dir([&](auto dn) {
+            constexpr int N = dn, mu = N >> 1, back = N & 1;
+            constexpr int stride = mu == 0 ? 64 : mu == 1 ? 16 : mu == 2 ? 4 : 1;
+            if (b[mu] == (back ? 0 : kSapB - 1)) return;  // that neighbour is outside the block
             const int tn = back ? t - stride : t + stride;
-            C<float> nb[12], u[6];
-#pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const float4 f = rs[q][tn];
-                nb[2 * q] = mk(f.x, f.y);
-                nb[2 * q + 1] = mk(f.z, f.w);
-            }
+            C<float> nb[12], h[6], M[9], w[6];
+            cplx3(rs[tn], rs[kSapSites + tn], rs[2 * kSapSites + tn], nb);
+            cplx3(rs[3 * kSapSites + tn], rs[4 * kSapSites + tn], rs[5 * kSapSites + tn], nb + 6);
             const int ci = inner_link(mu, back ? tn : t);
-            const float4 l0 = lq[mu][0][ci], l1 = lq[mu][1][ci], l2 = lq[mu][2][ci];
-            const float2 ph = lp[mu][ci];
-            u[0] = mk(l0.x, l0.y); u[1] = mk(l0.z, l0.w);
-            u[2] = mk(l1.x, l1.y); u[3] = mk(l1.z, l1.w);
-            u[4] = mk(l2.x, l2.y); u[5] = mk(l2.z, l2.w);
-            accumulate_dir<float, 0>(d, nb, u, ph.x, ph.y, hs);
-        }
+            cplx3(lq[mu][0][ci], lq[mu][1][ci], lq[mu][2][ci], M);
+            const float4 l3 = lq[mu][3][ci];
+            const float2 l4 = lr[mu][ci];
+            M[6] = mk(l3.x, l3.y); M[7] = mk(l3.z, l3.w); M[8] = mk(l4.x, l4.y);
+            project_dir_n<float, 0, N>(nb, h);
+            full_mul<back>(M, h, w);
+            add_rows_n<float, 0, N>(w, hs);
+        });
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) block_mul(pk + 36 * blk, r + 6 * blk, v + 6 * blk);
 #pragma unroll
@@ -294,12 +333,10 @@ __global__ __launch_bounds__(kSapSites) void k_sap_step(SapArgs a) {
 #pragma unroll
         for (int q = 0; q < 12; ++q) {
             madd(dl_[q], w, r[q]);
-            const C<float> wv = w * v[q];
-            r[q] = mk(r[q].r - wv.r, r[q].i - wv.i);
+            madd(r[q], mk(-w.r, -w.i), v[q]);
         }
-        __syncthreads();  // red is read by every thread before the next step overwrites it
     }
-    // psi += delta, rho = the block residual, delta kept for the next step's face update
+    // psi += delta, rho = the block residual, the faces of delta for the next step's update
     float4 *ps = a.psi + spinor_at(k, t);
     C<float> o[12];
     if (a.first) {
@@ -311,8 +348,17 @@ __global__ __launch_bounds__(kSapSites) void k_sap_step(SapArgs a) {
         for (int q = 0; q < 12; ++q) o[q] = mk(o[q].r + dl_[q].r, o[q].i + dl_[q].i);
     }
     store_sp(ps, o);
-    store_sp(a.rho + spinor_at(k, t), r);
-    store_sp(a.dlt + spinor_at(k, t), dl_);
+    if (a.keep) store_sp(a.rho + spinor_at(k, t), r);
+    if (!a.send) return;
+    each_dir([&](auto dn) {
+        constexpr int N = dn, mu = N >> 1, back = N & 1;
+        if (b[mu] != (back ? kSapB - 1 : 0)) return;  // the neighbour's hop N does not start here
+        C<float> h[6];
+        project_dir_n<float, 0, N>(dl_, h);
+        float4 *dst = a.faces + ((size_t)k * 8 + N) * 3 * kSapFace + face_site(mu, b);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) dst[q * kSapFace] = pair4(h[2 * q], h[2 * q + 1]);
+    });
 }
 
 // Block order of the fields (once per field): site (p, i) -> block k, site t
@@ -336,16 +382,23 @@ __global__ void k_sap_fields(Geom g, int p, int4 nb4, const float4 *__restrict__
     site_coords(g, i, p, x);
     block_pos(g, nb, x, k, t);
     const size_t vhp = (size_t)g.vhp;
-#pragma unroll 1
+    const int b[4] = {t >> 6, (t >> 4) & 3, (t >> 2) & 3, t & 3};
+    float4 *lk = blinks + (size_t)k * kSapLinks;
+#pragma unroll
     for (int d = 0; d < 8; ++d) {
+        const int mu = d >> 1;
+        const bool face = b[mu] == (d & 1 ? 0 : kSapB - 1);
+        if (!face && (d & 1)) continue;  // the forward link of t - stride serves this hop
+        const int n = face ? kSapFace : kSapInner, at = face ? face_site(mu, b) : inner_link(mu, t);
+        const int list = face ? d : mu;
         const float4 *src = site_ptr(links + (size_t)d * 3 * vhp, (uint32_t)i, 3);
-        float4 *dst = blinks + ((size_t)(k * 8 + d) * kSapLinkPlanes) * kSapSites + t;
+        float4 *dst = lk + (face ? kSapFaces : 0) + list * 3 * n + at;
         dst[0] = src[0];
-        dst[kSapSites] = src[kSB];
-        dst[2 * kSapSites] = src[2 * kSB];
+        dst[n] = src[kSB];
+        dst[2 * n] = src[2 * kSB];
         float sn, cs;
         sc(omega[(size_t)d * vhp + i], sn, cs);
-        dst[3 * kSapSites] = make_float4(cs, sn, 0.f, 0.f);
+        reinterpret_cast<float2 *>(lk + (face ? kSapFacePh : kSapInnerPh))[list * n + at] = make_float2(cs, sn);
     }
     const float4 *cs = site_ptr(clov, (uint32_t)i, 18);
     float4 *cd = bclov + (size_t)k * 18 * kSapSites + t;
@@ -394,7 +447,7 @@ void sap_apply(dirac_ctx *c, void *psi, const void *r, int ncy, int nmr, hipStre
     const int4 nb4 = make_int4(nb[0], nb[1], nb[2], nb[3]);
     const int vh = (int)c->vh;
     if (!c->sap_ready) {
-        c->sap_links.alloc((size_t)nblk * 8 * kSapLinkPlanes * kSapSites * sizeof(float4));
+        c->sap_links.alloc((size_t)nblk * kSapLinks * sizeof(float4));
         c->sap_clov.alloc((size_t)nblk * 18 * kSapSites * sizeof(float4));
         for (int p = 0; p < 2; ++p)
             k_sap_fields<<<grid_for(vh), kBlock, 0, s>>>(c->g, p, nb4, (const float4 *)c->f[DIRAC_F32].links[p].p,
@@ -405,8 +458,8 @@ void sap_apply(dirac_ctx *c, void *psi, const void *r, int ncy, int nmr, hipStre
         c->sap_ready = true;
     }
     const size_t vbytes = (size_t)nblk * 6 * kSapSites * sizeof(float4);
-    c->sap_rho.alloc(3 * vbytes);  // rho, psi, delta in block order
-    float4 *rho = (float4 *)c->sap_rho.p, *pb = rho + vbytes / sizeof(float4), *dlt = pb + vbytes / sizeof(float4);
+    c->sap_rho.alloc(3 * vbytes);  // rho, psi, the faces (8 x 3 x 64 = 6 x 256) in block order
+    float4 *rho = (float4 *)c->sap_rho.p, *pb = rho + vbytes / sizeof(float4), *faces = pb + vbytes / sizeof(float4);
     // the first cycle reads the residual from the NATIVE input (no reordering pass in), and psi
     // starts as the first cycle's corrections (no zero fill)
     SapArgs a{};
@@ -415,7 +468,7 @@ void sap_apply(dirac_ctx *c, void *psi, const void *r, int ncy, int nmr, hipStre
     a.clov = (const float4 *)c->sap_clov.p;
     a.rho = rho;
     a.psi = pb;
-    a.dlt = dlt;
+    a.faces = faces;
     for (int m = 0; m < 4; ++m) a.nb[m] = nb[m];
     a.nmr = nmr;
     for (int cy = 0; cy < ncy; ++cy)
@@ -423,6 +476,8 @@ void sap_apply(dirac_ctx *c, void *psi, const void *r, int ncy, int nmr, hipStre
             a.colour = col;
             a.update = !(cy == 0 && col == 0);
             a.first = cy == 0;
+            a.keep = cy + 1 < ncy;
+            a.send = a.keep || col == 0;
             a.rin = cy == 0 ? (const float4 *)r : nullptr;
             k_sap_step<<<nblk / 2, kSapSites, 0, s>>>(a);
             HIP_CHECK(hipGetLastError());
