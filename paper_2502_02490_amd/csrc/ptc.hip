@@ -98,11 +98,11 @@ template <typename A> struct TRaw {
     float4 lk[kFullPlanes];
 };
 
-// Load what T_path x_c needs at site (p, i) with coordinates x.  Every field of r is written on
-// every path (the link is zero for the unshifted path), so the compiler keeps r in registers.
+// Load what T_path x_c needs at site (p, i) with coordinates x: the spinor, and the link of a hop (zero for the
+// unshifted path).  Every field of r is written on every path, so the compiler keeps r in registers.
 template <typename A>
-DEV void transport_load(const PtcGeom &a, const typename Act<A>::vec *xc, int p, uint32_t i, const int x[4], int path,
-                        TRaw<A> &r) {
+DEV void spinor_load(const PtcGeom &a, const typename Act<A>::vec *xc, int p, uint32_t i, const int x[4], int path,
+                     typename Act<A>::vec *sp) {
     constexpr int NP = Act<A>::planes;
     const size_t hv = half_vecs<A>(a.g.vhp);
     const int n = path - 1;  // direction index 2 mu + back (path > 0)
@@ -120,15 +120,23 @@ DEV void transport_load(const PtcGeom &a, const typename Act<A>::vec *xc, int p,
     const int q = path > 0 ? 1 - p : p;
     const typename Act<A>::vec *b = site_ptr(xc + q * hv, j, NP);
 #pragma unroll
-    for (int k = 0; k < NP; ++k) r.sp[k] = b[k * kSB];
+    for (int k = 0; k < NP; ++k) sp[k] = b[k * kSB];
+}
+DEV void full_link_load(const PtcGeom &a, int p, uint32_t i, int path, float4 *lk) {
     if (path > 0) {
-        const float4 *lb = site_ptr(a.flinks[p] + (size_t)n * kFullPlanes * a.g.vhp, i, kFullPlanes);
+        const float4 *lb = site_ptr(a.flinks[p] + (size_t)(path - 1) * kFullPlanes * a.g.vhp, i, kFullPlanes);
 #pragma unroll
-        for (int k = 0; k < kFullPlanes; ++k) r.lk[k] = ld_stream(lb + k * kSB);  // read-once stream
+        for (int k = 0; k < kFullPlanes; ++k) lk[k] = ld_stream(lb + k * kSB);  // read-once stream
     } else {
 #pragma unroll
-        for (int k = 0; k < kFullPlanes; ++k) r.lk[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int k = 0; k < kFullPlanes; ++k) lk[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
+}
+template <typename A>
+DEV void transport_load(const PtcGeom &a, const typename Act<A>::vec *xc, int p, uint32_t i, const int x[4], int path,
+                        TRaw<A> &r) {
+    spinor_load<A>(a, xc, p, i, x, path, r.sp);
+    full_link_load(a, p, i, path, r.lk);
 }
 
 DEV void unpack4(const float4 *v, int nv, float *o) {
@@ -146,17 +154,17 @@ DEV void unpack_sp(const uint4 *v, float *o) {
     for (int k = 0; k < 3; ++k) St<__hip_bfloat16>::unpack(v[k], o + 8 * k);
 }
 
-template <typename A>
-DEV void transport_compute(const TRaw<A> &r, int path, C<float> t[12]) {
+template <typename V>
+DEV void transport_compute(const V *raw, const float4 *lk, int path, C<float> t[12]) {
     float sp[24];
-    unpack_sp(r.sp, sp);
+    unpack_sp(raw, sp);
     if (path == 0) {
 #pragma unroll
         for (int k = 0; k < 12; ++k) t[k] = mk(sp[2 * k], sp[2 * k + 1]);
         return;
     }
     float lf[20];
-    unpack4(r.lk, kFullPlanes, lf);
+    unpack4(lk, kFullPlanes, lf);
     C<float> f[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) f[k] = mk(lf[2 * k], lf[2 * k + 1]);
@@ -193,7 +201,7 @@ DEV void transport_site(const PtcGeom &a, const typename Act<A>::vec *xc, int p,
                         int path, C<float> t[12]) {
     TRaw<A> r;
     transport_load<A>(a, xc, p, i, x, path, r);
-    transport_compute<A>(r, path, t);
+    transport_compute(r.sp, r.lk, path, t);
 }
 
 // Store 12 consecutive reals (reals 12 h .. 12 h + 11 of the 24, half h of the spinor) of site
@@ -295,8 +303,12 @@ constexpr int kEoIn = 1, kEoOut = 2;  // even-odd deployment flags of the layer 
 // (p < 9) are formed from this layer's accumulators in registers -- the 16x16 accumulator tile t
 // of a lane is, rounded to BF16, its B operand of depth step t on the 16x16x16 instruction -- and
 // written to zout as 9 channels; y itself is written only when store_y is set.
+// Work-groups a compute unit holds: the input gradient of a hidden first layer (8 -> 1 channels: 140 registers) fits
+// three times (1.77 -> 1.56 ms at 32^3 x 64; four with a few spills 1.63); the others have more registers or little to wait for.
+constexpr int layer_groups(int nin, int nm, bool zout) { return nin >= 4 && nm == 1 && !zout ? 3 : 2; }
+
 template <int NIN, int NM, bool ZOUT, typename AI, typename AO>
-__global__ __launch_bounds__(256, 2) void k_ptc_layer_mfma(PtcGeom a, int nout, const uint4 *__restrict__ Af,
+__global__ __launch_bounds__(256, layer_groups(NIN, NM, ZOUT)) void k_ptc_layer_mfma(PtcGeom a, int nout, const uint4 *__restrict__ Af,
                                                         const typename Act<AI>::vec *__restrict__ xin,
                                                         typename Act<AO>::vec *__restrict__ yout,
                                                         const uint2 *__restrict__ Az, float4 *__restrict__ zout,
@@ -327,18 +339,7 @@ __global__ __launch_bounds__(256, 2) void k_ptc_layer_mfma(PtcGeom a, int nout, 
         for (int t = 0; t < NM; ++t)
 #pragma unroll
             for (int col = 0; col < 3; ++col) acc[t][col] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        auto pair_of = [&](int q) {
-            const int pr = 4 * q + g;
-            if constexpr (NPAIR % 4 != 0) return pr < NPAIR ? pr : NPAIR - 1;
-            return pr;
-        };
-        auto load = [&](int q, TRaw<AI> &r) {
-            const int pair = pair_of(q);
-            transport_load<AI>(a, xin + (size_t)(pair % NIN) * chin, p, ic, x, pair / NIN, r);
-        };
-        auto step = [&](int q, const TRaw<AI> &r) {
-            C<float> tr[12];
-            transport_compute<AI>(r, pair_of(q) / NIN, tr);
+        auto mul = [&](int q, const C<float> tr[12]) {
             bf16x8_t b[3];
 #pragma unroll
             for (int col = 0; col < 3; ++col) {
@@ -356,25 +357,66 @@ __global__ __launch_bounds__(256, 2) void k_ptc_layer_mfma(PtcGeom a, int nout, 
                     acc[t][col] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, b[col], acc[t][col], 0, 0, 0);
             }
         };
-        // software pipeline over three register sets in turn: the loads of K step q + 2 are
-        // issued before the transport and the matrix-core work of step q
-        // kEoIn: the input's odd half is zero, so at an even site every path but the unshifted
-        // one transports zeros; its K steps after those of path 0 add exact zeros and are skipped
-        const int nk = ((eo & kEoIn) && p == 0) ? (NIN + 3) / 4 : NK;
-        TRaw<AI> ra, rb, rc;
-        load(0, ra);
-        if (1 < nk) load(1, rb);
-#pragma nounroll
-        for (int q = 0; q < nk; q += 3) {
-            if (q + 2 < nk) load(q + 2, rc);
-            step(q, ra);
-            if (q + 1 < nk) {
-                if (q + 3 < nk) load(q + 3, ra);
-                step(q + 1, rb);
+        if constexpr (NIN >= 4) {
+            // Whole K steps per path: the steps unrolled, so that direction and neighbour are known at compile time,
+            // a link read once for the steps of its path, spinors two steps ahead.  32^3 x 64, 8 -> 8 channels with
+            // contractions 2.09 -> 1.57 ms (5,350 -> 3,900 VALU instructions a 16-site tile, 63 % of the SIMD cycles;
+            // without the scheduling fence, which keeps the loads ahead, 1.72), FP32 2.03 -> 1.77 ms (11 GB
+            // fetched past L2 at 6 TB/s; taking the tiles in the order of the weight gradient or in
+            // cubes per XCD fetches up to 15 % less in the same time).
+            constexpr int QP = NIN / 4, NLK = QP == 1 ? 3 : 2;  // steps of a path; links held: of the paths of q .. q + 2
+            typename Act<AI>::vec sp[3][Act<AI>::planes];
+            float4 lk[NLK][kFullPlanes];
+            auto load = [&](int q) {
+                const int path = q / QP;
+                spinor_load<AI>(a, xin + (size_t)(4 * (q % QP) + g) * chin, p, ic, x, path, sp[q % 3]);
+                if (q % QP == 0) full_link_load(a, p, ic, path, lk[path % NLK]);
+            };
+            load(0);
+            load(1);
+#pragma unroll
+            for (int q = 0; q < NK; ++q) {
+                if (q + 2 < NK) load(q + 2);
+                __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the step's arithmetic
+                C<float> tr[12];
+                transport_compute(sp[q % 3], lk[q / QP % NLK], q / QP, tr);
+                mul(q, tr);
             }
-            if (q + 2 < nk) {
-                if (q + 4 < nk) load(q + 4, rb);
-                step(q + 2, rc);
+        } else {
+            auto pair_of = [&](int q) {
+                const int pr = 4 * q + g;
+                if constexpr (NPAIR % 4 != 0) return pr < NPAIR ? pr : NPAIR - 1;
+                return pr;
+            };
+            auto load = [&](int q, TRaw<AI> &r) {
+                const int pair = pair_of(q);
+                transport_load<AI>(a, xin + (size_t)(pair % NIN) * chin, p, ic, x, pair / NIN, r);
+            };
+            auto step = [&](int q, const TRaw<AI> &r) {
+                C<float> tr[12];
+                transport_compute(r.sp, r.lk, pair_of(q) / NIN, tr);
+                mul(q, tr);
+            };
+            // software pipeline over three register sets in turn: the loads of K step q + 2 are
+            // issued before the transport and the matrix-core work of step q
+            // kEoIn (a network's first layer, one channel): the input's odd half is zero, so at an even site every
+            // path but the unshifted one transports zeros; its K steps after that of path 0 add exact zeros and are skipped
+            const int nk = ((eo & kEoIn) && p == 0) ? (NIN + 3) / 4 : NK;
+            TRaw<AI> ra, rb, rc;
+            load(0, ra);
+            if (1 < nk) load(1, rb);
+#pragma nounroll
+            for (int q = 0; q < nk; q += 3) {
+                if (q + 2 < nk) load(q + 2, rc);
+                step(q, ra);
+                if (q + 1 < nk) {
+                    if (q + 3 < nk) load(q + 3, ra);
+                    step(q + 1, rb);
+                }
+                if (q + 2 < nk) {
+                    if (q + 4 < nk) load(q + 4, rb);
+                    step(q + 2, rc);
+                }
             }
         }
         // lane (g, site) holds rows m = 16 t + 4 g + r, r < 4: channel 2 t + g / 2, spins
@@ -400,6 +442,16 @@ __global__ __launch_bounds__(256, 2) void k_ptc_layer_mfma(PtcGeom a, int nout, 
             // kEoOut: only the even half of the network's output is wanted, which reads z_0 at even
             // sites and z_1 .. z_8 at odd ones
             const bool eo_out = (eo & kEoOut) != 0;
+            s16x4_t yb[NM][3];
+#pragma unroll
+            for (int t = 0; t < NM; ++t)
+#pragma unroll
+                for (int col = 0; col < 3; ++col) {
+                    bf16x4_t b;
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) b[rr] = (__bf16)acc[t][col][rr];
+                    yb[t][col] = __builtin_bit_cast(s16x4_t, b);
+                }
             const int ntz = eo_out && p == 0 ? 1 : kZTiles;
 #pragma nounroll
             for (int tz = 0; tz < ntz; ++tz) {
@@ -410,13 +462,8 @@ __global__ __launch_bounds__(256, 2) void k_ptc_layer_mfma(PtcGeom a, int nout, 
                 for (int t = 0; t < NM; ++t) {
                     const s16x4_t A = __builtin_bit_cast(s16x4_t, Az[(tz * NM + t) * 64 + lane]);
 #pragma unroll
-                    for (int col = 0; col < 3; ++col) {
-                        bf16x4_t b;
-#pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) b[rr] = (__bf16)acc[t][col][rr];
-                        zacc[col] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, __builtin_bit_cast(s16x4_t, b),
-                                                                              zacc[col], 0, 0, 0);
-                    }
+                    for (int col = 0; col < 3; ++col)
+                        zacc[col] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, yb[t][col], zacc[col], 0, 0, 0);
                 }
                 const int pz = 2 * tz + (g >> 1);
                 const bool want = !eo_out || (p == 0 ? pz == 0 : pz > 0);
@@ -695,7 +742,7 @@ __global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *_
         for (int grp = 0; grp < W::NG; ++grp) {
             if (8 * grp + wave < W::NPAIR) {
                 C<float> t[12];
-                transport_compute<float>(raw, (8 * grp + wave) / NT, t);
+                transport_compute(raw.sp, raw.lk, (8 * grp + wave) / NT, t);
                 // an even lane packs the real parts of its own and the next site (row 2 s), an odd lane
                 // the imaginary parts of the previous and its own site (row 2 s + 1)
                 const bool odd = (lane & 1) != 0;
@@ -916,7 +963,7 @@ template <int NIN, int NM>
 void launch_layer(const PtcGeom &a, int nout, const uint4 *Af, const void *x, void *y, const ZArgs &zo, Io io,
                   hipStream_t s) {
     const int nblk = 2 * (int)((a.g.vh + 63) / 64);
-    const int grid = std::min(nblk, 2 * compute_units());
+    const int grid = std::min(nblk, layer_groups(NIN, NM, zo.z != nullptr) * compute_units());
     if (zo.z) {
         if (io == Io::In) launch_io<NIN, NM, true, float, bf16s>(grid, a, nout, Af, x, y, zo, s);
         else if (io == Io::Mid) launch_io<NIN, NM, true, bf16s, bf16s>(grid, a, nout, Af, x, y, zo, s);
