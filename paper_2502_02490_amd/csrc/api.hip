@@ -162,9 +162,10 @@ dirac_status dirac_create(const dirac_params *prm, const void *su3_links, const 
         c->g.h1 = prm->dims[1] / 2;
         // scratch, released on return: the compressed links and the clover field are built from it
         planes.alloc_field(dl::link_planes_bytes(c->g));
-        dl::links_to_planes(c, su3_links, planes.p, s);
-        dl::import_links(c, planes.p, u1_angles, s);
-        dl::clover_build(c, planes.p, u1_angles, s);
+        dl::links_to_planes(c, su3_links, u1_angles, planes.p, s);
+        const double *theta = u1_angles ? dl::theta_planes(planes.p, c->g) : nullptr;
+        dl::import_links(c, planes.p, theta, s);
+        dl::clover_build(c, planes.p, theta, s);
         const int64_t bad = dl::clover_invert_parity(c, 1, s);
         HIP_CHECK(hipStreamSynchronize(s));
         planes.retire();  // read on `s` alone

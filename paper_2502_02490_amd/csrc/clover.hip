@@ -13,120 +13,94 @@ struct M3 {
     C<double> m[9];
 };
 
-// link U_mu of site (parity, half index) from the plane copy of the gauge field (links_to_planes)
-DEV M3 ld(const Geom &g, const double2 *__restrict__ U, int parity, int i, int mu) {
-    asm volatile("" : "+v"(i));  // a link used twice is read twice (L1), not kept in 36 registers between
-    const double2 *u = site_ptr(U + (size_t)(4 * parity + mu) * 9 * g.vhp, (uint32_t)i, 9);
-    M3 r;
+// t = t b or, DAG, t b^dag, row by row: one row more than t and b in registers
+template <bool DAG>
+DEV void mul_right(M3 &t, const M3 &b) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        double2 v = u[k * kSB];
-        r.m[k] = mk(v.x, v.y);
+    for (int i = 0; i < 3; ++i) {
+        C<double> r[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            auto B = [&](int k) { return DAG ? conj(b.m[3 * j + k]) : b.m[3 * k + j]; };
+            r[j] = t.m[3 * i] * B(0);
+            madd(r[j], t.m[3 * i + 1], B(1));
+            madd(r[j], t.m[3 * i + 2], B(2));
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) t.m[3 * i + j] = r[j];
     }
-    return r;
-}
-DEV M3 mul(const M3 &a, const M3 &b) {  // a b
-    M3 r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            C<double> s = a.m[3 * i] * b.m[j];
-            madd(s, a.m[3 * i + 1], b.m[3 + j]);
-            madd(s, a.m[3 * i + 2], b.m[6 + j]);
-            r.m[3 * i + j] = s;
-        }
-    return r;
-}
-DEV M3 mul_nd(const M3 &a, const M3 &b) {  // a b^dag
-    M3 r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            C<double> s = a.m[3 * i] * conj(b.m[3 * j]);
-            madd(s, a.m[3 * i + 1], conj(b.m[3 * j + 1]));
-            madd(s, a.m[3 * i + 2], conj(b.m[3 * j + 2]));
-            r.m[3 * i + j] = s;
-        }
-    return r;
-}
-DEV M3 mul_dd(const M3 &a, const M3 &b) {  // a^dag b^dag
-    M3 r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            C<double> s = conj_mul(a.m[i], conj(b.m[3 * j]));
-            cmadd(s, a.m[3 + i], conj(b.m[3 * j + 1]));
-            cmadd(s, a.m[6 + i], conj(b.m[3 * j + 2]));
-            r.m[3 * i + j] = s;
-        }
-    return r;
-}
-DEV M3 mul_dn(const M3 &a, const M3 &b) {  // a^dag b
-    M3 r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            C<double> s = conj_mul(a.m[i], b.m[j]);
-            cmadd(s, a.m[3 + i], b.m[3 + j]);
-            cmadd(s, a.m[6 + i], b.m[6 + j]);
-            r.m[3 * i + j] = s;
-        }
-    return r;
 }
 
 // F'_{mu nu}(x) = c_sw (Q - Q^dag)/8 + c_qed qhat (q - q*)/8, Q / q the sum of the four
 // plaquette leaves at x in the (mu, nu) plane from U / from exp(i theta).  F' is anti-Hermitian: out
 // holds its 9 independent reals, Im F_00, Im F_11, Im F_22, then (re, im) of F_01, F_02, F_12.
-template <int mu, int nu>
+//
+// Leaf l walks the steps c = l, l + 1, .. (mod 4) of +mu, +nu, -mu, -nu round from x and back, the links multiplied from
+// the right as they are met: a rolled loop of 16 links, which holds the sum, the product and one link.
 DEV void plane_field(const Geom &g, int p, const double2 *__restrict__ U, const double *__restrict__ th, const int x[4],
-                     double csw, double cq, double out[9]) {
-    struct At {
-        int i, lam;
-    };
-    auto at = [&](int dm, int dn) {
-        int y[4] = {x[0], x[1], x[2], x[3]};
-        // each step that crosses the boundary of a C* direction also moves x1 (the shifts commute)
-        auto step = [&](int d, int k) {
-            if (k == 0) return;
-            const bool cross = k > 0 ? y[d] == g.L[d] - 1 : y[d] == 0;
-            y[d] = k > 0 ? wrap_up(y[d], g.L[d]) : wrap_dn(y[d], g.L[d]);
-            y[1] = cstar_x1(g, d, cross, y[1]);
-        };
-        step(mu, dm);
-        step(nu, dn);
-        return At{half_index(g, y), lex_index(g, y)};
-    };
-    const At x0 = at(0, 0), xpm = at(1, 0), xpn = at(0, 1), xmm = at(-1, 0), xmn = at(0, -1);
-    const At xmm_pn = at(-1, 1), xmm_mn = at(-1, -1), xpm_mn = at(1, -1);
-    // sites an odd number of steps away have the other parity
-    auto e = [&](const At &y, int d) { return ld(g, U, p, y.i, d); };
-    auto o = [&](const At &y, int d) { return ld(g, U, 1 - p, y.i, d); };
-    // each leaf as a chain of products with one more link at a time (two halves multiplied at the end
-    // need one more matrix in registers)
+                     const double2 (*star)[9][kSB], int lane, int mu, int nu, double csw, double cq, double out[9]) {
+    const bool u1 = th && cq != 0.0;
+    int y[4] = {x[0], x[1], x[2], x[3]};
     M3 q, t;
-    auto add = [&]() {
+    double ang = 0.0, sines = 0.0;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) q.m[k] = q.m[k] + t.m[k];
-    };
-    q = mul(e(x0, mu), o(xpm, nu));
-    q = mul_nd(q, o(xpn, mu));
-    q = mul_nd(q, e(x0, nu));
-    t = mul_nd(e(x0, nu), e(xmm_pn, mu));
-    t = mul_nd(t, o(xmm, nu));
-    t = mul(t, o(xmm, mu));
-    add();
-    t = mul_dd(o(xmm, mu), e(xmm_mn, nu));
-    t = mul(t, e(xmm_mn, mu));
-    t = mul(t, o(xmn, nu));
-    add();
-    t = mul_dn(o(xmn, nu), o(xmn, mu));
-    t = mul(t, e(xpm_mn, nu));
-    t = mul_nd(t, e(x0, mu));
-    add();
+    for (int k = 0; k < 9; ++k) q.m[k] = t.m[k] = mk(0.0, 0.0);
+#pragma nounroll
+    for (int n = 0; n < 16; ++n) {
+        const int c = ((n >> 2) + n) & 3, d = c & 1 ? nu : mu;
+        const bool back = c >= 2;
+        // one step along d; one that crosses the boundary of a C* direction also moves x1
+        int z[4];
+        bool cross = false;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int zm = back ? wrap_dn(y[m], g.L[m]) : wrap_up(y[m], g.L[m]);
+            cross = cross || (m == d && (back ? zm > y[m] : zm < y[m]));
+            z[m] = m == d ? zm : y[m];
+        }
+        z[1] = cstar_x1(g, d, cross, z[1]);
+        int at[4];  // the site the link starts from
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            at[m] = back ? z[m] : y[m];
+            y[m] = z[m];
+        }
+        const int par = p ^ ((n + (back ? 1 : 0)) & 1), i = half_index(g, at), s = n & 3;
+        M3 u;
+        if (s == 0 || s == 3) {
+            const int e = 2 * d + ((s == 0) == back);
+#pragma unroll
+            for (int k = 0; k < 9; ++k) u.m[k] = mk(star[e][k][lane].x, star[e][k][lane].y);
+        } else {
+            const double2 *q9 = site_ptr(U + (size_t)(4 * par + d) * 9 * g.vhp, (uint32_t)i, 9);
+#pragma unroll
+            for (int k = 0; k < 9; ++k) u.m[k] = mk(q9[k * kSB].x, q9[k * kSB].y);
+        }
+        if (u1) {
+            const double a = th[(size_t)(4 * par + d) * g.vhp + i];
+            ang += back ? -a : a;
+        }
+        if (s == 0) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) t.m[3 * i + j] = back ? conj(u.m[3 * j + i]) : u.m[3 * i + j];
+        } else if (back) {
+            mul_right<true>(t, u);
+        } else {
+            mul_right<false>(t, u);
+        }
+        if (s == 3) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) q.m[k] = q.m[k] + t.m[k];
+            if (u1) {
+                double sn, cs;
+                sc(ang, sn, cs);
+                sines += sn;
+                ang = 0.0;
+            }
+        }
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a) out[a] = (csw * 0.125) * (q.m[4 * a].i - (-q.m[4 * a].i));
     int k = 3;
@@ -139,19 +113,8 @@ DEV void plane_field(const Geom &g, int p, const double2 *__restrict__ U, const 
             out[k + 1] = f.i;
             k += 2;
         }
-    if (th && cq != 0.0) {
-        auto T = [&](const At &y, int d) { return th[(size_t)y.lam * 4 + d]; };
-        const double a1 = T(x0, mu) + T(xpm, nu) - T(xpn, mu) - T(x0, nu);
-        const double a2 = T(x0, nu) - T(xmm_pn, mu) - T(xmm, nu) + T(xmm, mu);
-        const double a3 = -T(xmm, mu) - T(xmm_mn, nu) + T(xmm_mn, mu) + T(xmn, nu);
-        const double a4 = -T(xmn, nu) + T(xmn, mu) + T(xpm_mn, nu) - T(x0, mu);
-        // (q - q*) / 8 = i Im(q) / 4
-        double s1, s2, s3, s4, c;
-        sc(a1, s1, c);
-        sc(a2, s2, c);
-        sc(a3, s3, c);
-        sc(a4, s4, c);
-        const double im = cq * 0.25 * (s1 + s2 + s3 + s4);
+    if (u1) {
+        const double im = cq * 0.25 * sines;  // (q - q*) / 8 = i Im(q) / 4
 #pragma unroll
         for (int a = 0; a < 3; ++a) out[a] += im;
     }
@@ -162,34 +125,61 @@ DEV void plane_field(const Geom &g, int p, const double2 *__restrict__ U, const 
 // term (i/4) sum sigma_{mu nu} F_{mu nu} is, per chirality block, [[G3, G1 - i G2], [G1 + i G2, -G3]]:
 //   block +: G1 = (i/2)(F01 - F23), G2 = (i/2)(F02 + F13), G3 = (i/2)(F03 - F12)
 //   block -: G1 = -(i/2)(F01 + F23), G2 = -(i/2)(F02 - F13), G3 = -(i/2)(F03 + F12)
-// A work-group of six wavefronts takes 64 sites, one plane (mu, nu) per wavefront (the 12 links of a
-// plane and its products fit the registers; one thread for all six planes spilled 6 KB per lane), the
-// fields meet in LDS, and wavefront w forms planes 3 w .. 3 w + 2 of block + and of block -.  Bound by
-// the latency of its chain of link loads and FP64 products (7800 FMAs and 864 16-byte loads per
-// site: 0.15 ms per parity at full rates) at 1.5 wavefronts per SIMD.  At 24^3 x 48, both parities:
-// 4.0 -> 1.07 ms.
+// A work-group of twelve wavefronts takes two blocks of 64 sites, one plane (mu, nu) and block per wavefront; the
+// eight links at a site, which its planes use 48 times, are staged in LDS (one work-group on a CU: three
+// wavefronts on each SIMD; work-groups of six wavefronts, on 2 + 2 + 1 + 1 SIMDs, ran one at a time even where two
+// fitted), the fields meet there afterwards, and wavefront w forms planes 3 w .. 3 w + 2 of block + and of
+// block - of its sites.  Bound by issue and the latency of its chain of products (16 steps of about 190 VALU
+// instructions; loading all links from the own site or leaving the products out saves 10-20 %), against 0.15 ms
+// for the FP64 operations alone.  24^3 x 48, a parity: 515 -> 456 us; 64 x 32^3 1.51 -> 1.35 ms.
 constexpr int kFReals = 9;
-__global__ __launch_bounds__(384, 2) void k_clover_build(Geom g, int p, const double2 *__restrict__ U,
+__global__ __launch_bounds__(768, 3) void k_clover_build(Geom g, int p, const double2 *__restrict__ U,
                                                          const double *__restrict__ th, double csw, double cq,
                                                          double diag, double2 *__restrict__ out) {
-    __shared__ double fs[6][kFReals][kSB];
-    const int lane = threadIdx.x & (kSB - 1), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int i = min((int)blockIdx.x * kSB + lane, g.vh - 1);  // lanes past the end repeat the last site
+    __shared__ double2 stars[2][8][9][kSB];  // slot 2 mu + back: the link from x or into x; then the fields
+    const int lane = threadIdx.x & (kSB - 1), w12 = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int sub = w12 >= 6, w = w12 - 6 * sub;
+    const int first = 2 * xcd_block((int)gridDim.x);
+    if (first * kSB >= g.vh) return;  // the whole work-group
+    double2 (*star)[9][kSB] = stars[sub];
+    double (*fs)[kFReals][kSB] = reinterpret_cast<double (*)[kFReals][kSB]>(&star[0][0][0]);
+    const int blk = first + sub;
+    const int i = min(blk * kSB + lane, g.vh - 1);  // lanes past the end repeat the last site
     int x[4];
     site_coords(g, i, p, x);
-    double f[kFReals];
-    switch (w) {
-        case 0: plane_field<0, 1>(g, p, U, th, x, csw, cq, f); break;
-        case 1: plane_field<0, 2>(g, p, U, th, x, csw, cq, f); break;
-        case 2: plane_field<0, 3>(g, p, U, th, x, csw, cq, f); break;
-        case 3: plane_field<1, 2>(g, p, U, th, x, csw, cq, f); break;
-        case 4: plane_field<1, 3>(g, p, U, th, x, csw, cq, f); break;
-        default: plane_field<2, 3>(g, p, U, th, x, csw, cq, f); break;
+    {
+        // the 72 planes of the star, 12 a wavefront: of slots e0 and e0 + 1
+        const int e0 = 12 * w / 9, n0 = 9 * (e0 + 1) - 12 * w;
+        const double2 *src[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int e = e0 + j, mu = e >> 1, back = e & 1;
+            int y[4];
+            bool cross = false;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int ym = back ? wrap_dn(x[m], g.L[m]) : x[m];
+                cross = cross || (m == mu && ym > x[m]);
+                y[m] = m == mu ? ym : x[m];
+            }
+            y[1] = cstar_x1(g, mu, cross, y[1]);
+            src[j] = site_ptr(U + (size_t)(4 * (p ^ back) + mu) * 9 * g.vhp, (uint32_t)half_index(g, y), 9);
+        }
+        double2 v[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) v[k] = k < n0 ? src[0][(9 - n0 + k) * kSB] : src[1][(k - n0) * kSB];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) star[e0][0][(9 - n0 + k) * kSB + lane] = v[k];
+        __syncthreads();
     }
+    const int mu = w < 3 ? 0 : w < 5 ? 1 : 2, nu = w < 3 ? w + 1 : w < 5 ? w - 1 : 3;  // 01 02 03 12 13 23
+    double f[kFReals];
+    plane_field(g, p, U, th, x, star, lane, mu, nu, csw, cq, f);
+    __syncthreads();  // the star is read before the fields take its place
 #pragma unroll
     for (int k = 0; k < kFReals; ++k) fs[w][k][lane] = f[k];
     __syncthreads();
-    if ((int)blockIdx.x * kSB + lane >= g.vh) return;  // no barrier follows
+    if (blk * kSB + lane >= g.vh) return;  // no barrier follows
     // element k = 3 a + b of the anti-Hermitian field of plane n
     auto F = [&](int n, int k) -> C<double> {
         const int a = k / 3, b = k % 3;
@@ -398,7 +388,7 @@ void clover_build(dirac_ctx *c, const void *planes, const double *theta, hipStre
     const double diag = 1.0 / (2.0 * c->p.kappa);
     for (int p = 0; p < 2; ++p) {
         f.clov[p].alloc_field((size_t)72 * sizeof(double) * c->g.vhp);
-        k_clover_build<<<c->g.vhp / kSB, 384, 0, s>>>(c->g, p, (const double2 *)planes, theta, c->p.csw,
+        k_clover_build<<<((c->g.vhp / kSB + 1) / 2 + 7) & ~7, 768, 0, s>>>(c->g, p, (const double2 *)planes, theta, c->p.csw,
                                                       c->p.csw_qed * c->p.qhat, diag, (double2 *)f.clov[p].p);
     }
     HIP_CHECK(hipGetLastError());

@@ -13,10 +13,11 @@ namespace {
 // The LEX gauge field [V][4][9] as planes, per parity and direction [block][9][64 sites] of complex
 // numbers, from which the clover field and the compressed links are built with coalesced reads.
 // 128 consecutive LEX sites are the 64 even and 64 odd sites of one site block: they are read as they
-// lie (72 KB, in four pieces of one direction each) and go through LDS.  Bandwidth-bound: 1152 B per
-// site; 0.21 ms at 24^3 x 48 (3.6 TB/s).
+// lie (72 KB, in four pieces of one direction each) and go through LDS; the angles follow in planes of
+// reals.  Bandwidth-bound: 1216 B per site; 0.22 ms at 24^3 x 48 (3.7 TB/s).
 __global__ __launch_bounds__(kBlock) void k_link_planes(Geom g, const double2 *__restrict__ U,
-                                                        double2 *__restrict__ planes) {
+                                                        const double *__restrict__ theta,
+                                                        double2 *__restrict__ planes, double *__restrict__ tp) {
     __shared__ double2 t[2 * kSB * 9];
     const int i0 = (int)blockIdx.x * kSB;
     const int ns = 2 * min(kSB, g.vh - i0);  // sites of this block
@@ -38,6 +39,9 @@ __global__ __launch_bounds__(kBlock) void k_link_planes(Geom g, const double2 *_
         }
         __syncthreads();
     }
+    if (!theta || 2 * lane >= ns) return;
+    for (int k = w; k < 8; k += kBlock / kSB)
+        tp[(size_t)k * g.vhp + i0 + lane] = theta[((size_t)2 * i0 + 2 * lane + (odd ^ (k >> 2))) * 4 + (k & 3)];
 }
 
 // For site x of parity p (half index i) and direction mu:
@@ -66,13 +70,13 @@ __global__ __launch_bounds__(kBlock) void k_import_links(Geom g, int p, const do
                 y[mu] = wrap_dn(y[mu], g.L[mu]);
                 y[1] = cstar_x1(g, mu, cross, y[1]);  // C*: the link behind x may sit in the mirror copy
             }
-            const int lam = lex_index(g, y);
-            const double2 *u = site_ptr(U + (size_t)(4 * (p ^ back) + mu) * 9 * vhp, (uint32_t)half_index(g, y), 9);
+            const int n = 4 * (p ^ back) + mu, j = half_index(g, y);
+            const double2 *u = site_ptr(U + (size_t)n * 9 * vhp, (uint32_t)j, 9);
             const int dir = 2 * mu + back;
             double2 *dst = site_ptr(planes + (size_t)dir * 6 * vhp, (uint32_t)i, 6);
 #pragma unroll
             for (int k = 0; k < 6; ++k) dst[k * kSB] = u[k * kSB];
-            double w = (theta ? qhat * theta[(size_t)lam * 4 + mu] : 0.0) + (y[mu] == g.L[mu] - 1 ? ph[mu] : 0.0);
+            double w = (theta ? qhat * theta[n * vhp + j] : 0.0) + (y[mu] == g.L[mu] - 1 ? ph[mu] : 0.0);
             omega[(size_t)dir * vhp + i] = w;
             if (!back) {
                 // deviation from SU(3): max |U U^dag - 1| and |det U - 1|; the row-2 rebuild needs det U = 1
@@ -334,8 +338,9 @@ void openqxd_links_to_lex(const Geom &g, const double *u_odd, const double *a_od
 
 size_t link_plane_bytes(dirac_prec pr) { return pr == DIRAC_F64 ? 96 : pr == DIRAC_F32 ? 48 : 24; }
 
-void links_to_planes(const dirac_ctx *c, const void *su3_links, void *planes, hipStream_t s) {
-    k_link_planes<<<c->g.vhp / kSB, kBlock, 0, s>>>(c->g, (const double2 *)su3_links, (double2 *)planes);
+void links_to_planes(const dirac_ctx *c, const void *su3_links, const double *theta, void *planes, hipStream_t s) {
+    k_link_planes<<<c->g.vhp / kSB, kBlock, 0, s>>>(c->g, (const double2 *)su3_links, theta, (double2 *)planes,
+                                                    theta_planes(planes, c->g));
     HIP_CHECK(hipGetLastError());
 }
 

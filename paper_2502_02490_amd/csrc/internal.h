@@ -133,9 +133,11 @@ inline int grid_xcd(int64_t n) { return (grid_for(n) + 7) & ~7; }
 size_t link_plane_bytes(dirac_prec pr);  // bytes of one 12-real link plane set, per site and direction
 
 // fields.hip
-// the LEX gauge field as per-parity planes of complex numbers (link_planes_bytes of scratch)
-void links_to_planes(const dirac_ctx *c, const void *su3_links, void *planes, hipStream_t s);
-inline size_t link_planes_bytes(const Geom &g) { return (size_t)2 * 4 * 9 * 16 * g.vhp; }
+// the LEX gauge field as per-parity planes of complex numbers, then the angles (theta, if any) likewise
+// (link_planes_bytes of scratch); import_links and clover_build take the planes of both
+void links_to_planes(const dirac_ctx *c, const void *su3_links, const double *theta, void *planes, hipStream_t s);
+inline size_t link_planes_bytes(const Geom &g) { return (size_t)2 * 4 * (9 * 16 + 8) * g.vhp; }
+inline double *theta_planes(void *planes, const Geom &g) { return (double *)planes + (size_t)2 * 4 * 9 * 2 * g.vhp; }
 void import_links(dirac_ctx *c, const void *planes, const double *theta, hipStream_t s);
 // openQxD odd-point gauge storage (u_odd [V/2][8][3][3], a_odd [V/2][8] or NULL) to LEX [V][4] arrays
 void openqxd_links_to_lex(const Geom &g, const double *u_odd, const double *a_odd, double *U, double *th,
