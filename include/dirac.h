@@ -122,7 +122,9 @@ typedef struct {
 /* Create a context: copies the gauge field, compresses the links (two rows of
  * SU(3) plus one phase per link), builds the clover field on the device and
  * inverts its odd-site blocks.  Returns DIRAC_ESINGULAR if an odd-site block is
- * singular (the context is still created and must be destroyed).  Blocking. */
+ * singular (the context is still created and must be destroyed).  Blocking.
+ * Field memory of a destroyed context is kept for the next one, at most 1/32 of the device's
+ * memory, and given back when an allocation of the library fails. */
 dirac_status dirac_create(const dirac_params *params, const void *su3_links, const double *u1_angles,
                           void *stream, dirac_ctx **out);
 dirac_status dirac_destroy(dirac_ctx *ctx);
