@@ -130,8 +130,8 @@ DEV void plane_field(const Geom &g, int p, const double2 *__restrict__ U, const 
 // wavefronts on each SIMD; work-groups of six wavefronts, on 2 + 2 + 1 + 1 SIMDs, ran one at a time even where two
 // fitted), the fields meet there afterwards, and wavefront w forms planes 3 w .. 3 w + 2 of block + and of
 // block - of its sites.  Bound by issue and the latency of its chain of products (16 steps of about 190 VALU
-// instructions; loading all links from the own site or leaving the products out saves 10-20 %), against 0.15 ms
-// for the FP64 operations alone.  24^3 x 48, a parity: 515 -> 456 us; 64 x 32^3 1.51 -> 1.35 ms.
+// instructions; with unstaged links, reading all of them at the own site saved 19 %, leaving the products out
+// 2 %), against 0.15 ms for the FP64 operations alone.  24^3 x 48, a parity: 515 -> 456 us; 64 x 32^3 1.51 -> 1.35 ms.
 constexpr int kFReals = 9;
 __global__ __launch_bounds__(768, 3) void k_clover_build(Geom g, int p, const double2 *__restrict__ U,
                                                          const double *__restrict__ th, double csw, double cq,
