@@ -91,7 +91,8 @@ bool graphs_enabled() {
 // act); 2: end of a cycle, after the true residual (the systems in cyc).  A system whose residual
 // norm is not finite, or at most its target, leaves the active set; at the start and the end of a
 // cycle the latter is marked converged, and at the end of a cycle the others restart.  One
-// wavefront; the count of active systems is summed in a fixed order.
+// wavefront; the count of active systems is summed in a fixed order.  A system that took an empty step (GCR met a
+// dependent direction) waits for the end of the cycle.
 __global__ void k_bat_status(int R, int mode, int k, int *act, const int *cyc, int *cnt, const double *scal) {
     __shared__ int part[64];
     int na = 0;
@@ -110,6 +111,8 @@ __global__ void k_bat_status(int R, int mode, int k, int *act, const int *cyc, i
             } else if (sqrt(rn2) <= sq[S_TGT]) {
                 act[q] = 0;
                 if (mode != 0) cnt[3 * R + q] |= 1;
+            } else if (mode == 0) {
+                if (sq[S_RED + 6] != 0.0) act[q] = 0;  // an empty step: the rest of the cycle would repeat it
             } else if (mode == 2) {
                 act[q] = 1;
                 ++cnt[R + q];

@@ -21,8 +21,9 @@ struct BatchSpec {
     int sstride = 0;
 };
 
-// device scalar slots (doubles) of a system: residual norm^2 at S_RED + 4, {1 / gamma, alpha}, free slots, per
-// iteration gamma_k, alpha_k, the solution's coefficients c_k, |Q_k|^2 and the beta_kj
+// device scalar slots (doubles) of a system: residual norm^2 at S_RED + 4, flags of the step (empty, to be
+// corrected) at S_RED + 6, {1 / gamma, estimate of alpha, its correction}, free slots, per iteration gamma_k,
+// alpha_k, the solution's coefficients c_k, |Q_k|^2 and the beta_kj
 constexpr int kGcrMax = 64;  // longest cycle
 constexpr int S_RED = 0, S_SC = 8, S_MISC = 16, S_GAM = 64, S_ALP = 192, S_C = 320, S_N2 = 448, S_BETA = 512;
 constexpr int kSysScal = 8768;  // device scalar doubles per system: GCR(64) coefficients and 64 free slots
@@ -35,9 +36,10 @@ struct Blas {
     // out[j] = scale <Q_j, q>, j < k (complex, 2 doubles each)
     void mdot(dirac_prec pr, int nh, const void *Q, int k, const void *q, double *out_dev, double scale, hipStream_t s,
               const BatchSpec &bs = BatchSpec());
-    // Step k of a GCR cycle (basis vectors Q_0 .. Q_{k-1}, q = A p_k): the scalars beta_k, gamma_k, alpha_k, then
-    // q <- the new basis vector, rnew = r - alpha q (rnew may be r), |rnew|^2 in S_RED + 4; with ctl (one system) the
-    // iteration control of the cycle is advanced against `target`.
+    // Step k of a GCR cycle (basis vectors Q_0 .. Q_{k-1}, q = A p_k): the scalars beta_k and gamma_k and an estimate of
+    // alpha_k, then q <- the new basis vector, rnew = r - alpha q (rnew may be r), |rnew|^2 in S_RED + 4, and
+    // S_RED + 6 = 1 when nothing was left of q (then rnew = r, and the cycle should end), else 0; with ctl (one
+    // system) the iteration control of the cycle is advanced against `target`.
     void gcr_dots(dirac_prec pr, int nh, const void *Q, int k, const void *q, const void *r, double scale, hipStream_t s,
                   const BatchSpec &bs = BatchSpec());
     void gcr_step(dirac_prec pr, int nh, const void *Q, int k, void *q, const void *r, void *rnew, double scale,

@@ -151,22 +151,30 @@ __global__ __launch_bounds__(kRed) void k_reduce(int nblk, int nent, int nc, con
 
 // ------------------------------------------------------------------ one GCR orthogonalisation step
 // Two kernels per iteration, each finished by its last work-group per system, instead of a kernel and a
-// reduction for each of the dots, the subtraction and the update, and one for the scalars:
-//   k_gcr_dots: <Q_j, q> (j < k), |q|^2 and <q, r> in one pass over Q, q and r; then
-//     beta_j = <Q_j, q> / |Q_j|^2,  gamma^2 = |q|^2 - sum_j |<Q_j, q>|^2 / |Q_j|^2,  alpha = <q, r> / gamma
-//     (r is orthogonal to the Q_j, so <q - sum beta_j Q_j, r> = <q, r>);
-//   k_gcr_step: q <- (q - sum_j beta_j Q_j) / gamma, r_new = r - alpha q, |q|^2 (kept as |Q_k|^2) and |r_new|^2.
-// gamma from the difference is as accurate as FP64 sums of the stored vectors make it; what is left of
-// an inexact gamma is in the kept |Q_k|^2, by which the later beta are divided.  A q that lies in the
-// span of the Q_j up to the rounding of the stored vectors (gamma^2 <= eps |q|^2) gives Q_k = 0 and no step.
+// reduction for each of the dots, the subtraction and the update, and one for the scalars; a third one corrects:
+//   k_gcr_dots: <Q_j, q> (j < k), |q|^2 and <q, r> in one pass over Q, q and r; then beta_j = <Q_j, q> / |Q_j|^2,
+//     gamma = |q|, and an estimate a of alpha: |q_perp|^2 = |q|^2 - sum_j |<Q_j, q>|^2 / |Q_j|^2 and <q_perp, r> = <q, r>
+//     hold for orthogonal Q_j and r; a = 0 where less than a hundredth of |q|^2 is left by that;
+//   k_gcr_step: Q_k = (q - sum_j beta_j Q_j) / gamma over q (k = 0: Q_0 = q, gamma = 1), r_new = r - a Q_k, and |Q_k|^2,
+//     <Q_k, r>, |r_new|^2 of the vectors as stored; then alpha = <Q_k, r> / |Q_k|^2 is known;
+//   k_gcr_correct: r_new -= (alpha - a) Q_k and |r_new|^2 anew, where |alpha - a|^2 |Q_k|^2 (what the estimate adds to the
+//     least |r_new|^2) is above `slack` |r_new|^2, 1e-10 or what rounding the stored r adds; else it returns at once
+//     (2 us), and alpha = a counts as taken.
+// So the beta, the step and the solution's coefficients rest on sums over the stored vectors: the estimate
+// cancels where q nearly lies in the span of the Q_j, and with alpha and gamma from it alone directions with
+// |q_perp| / |q| below 1e-7 in FP64 (3e-5 in FP32) had to be left out, and solves that need one did not
+// converge.  Here such a direction is taken with what is left of it, be it rounding (which leads out of a
+// breakdown of GCR, where <r, A r> = 0).  Where nothing is left, Q_k = 0, the step is empty and the cycle ends.
 // r_new goes to the next direction's slot (or over r): r is not stored a second time.  Passes over
-// vectors per iteration: 2 k + 6, against 2 k + 9.
-// Work-groups take chunks of BS sites in turn, one site per thread; BS = 512, or 256 where 512 would leave compute
-// units without a work-group.  On the smallest lattices (kWideSites) a thread would still wait for one basis
-// vector after the other (1.6 us each in FP64), so there (WIDE) a chunk is 64 sites and wavefront w of eight
-// takes the basis vectors w, w + 8, ...: at 8^4 a kernel of an FP64 GCR(32) step falls from 34 to 10 us on
-// average; at 16^3 x 32 one right-hand side is slower that way (92 against 78 us per iteration).  The partial sums and the finishing work-group's reads of
-// them are agent-scope accesses (the XCDs' L2s are not coherent with each other), summed in a fixed order.
+// vectors per iteration: 2 k + 6 (5 for k = 0), against 2 k + 9; 2 k + 9 with a correction.
+// Work-groups of k_gcr_dots and k_gcr_step take chunks of BS sites in turn, one site per thread; BS = 512, or 256
+// where 512 would leave compute units without a work-group.  On the smallest lattices (kWideSites) a thread would
+// still wait for one basis vector after the other (1.6 us each in FP64), so there (WIDE) a chunk is 64 sites and
+// wavefront w of eight takes the basis vectors w, w + 8, ...: at 8^4 a kernel of an FP64 GCR(32) step falls from 34
+// to 10 us on average; at 16^3 x 32 one right-hand side is slower that way (92 against 78 us per iteration).
+// k_gcr_correct, which reads no basis vectors, takes one 16-byte vector per thread.  The partial sums and the
+// finishing work-group's reads of them are agent-scope accesses (the XCDs' L2s are not coherent with each
+// other), summed in a fixed order.
 constexpr int kGcr = 512;
 constexpr int kGcrBlocks = 512;  // work-groups per system at most: two per compute unit
 constexpr int kGcrEnt = 2 * (64 + 2);
@@ -230,6 +238,52 @@ DEV bool gcr_finish(double (*acc)[kGcrEnt], int ne, int nblk, int sys, int blk, 
     return true;
 }
 
+// The same for few sums that every thread holds a part of, v[e]: the totals are in v of thread 0 of the work-group
+// that finishes last (which all of its threads are told).
+template <int BS, int NE>
+DEV bool gcr_finish_few(double (&v)[NE], int nblk, int sys, int blk, double *part, unsigned *ctr) {
+    static_assert(kGcrBlocks <= 2 * BS, "two partial sums per thread at most");
+    __shared__ double red[BS / 64][NE];
+    __shared__ bool last;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    auto group = [&]() {  // v of thread 0 = sum over the work-group
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            v[e] = wave_sum63(v[e]);
+            if (lane == 63) red[w][e] = v[e];
+        }
+        __syncthreads();
+        if (tid == 0) {
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                v[e] = red[0][e];
+#pragma unroll
+                for (int u = 1; u < BS / 64; ++u) v[e] += red[u][e];
+            }
+        }
+    };
+    group();
+    part += (size_t)sys * nblk * NE;
+    if (tid == 0) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            __hip_atomic_store(part + (size_t)blk * NE + e, v[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the partial sums have arrived before the count goes up
+        last = __hip_atomic_fetch_add(ctr + sys, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nblk - 1;
+    }
+    __syncthreads();
+    if (!last) return false;
+    if (tid == 0) __hip_atomic_store(ctr + sys, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        v[e] = 0.0;
+        for (int b = tid; b < nblk; b += BS)
+            v[e] += __hip_atomic_load(part + (size_t)b * NE + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    group();
+    return true;
+}
+
 // Back-substitution at the end of a cycle, one work-group per system: alpha_j = c_j gamma_j + sum_{k > j} c_k beta_kj,
 // solved for c_{n-1} .. c_0 with one wavefront (lane j holds what is left of alpha_j), the beta in LDS.
 // n = counts[sys], or n_all; c_j = 0 for n <= j < kmax.
@@ -267,12 +321,12 @@ __global__ __launch_bounds__(256) void k_gcr_backsub(const int *active, const in
 
 template <typename S, bool WIDE, int BS>
 __global__ __launch_bounds__(BS) void k_gcr_dots(Bat B, int nblk, const typename St<S>::vec *Q, int k,
-                                                   const typename St<S>::vec *q, const typename St<S>::vec *rv,
-                                                   double *part, unsigned *ctr, double scale, double eps, double *scal) {
+                                                 const typename St<S>::vec *q, const typename St<S>::vec *rv, double *part,
+                                                 unsigned *ctr, double scale, double *scal) {
     __shared__ double acc[BS / 64][kGcrEnt];
     const int sys = (int)blockIdx.x / nblk, blk = (int)blockIdx.x - sys * nblk;
     if (B.active && !B.active[sys]) return;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, ne = 2 * (k + 2);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, ne = 2 * k + 3;
     for (int e = lane; e < ne; e += 64) acc[w][e] = 0.0;
     const size_t vs = vstride<S>(B);
     q += sys * vs;
@@ -299,9 +353,8 @@ __global__ __launch_bounds__(BS) void k_gcr_dots(Bat B, int nblk, const typename
 #pragma unroll
             for (int m = 0; m < 3; ++m) v[m] = wave_sum63(v[m]);
             if (lane == 63) {
-                acc[w][2 * k] += v[0];
-                acc[w][2 * k + 2] += v[1];
-                acc[w][2 * k + 3] += v[2];
+#pragma unroll
+                for (int m = 0; m < 3; ++m) acc[w][2 * k + m] += v[m];
             }
         }
         for (int j = WIDE ? w : 0; j < k; j += WIDE ? (BS / 64) : 1) {
@@ -339,16 +392,13 @@ __global__ __launch_bounds__(BS) void k_gcr_dots(Bat B, int nblk, const typename
     }
     sub = wave_sum63(sub);
     if (lane == 63) {
-        const double qq = scale * tot[2 * k], g2 = qq - sub;
-        const bool in_span = g2 <= eps * qq;  // false for NaN, which goes on into the step
-        const double g = in_span ? 1.0 : sqrt(g2), ig = in_span ? 0.0 : 1.0 / g;
-        const double ar = scale * tot[2 * k + 2] * ig, ai = scale * tot[2 * k + 3] * ig;
-        scal[S_SC] = ig;
-        scal[S_SC + 1] = ar;
-        scal[S_SC + 2] = ai;
+        const double qq = scale * tot[2 * k], perp = qq - sub;
+        const double g = k == 0 || qq == 0.0 ? 1.0 : sqrt(qq);  // NaN goes on into the step
+        const double f = perp <= 0.01 * qq ? 0.0 : scale * g / perp;
+        scal[S_SC] = 1.0 / g;
+        scal[S_SC + 1] = f * tot[2 * k + 1];
+        scal[S_SC + 2] = f * tot[2 * k + 2];
         scal[S_GAM + k] = g;
-        scal[S_ALP + 2 * k] = ar;
-        scal[S_ALP + 2 * k + 1] = ai;
     }
 }
 
@@ -371,15 +421,25 @@ DEV void st_rounded(typename St<S>::vec *p, int t, int vh, double *o) {
     }
 }
 
-// ctl (one system): after the sums, ++ctl[1]; ctl[0] = 0 when the new residual norm is at most target or not
-// finite (then ctl[2] = 1).  WIDE: the wavefronts' parts of sum_j beta_j Q_j meet in LDS, and wavefront w then
-// takes the storage planes w, w + 8 of the chunk's sites.
+// Iteration control of a cycle (one system) after a step to the residual norm^2 rn2: ++ctl[1]; ctl[0] = 0 when the norm
+// is at most target or not finite (then ctl[2] = 1), or when the step was empty.
+DEV void gcr_control(int *ctl, double rn2, double target, bool empty) {
+    ++ctl[1];
+    if (!isfinite(rn2)) {
+        ctl[2] = 1;
+        ctl[0] = 0;
+    } else if (sqrt(rn2) <= target || empty) {
+        ctl[0] = 0;
+    }
+}
+
+// WIDE: the wavefronts' parts of sum_j beta_j Q_j meet in LDS, and wavefront w then takes the storage planes
+// w, w + 8 of the chunk's sites.
 template <typename S, bool WIDE, int BS>
 __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename St<S>::vec *Q, int k,
-                                                   typename St<S>::vec *q, const typename St<S>::vec *rv,
-                                                   typename St<S>::vec *rnew, double *part, unsigned *ctr, double scale,
-                                                   double *scal, int *ctl, double target) {
-    __shared__ double acc[BS / 64][kGcrEnt];
+                                                 typename St<S>::vec *q, const typename St<S>::vec *rv,
+                                                 typename St<S>::vec *rnew, double *part, unsigned *ctr, double scale,
+                                                 double slack, double *scal, int *ctl, double target) {
     __shared__ double sub[WIDE ? (BS / 64) : 1][WIDE ? 24 : 1][64];
     const int sys = (int)blockIdx.x / nblk, blk = (int)blockIdx.x - sys * nblk;
     if (B.active && !B.active[sys]) return;
@@ -391,7 +451,12 @@ __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename
     scal += (size_t)sys * B.sstride;
     const double2 *cf = reinterpret_cast<const double2 *>(scal + S_BETA + 2 * kGcrMax * k);
     const double ig = scal[S_SC], ar = scal[S_SC + 1], ai = scal[S_SC + 2];
-    double v[2] = {0.0, 0.0};
+    double v[4] = {0.0, 0.0, 0.0, 0.0};  // |Q_k|^2, <Q_k, r>, |r_new|^2
+    auto dots = [&](double yr, double yi, double rr, double ri) {  // one complex component of Q_k and r
+        v[0] = fma(yr, yr, fma(yi, yi, v[0]));
+        v[1] = fma(yr, rr, fma(yi, ri, v[1]));
+        v[2] = fma(yr, ri, fma(-yi, rr, v[2]));
+    };
     constexpr int CH = WIDE ? 64 : BS;
     const int nch = (B.n + CH - 1) / CH;
     for (int c = blk; c < nch; c += nblk) {
@@ -409,22 +474,22 @@ __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename
         if constexpr (!WIDE) {
             if (t >= B.n) continue;
             ld<S>(q, t, B.vh, a);
-            for (int j = 0; j < k; ++j) take(j);
+            if (k) {
+                for (int j = 0; j < k; ++j) take(j);
 #pragma unroll
-            for (int m = 0; m < 24; ++m) a[m] *= ig;
-            st_rounded<S>(q, t, B.vh, a);  // the stored (rounded) q is what the recurrence uses
+                for (int m = 0; m < 24; ++m) a[m] *= ig;
+                st_rounded<S>(q, t, B.vh, a);  // the stored (rounded) vector is what the recurrence uses
+            }
             ld<S>(rv, t, B.vh, b);
 #pragma unroll
             for (int m = 0; m < 12; ++m) {
+                dots(a[2 * m], a[2 * m + 1], b[2 * m], b[2 * m + 1]);
                 b[2 * m] -= ar * a[2 * m] - ai * a[2 * m + 1];
                 b[2 * m + 1] -= ar * a[2 * m + 1] + ai * a[2 * m];
             }
             st_rounded<S>(rnew, t, B.vh, b);
 #pragma unroll
-            for (int m = 0; m < 24; ++m) {
-                v[0] = fma(a[m], a[m], v[0]);
-                v[1] = fma(b[m], b[m], v[1]);
-            }
+            for (int m = 0; m < 24; ++m) v[3] = fma(b[m], b[m], v[3]);
         } else {
             constexpr int W = St<S>::W, NP = 24 / W;
             const int nw = min(k, (BS / 64));  // wavefronts with a basis vector
@@ -446,21 +511,24 @@ __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename
                     typename St<S>::acc f[W];
                     double y[W];
                     St<S>::unpack(vq, f);
+                    if (k) {
 #pragma unroll
-                    for (int e = 0; e < W; ++e) {
-                        double z = (double)f[e];
-                        for (int u = 0; u < nw; ++u) z += sub[u][pl * W + e][lane];
-                        f[e] = (typename St<S>::acc)(z * ig);
+                        for (int e = 0; e < W; ++e) {
+                            double z = (double)f[e];
+                            for (int u = 0; u < nw; ++u) z += sub[u][pl * W + e][lane];
+                            f[e] = (typename St<S>::acc)(z * ig);
+                        }
+                        vq = St<S>::pack(f);
+                        site(q)[pl * kSB] = vq;
+                        St<S>::unpack(vq, f);  // the stored (rounded) vector is what the recurrence uses
                     }
-                    vq = St<S>::pack(f);
-                    site(q)[pl * kSB] = vq;
-                    St<S>::unpack(vq, f);  // the stored (rounded) q is what the recurrence uses
 #pragma unroll
                     for (int e = 0; e < W; ++e) y[e] = (double)f[e];
                     typename St<S>::vec vr = site(rv)[pl * kSB];
                     St<S>::unpack(vr, f);
 #pragma unroll
                     for (int e = 0; e < W; e += 2) {
+                        dots(y[e], y[e + 1], (double)f[e], (double)f[e + 1]);
                         const double re = (double)f[e] - (ar * y[e] - ai * y[e + 1]);
                         const double im = (double)f[e + 1] - (ar * y[e + 1] + ai * y[e]);
                         f[e] = (typename St<S>::acc)re;
@@ -470,35 +538,85 @@ __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename
                     site(rnew)[pl * kSB] = vr;
                     St<S>::unpack(vr, f);
 #pragma unroll
-                    for (int e = 0; e < W; ++e) {
-                        v[0] = fma(y[e], y[e], v[0]);
-                        v[1] = fma((double)f[e], (double)f[e], v[1]);
-                    }
+                    for (int e = 0; e < W; ++e) v[3] = fma((double)f[e], (double)f[e], v[3]);
                 }
             }
             __syncthreads();  // sub is read before the next chunk overwrites it
         }
     }
-    v[0] = wave_sum63(v[0]);
-    v[1] = wave_sum63(v[1]);
-    if (lane == 63) {
-        acc[w][0] = v[0];
-        acc[w][1] = v[1];
-    }
-    if (!gcr_finish<BS>(acc, 2, nblk, sys, blk, part, ctr)) return;
+    if (!gcr_finish_few<BS>(v, nblk, sys, blk, part, ctr)) return;
     if (threadIdx.x) return;
-    const double rn2 = scale * acc[0][1];
-    scal[S_N2 + k] = scale * acc[0][0];
+    const double n2 = scale * v[0], rn2 = scale * v[3];
+    const bool empty = n2 == 0.0;
+    const double f = empty ? 0.0 : scale / n2, er = empty ? 0.0 : ar, ei = empty ? 0.0 : ai;  // step taken, if not corrected
+    const double dr = f * v[1] - er, di = f * v[2] - ei;
+    const bool correct = (dr * dr + di * di) * n2 > slack * rn2;  // false for NaN
+    scal[S_N2 + k] = n2;
+    scal[S_ALP + 2 * k] = correct ? er + dr : er;
+    scal[S_ALP + 2 * k + 1] = correct ? ei + di : ei;
+    scal[S_SC + 3] = dr;
+    scal[S_SC + 4] = di;
     scal[S_RED + 4] = rn2;
-    if (ctl) {
-        ++ctl[1];
-        if (!isfinite(rn2)) {
-            ctl[2] = 1;
-            ctl[0] = 0;
-        } else if (sqrt(rn2) <= target) {
-            ctl[0] = 0;
+    scal[S_RED + 6] = empty ? 1.0 : 0.0;
+    scal[S_RED + 7] = correct ? 1.0 : 0.0;
+    if (ctl && !correct) gcr_control(ctl, rn2, target, empty);
+}
+
+// The vectors of a system are taken as they lie, 16 bytes a thread, kU loads of each in flight.
+template <typename S>
+__global__ __launch_bounds__(kGcr) void k_gcr_correct(Bat B, int nblk, const typename St<S>::vec *q,
+                                                      typename St<S>::vec *rnew, double *part, unsigned *ctr,
+                                                      double scale, double *scal, int *ctl, double target) {
+    using V = typename St<S>::vec;
+    constexpr int W = St<S>::W, NP = 24 / W, kU = 4;
+    const int sys = (int)blockIdx.x / nblk, blk = (int)blockIdx.x - sys * nblk;
+    if (B.active && !B.active[sys]) return;
+    scal += (size_t)sys * B.sstride;
+    if (scal[S_RED + 7] == 0.0) return;
+    const size_t vs = vstride<S>(B);
+    q += sys * vs;
+    rnew += sys * vs;
+    const double dr = scal[S_SC + 3], di = scal[S_SC + 4];
+    // (32 bits: a solve keeps more than nine vectors, so one has less than 2^31 of its 16-byte pieces)
+    const uint32_t half = (uint32_t)NP * (uint32_t)padded_sites(B.vh), nv = (uint32_t)vs, step = (uint32_t)nblk * kGcr;
+    double v[1] = {0.0};
+    for (uint32_t e0 = (uint32_t)blk * kGcr + threadIdx.x; e0 < nv; e0 += kU * step) {
+        V vq[kU], vr[kU];
+        bool on[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint32_t e = e0 + u * step, h = e >= half ? e - half : e;  // padding sites are left alone
+            on[u] = e < nv && (h / (NP * kSB)) * kSB + (h & (kSB - 1)) < (uint32_t)B.vh;
+            if (on[u]) {
+                vq[u] = q[e];
+                vr[u] = rnew[e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (!on[u]) continue;
+            typename St<S>::acc y[W], f[W];
+            St<S>::unpack(vq[u], y);
+            St<S>::unpack(vr[u], f);
+#pragma unroll
+            for (int c = 0; c < W; c += 2) {
+                const double yr = (double)y[c], yi = (double)y[c + 1];
+                const double re = (double)f[c] - (dr * yr - di * yi), im = (double)f[c + 1] - (dr * yi + di * yr);
+                f[c] = (typename St<S>::acc)re;
+                f[c + 1] = (typename St<S>::acc)im;
+            }
+            const V o = St<S>::pack(f);
+            rnew[e0 + u * step] = o;
+            St<S>::unpack(o, f);
+#pragma unroll
+            for (int c = 0; c < W; ++c) v[0] = fma((double)f[c], (double)f[c], v[0]);
         }
     }
+    if (!gcr_finish_few<kGcr>(v, nblk, sys, blk, part, ctr)) return;
+    if (threadIdx.x) return;
+    const double rn2 = scale * v[0];
+    scal[S_RED + 4] = rn2;
+    if (ctl) gcr_control(ctl, rn2, target, false);
 }
 
 // x += xscale_r sum_j coef_j P_j (x and P may have different precisions)
@@ -678,8 +796,11 @@ void Blas::mdot(dirac_prec pr, int nh, const void *Q, int k, const void *q, doub
 }
 
 namespace {
-// rounding of the stored vectors, squared and summed incoherently, leaves gamma^2 / |q|^2 uncertain by about this
-double span_eps(dirac_prec pr) { return pr == DIRAC_F64 ? 1e-14 : pr == DIRAC_F32 ? 1e-9 : 1e-6; }
+// |r|^2 gains about u^2 / 4 |r|^2 when r is rounded to the storage (relative steps of at most u, uniform): 4e-6 in BF16
+double gcr_slack(dirac_prec pr) {
+    const double u = pr == DIRAC_F16 ? 0x1p-11 : pr == DIRAC_BF16 ? 0x1p-8 : 0.0;
+    return std::max(1e-10, 0.25 * u * u);
+}
 bool gcr_wide(const Bat &b) { return (int64_t)b.n * b.nrhs <= kWideSites; }
 int gcr_block_size(const Bat &b) { return gcr_wide(b) || (int64_t)b.n * b.nrhs >= 256 * kGcr ? kGcr : kGcr / 2; }
 int gcr_blocks(const Bat &b) {
@@ -692,11 +813,11 @@ void Blas::gcr_dots(dirac_prec pr, int nh, const void *Q, int k, const void *q, 
                     hipStream_t s, const BatchSpec &bs) {
     const Bat b = make_bat(c, nh, bs);
     const int nblk = gcr_blocks(b);
-#define FNW(S, WIDE, BS)                                                                                                  \
-    k_gcr_dots<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,                     \
-                                                       (const typename St<S>::vec *)q, (const typename St<S>::vec *)r, \
-                                                       (double *)part.p, (unsigned *)count.p, scale, span_eps(pr),     \
-                                                       (double *)scal.p);
+#define FNW(S, WIDE, BS)                                                                                                \
+    k_gcr_dots<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,                   \
+                                                         (const typename St<S>::vec *)q,                               \
+                                                         (const typename St<S>::vec *)r, (double *)part.p,             \
+                                                         (unsigned *)count.p, scale, (double *)scal.p);
 #define FN(S) if (gcr_wide(b)) { FNW(S, true, kGcr) } else if (gcr_block_size(b) == kGcr) { FNW(S, false, kGcr) } else { FNW(S, false, kGcr / 2) }
     DISPATCH_PREC(pr, FN)
 #undef FN
@@ -713,12 +834,19 @@ void Blas::gcr_step(dirac_prec pr, int nh, const void *Q, int k, void *q, const 
                     hipStream_t s, const BatchSpec &bs, int *ctl, double target) {
     const Bat b = make_bat(c, nh, bs);
     const int nblk = gcr_blocks(b);
-#define FNW(S, WIDE, BS)                                                                                            \
-    k_gcr_step<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,               \
-                                                       (typename St<S>::vec *)q, (const typename St<S>::vec *)r, \
-                                                       (typename St<S>::vec *)rnew, (double *)part.p,            \
-                                                       (unsigned *)count.p, scale, (double *)scal.p, ctl, target);
-#define FN(S) if (gcr_wide(b)) { FNW(S, true, kGcr) } else if (gcr_block_size(b) == kGcr) { FNW(S, false, kGcr) } else { FNW(S, false, kGcr / 2) }
+    const int64_t nv = (int64_t)(b.n / b.vh) * (24 * real_size(pr) / 16) * padded_sites(b.vh);  // 16-byte vectors
+    const int nr = (int)std::min<int64_t>((nv + kGcr - 1) / kGcr, kGcrBlocks / 2);  // rarely with work: one per compute unit
+#define FNW(S, WIDE, BS)                                                                                              \
+    k_gcr_step<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,                 \
+                                                         (typename St<S>::vec *)q, (const typename St<S>::vec *)r,   \
+                                                         (typename St<S>::vec *)rnew, (double *)part.p,              \
+                                                         (unsigned *)count.p, scale, gcr_slack(pr), (double *)scal.p, \
+                                                         ctl, target);
+#define FN(S)                                                                                                         \
+    if (gcr_wide(b)) { FNW(S, true, kGcr) } else if (gcr_block_size(b) == kGcr) { FNW(S, false, kGcr) } else { FNW(S, false, kGcr / 2) } \
+    k_gcr_correct<S><<<nr * b.nrhs, kGcr, 0, s>>>(b, nr, (const typename St<S>::vec *)q, (typename St<S>::vec *)rnew, \
+                                                  (double *)part.p, (unsigned *)count.p, scale, (double *)scal.p,     \
+                                                  ctl, target);
     DISPATCH_PREC(pr, FN)
 #undef FN
 #undef FNW

@@ -41,7 +41,7 @@ double *sc_ptr(SolverWork &w, int slot) { return (double *)w.blas.scal.p + slot;
 // Device-side iteration control of one GCR cycle without a preconditioner: ctl[0] = 1 while the
 // system is active, ctl[1] = iterations done in the cycle, ctl[2] = 1 after a non-finite residual.
 // The last work-group of each iteration compares the updated residual norm with the target and clears
-// ctl[0]; every kernel of a later iteration of the cycle takes ctl as its active mask and does
+// ctl[0] (also after an empty step); every kernel of a later iteration of the cycle takes ctl as its active mask and does
 // nothing, so the host only reads ctl every kPoll iterations and at the end of the cycle.
 constexpr int kPoll = 4;
 
@@ -172,14 +172,16 @@ GcrOut gcr(dirac_ctx *c, SolverWork &w, dirac_prec pr, void *x, const void *b, b
                 void *rk = M ? r : P + k * hb, *rn = M ? r : P + (k + 1) * hb;
                 B.gcr_dots(pr, nh, Q, k, qk, rk, scale, s);
                 B.gcr_step(pr, nh, Q, k, qk, rk, rn, scale, s);
-                rn2 = read_scalar(w, S_RED + 4, s);
+                read_pinned(w, sc_ptr(w, S_RED + 4), 3 * sizeof(double), s);
+                rn2 = w.pin[0];
+                const bool empty = w.pin[2] != 0.0;
                 ++out.iters;
                 n = k + 1;
                 if (!std::isfinite(rn2)) {
                     out.nonfinite = true;
                     return out;
                 }
-                if (std::sqrt(rn2) <= target || out.iters >= max_iter || k + 1 == m) break;
+                if (std::sqrt(rn2) <= target || empty || out.iters >= max_iter || k + 1 == m) break;
                 if (M) (*M)(P + (k + 1) * hb, r);
             }
         }
