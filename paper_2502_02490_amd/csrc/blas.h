@@ -21,16 +21,16 @@ struct BatchSpec {
     int sstride = 0;
 };
 
-// device scalar slots (doubles) of a system: residual norm^2 at S_RED + 4, flags of the step (empty, to be
-// corrected) at S_RED + 6, {1 / gamma, estimate of alpha, its correction}, free slots, per iteration gamma_k,
-// alpha_k, the solution's coefficients c_k, |Q_k|^2 and the beta_kj
+// device scalar slots (doubles) of a system: work-groups finished (an integer, zero between launches), residual
+// norm^2 at S_RED + 4, flags of the step (empty, to be corrected) at S_RED + 6, {1 / gamma, estimate of alpha, its
+// correction}, free slots, per iteration gamma_k, alpha_k, the solution's coefficients c_k, |Q_k|^2 and the beta_kj
 constexpr int kGcrMax = 64;  // longest cycle
-constexpr int S_RED = 0, S_SC = 8, S_MISC = 16, S_GAM = 64, S_ALP = 192, S_C = 320, S_N2 = 448, S_BETA = 512;
+constexpr int S_COUNT = 0, S_RED = 0, S_SC = 8, S_MISC = 16, S_GAM = 64, S_ALP = 192, S_C = 320, S_N2 = 448, S_BETA = 512;
 constexpr int kSysScal = 8768;  // device scalar doubles per system: GCR(64) coefficients and 64 free slots
 
 struct Blas {
     dirac_ctx *c = nullptr;
-    DevBuf part, scal, count;  // partial sums, scalars, work-groups finished per system (zero between launches)
+    DevBuf part, scal;  // partial sums, scalars
 
     void reserve(int64_t nsites_max, int kmax, int nrhs = 1);
     // out[j] = scale <Q_j, q>, j < k (complex, 2 doubles each)

@@ -197,6 +197,9 @@ DEV double wave_sum63(double v) {
     return v;
 }
 
+// A system's count of finished work-groups, zero between launches: a slot of its scalars.
+DEV unsigned *gcr_count(double *scal) { return reinterpret_cast<unsigned *>(scal + S_COUNT); }
+
 // Partial sums of a work-group, acc[wave][e] for e < ne, to part; true in every thread of the work-group that
 // finishes last of the system's nblk, with tot[e] (in acc[0]) the sums over all of them.
 template <int BS>
@@ -215,10 +218,10 @@ DEV bool gcr_finish(double (*acc)[kGcrEnt], int ne, int nblk, int sys, int blk, 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the partial sums have arrived before the count goes up
     __syncthreads();
     if (tid == 0)
-        last = __hip_atomic_fetch_add(ctr + sys, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nblk - 1;
+        last = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nblk - 1;
     __syncthreads();
     if (!last) return false;
-    if (tid == 0) __hip_atomic_store(ctr + sys, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
     double *flat = &acc[0][0];
     const int groups = BS / ne, g = tid / ne, e = tid - g * ne;
     double s = 0.0;
@@ -269,11 +272,11 @@ DEV bool gcr_finish_few(double (&v)[NE], int nblk, int sys, int blk, double *par
         for (int e = 0; e < NE; ++e)
             __hip_atomic_store(part + (size_t)blk * NE + e, v[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the partial sums have arrived before the count goes up
-        last = __hip_atomic_fetch_add(ctr + sys, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nblk - 1;
+        last = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nblk - 1;
     }
     __syncthreads();
     if (!last) return false;
-    if (tid == 0) __hip_atomic_store(ctr + sys, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
         v[e] = 0.0;
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(256) void k_gcr_backsub(const int *active, const in
 template <typename S, bool WIDE, int BS>
 __global__ __launch_bounds__(BS) void k_gcr_dots(Bat B, int nblk, const typename St<S>::vec *Q, int k,
                                                  const typename St<S>::vec *q, const typename St<S>::vec *rv, double *part,
-                                                 unsigned *ctr, double scale, double *scal) {
+                                                 double scale, double *scal) {
     __shared__ double acc[BS / 64][kGcrEnt];
     const int sys = (int)blockIdx.x / nblk, blk = (int)blockIdx.x - sys * nblk;
     if (B.active && !B.active[sys]) return;
@@ -376,11 +379,11 @@ __global__ __launch_bounds__(BS) void k_gcr_dots(Bat B, int nblk, const typename
             }
         }
     }
-    if (!gcr_finish<BS>(acc, ne, nblk, sys, blk, part, ctr)) return;
+    scal += (size_t)sys * B.sstride;
+    if (!gcr_finish<BS>(acc, ne, nblk, sys, blk, part, gcr_count(scal))) return;
     if (w) return;
     // one wavefront: lane j forms beta_j
     const double *tot = acc[0];
-    scal += (size_t)sys * B.sstride;
     double sub = 0.0;
     if (lane < k) {
         const double n2 = scal[S_N2 + lane], inv = n2 > 0.0 ? 1.0 / n2 : 0.0;
@@ -438,8 +441,8 @@ DEV void gcr_control(int *ctl, double rn2, double target, bool empty) {
 template <typename S, bool WIDE, int BS>
 __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename St<S>::vec *Q, int k,
                                                  typename St<S>::vec *q, const typename St<S>::vec *rv,
-                                                 typename St<S>::vec *rnew, double *part, unsigned *ctr, double scale,
-                                                 double slack, double *scal, int *ctl, double target) {
+                                                 typename St<S>::vec *rnew, double *part, double scale, double slack,
+                                                 double *scal, int *ctl, double target) {
     __shared__ double sub[WIDE ? (BS / 64) : 1][WIDE ? 24 : 1][64];
     const int sys = (int)blockIdx.x / nblk, blk = (int)blockIdx.x - sys * nblk;
     if (B.active && !B.active[sys]) return;
@@ -544,7 +547,7 @@ __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename
             __syncthreads();  // sub is read before the next chunk overwrites it
         }
     }
-    if (!gcr_finish_few<BS>(v, nblk, sys, blk, part, ctr)) return;
+    if (!gcr_finish_few<BS>(v, nblk, sys, blk, part, gcr_count(scal))) return;
     if (threadIdx.x) return;
     const double n2 = scale * v[0], rn2 = scale * v[3];
     const bool empty = n2 == 0.0;
@@ -565,8 +568,8 @@ __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename
 // The vectors of a system are taken as they lie, 16 bytes a thread, kU loads of each in flight.
 template <typename S>
 __global__ __launch_bounds__(kGcr) void k_gcr_correct(Bat B, int nblk, const typename St<S>::vec *q,
-                                                      typename St<S>::vec *rnew, double *part, unsigned *ctr,
-                                                      double scale, double *scal, int *ctl, double target) {
+                                                      typename St<S>::vec *rnew, double *part, double scale,
+                                                      double *scal, int *ctl, double target) {
     using V = typename St<S>::vec;
     constexpr int W = St<S>::W, NP = 24 / W, kU = 4;
     const int sys = (int)blockIdx.x / nblk, blk = (int)blockIdx.x - sys * nblk;
@@ -612,7 +615,7 @@ __global__ __launch_bounds__(kGcr) void k_gcr_correct(Bat B, int nblk, const typ
             for (int c = 0; c < W; ++c) v[0] = fma((double)f[c], (double)f[c], v[0]);
         }
     }
-    if (!gcr_finish_few<kGcr>(v, nblk, sys, blk, part, ctr)) return;
+    if (!gcr_finish_few<kGcr>(v, nblk, sys, blk, part, gcr_count(scal))) return;
     if (threadIdx.x) return;
     const double rn2 = scale * v[0];
     scal[S_RED + 4] = rn2;
@@ -762,10 +765,13 @@ void Blas::reserve(int64_t nsites_max, int kmax, int nrhs) {
     nrhs = std::max(nrhs, 1);
     part.alloc(std::max(nb * (size_t)nrhs * (size_t)std::max(kmax, 4) * 2 * sizeof(double) + 64,
                         (size_t)nrhs * kGcrBlocks * kGcrEnt * sizeof(double)));
-    scal.alloc((size_t)nrhs * kSysScal * sizeof(double));
-    if (count.bytes < (size_t)nrhs * sizeof(unsigned)) {  // zero between launches
-        count.alloc((size_t)nrhs * sizeof(unsigned));
-        HIP_CHECK(hipMemset(count.p, 0, count.bytes));
+    const size_t n = (size_t)nrhs * kSysScal;
+    if (scal.bytes < n * sizeof(double)) {
+        scal.alloc(n * sizeof(double));
+        // zeros (S_COUNT) that have arrived when this returns: solves run on streams that do not wait for the null
+        // stream, as a hipMemset would need
+        const std::vector<double> zero(n, 0.0);
+        HIP_CHECK(hipMemcpy(scal.p, zero.data(), n * sizeof(double), hipMemcpyHostToDevice));
     }
 }
 
@@ -816,8 +822,7 @@ void Blas::gcr_dots(dirac_prec pr, int nh, const void *Q, int k, const void *q, 
 #define FNW(S, WIDE, BS)                                                                                                \
     k_gcr_dots<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,                   \
                                                          (const typename St<S>::vec *)q,                               \
-                                                         (const typename St<S>::vec *)r, (double *)part.p,             \
-                                                         (unsigned *)count.p, scale, (double *)scal.p);
+                                                         (const typename St<S>::vec *)r, (double *)part.p, scale, (double *)scal.p);
 #define FN(S) if (gcr_wide(b)) { FNW(S, true, kGcr) } else if (gcr_block_size(b) == kGcr) { FNW(S, false, kGcr) } else { FNW(S, false, kGcr / 2) }
     DISPATCH_PREC(pr, FN)
 #undef FN
@@ -839,13 +844,12 @@ void Blas::gcr_step(dirac_prec pr, int nh, const void *Q, int k, void *q, const 
 #define FNW(S, WIDE, BS)                                                                                              \
     k_gcr_step<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,                 \
                                                          (typename St<S>::vec *)q, (const typename St<S>::vec *)r,   \
-                                                         (typename St<S>::vec *)rnew, (double *)part.p,              \
-                                                         (unsigned *)count.p, scale, gcr_slack(pr), (double *)scal.p, \
+                                                         (typename St<S>::vec *)rnew, (double *)part.p, scale, gcr_slack(pr), (double *)scal.p, \
                                                          ctl, target);
 #define FN(S)                                                                                                         \
     if (gcr_wide(b)) { FNW(S, true, kGcr) } else if (gcr_block_size(b) == kGcr) { FNW(S, false, kGcr) } else { FNW(S, false, kGcr / 2) } \
     k_gcr_correct<S><<<nr * b.nrhs, kGcr, 0, s>>>(b, nr, (const typename St<S>::vec *)q, (typename St<S>::vec *)rnew, \
-                                                  (double *)part.p, (unsigned *)count.p, scale, (double *)scal.p,     \
+                                                  (double *)part.p, scale, (double *)scal.p,     \
                                                   ctl, target);
     DISPATCH_PREC(pr, FN)
 #undef FN

@@ -242,7 +242,6 @@ void free_solver_work(dirac_ctx *c) {
     SolverWork &w = *c->work;
     w.blas.part.release();
     w.blas.scal.release();
-    w.blas.count.release();
     if (w.pin) (void)hipHostFree(w.pin);
     w.ctl.release();
     w.P.release(); w.Q.release(); w.r.release(); w.e.release(); w.b.release();
