@@ -74,6 +74,14 @@ struct Scratch : dl::DevBuf {
     ~Scratch() { release(); }
 };
 
+// p itself, or a copy of it (in tmp) where it is not aligned to `align` bytes as the kernels read it
+const void *aligned_input(const void *p, size_t bytes, size_t align, Scratch &tmp, hipStream_t s) {
+    if (!p || ((uintptr_t)p & (align - 1)) == 0) return p;
+    tmp.alloc(bytes);
+    HIP_CHECK(hipMemcpyAsync(tmp.p, p, bytes, hipMemcpyDeviceToDevice, s));
+    return tmp.p;
+}
+
 void check_ctx(const dirac_ctx *c) { require(c != nullptr, "context is NULL"); }
 
 void check_prec(int pr) { require(pr >= DIRAC_F64 && pr <= DIRAC_BF16, "unknown precision"); }
@@ -129,7 +137,7 @@ const char *dirac_last_error(void) { return g_err.c_str(); }
 dirac_status dirac_create(const dirac_params *prm, const void *su3_links, const double *u1_angles, void *stream,
                           dirac_ctx **out) {
     dirac_ctx *c = nullptr;
-    Scratch planes;
+    Scratch planes, links, angles;
     g_err.clear();
     try {
         require(prm != nullptr && out != nullptr, "params and out must not be NULL");
@@ -162,7 +170,9 @@ dirac_status dirac_create(const dirac_params *prm, const void *su3_links, const 
         c->g.h1 = prm->dims[1] / 2;
         // scratch, released on return: the compressed links and the clover field are built from it
         planes.alloc_field(dl::link_planes_bytes(c->g));
-        dl::links_to_planes(c, su3_links, u1_angles, planes.p, s);
+        const void *U = aligned_input(su3_links, (size_t)V * 4 * 9 * 16, 16, links, s);
+        const void *th = aligned_input(u1_angles, (size_t)V * 4 * 8, 8, angles, s);
+        dl::links_to_planes(c, U, (const double *)th, planes.p, s);
         const double *theta = u1_angles ? dl::theta_planes(planes.p, c->g) : nullptr;
         dl::import_links(c, planes.p, theta, s);
         dl::clover_build(c, planes.p, theta, s);
