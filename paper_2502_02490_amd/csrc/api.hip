@@ -74,9 +74,9 @@ struct Scratch : dl::DevBuf {
     ~Scratch() { release(); }
 };
 
-// p itself, or a copy of it (in tmp) where it is not aligned to `align` bytes as the kernels read it
-const void *aligned_input(const void *p, size_t bytes, size_t align, Scratch &tmp, hipStream_t s) {
-    if (!p || ((uintptr_t)p & (align - 1)) == 0) return p;
+// p itself where the kernels can read it, aligned to `align` bytes, or a copy of it (in tmp)
+const void *readable_input(const void *p, size_t bytes, size_t align, Scratch &tmp, hipStream_t s) {
+    if (!p || dl::in_place(p, align)) return p;
     tmp.alloc(bytes);
     HIP_CHECK(hipMemcpyAsync(tmp.p, p, bytes, hipMemcpyDeviceToDevice, s));
     return tmp.p;
@@ -128,6 +128,17 @@ namespace dl {
 dirac_status api_fail(dirac_status s, const std::string &m) { return fail(s, m); }
 void api_clear_error() { g_err.clear(); }
 void api_check_dev(const void *ptr, size_t bytes, const char *name) { check_dev(ptr, bytes, name); }
+
+bool in_place(const void *p, size_t align) {
+    if ((uintptr_t)p & (align - 1)) return false;
+    hipPointerAttribute_t at;
+    int dev = -1;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeManaged || at.device == dev;
+}
 }  // namespace dl
 
 extern "C" {
@@ -170,8 +181,8 @@ dirac_status dirac_create(const dirac_params *prm, const void *su3_links, const 
         c->g.h1 = prm->dims[1] / 2;
         // scratch, released on return: the compressed links and the clover field are built from it
         planes.alloc_field(dl::link_planes_bytes(c->g));
-        const void *U = aligned_input(su3_links, (size_t)V * 4 * 9 * 16, 16, links, s);
-        const void *th = aligned_input(u1_angles, (size_t)V * 4 * 8, 8, angles, s);
+        const void *U = readable_input(su3_links, (size_t)V * 4 * 9 * 16, 16, links, s);
+        const void *th = readable_input(u1_angles, (size_t)V * 4 * 8, 8, angles, s);
         dl::links_to_planes(c, U, (const double *)th, planes.p, s);
         const double *theta = u1_angles ? dl::theta_planes(planes.p, c->g) : nullptr;
         dl::import_links(c, planes.p, theta, s);
@@ -620,9 +631,9 @@ dirac_status dirac_dot(dirac_ctx *c, const void *a, const void *b, dirac_prec pr
 }
 
 // ---------------------------------------------------------------- learned preconditioner
-// The network's input: the caller's vector itself, or a copy in acts[0] (NULL) when it is not 16-byte aligned.
+// The network's input: the caller's vector itself, or a copy in acts[0] (NULL) when the kernels cannot read it in place.
 static const void *ptc_input(dirac_ctx *c, dirac_ptc *n, const void *in, hipStream_t s) {
-    if (dl::ptc_in_place(in)) return in;
+    if (dl::in_place(in)) return in;
     HIP_CHECK(hipMemcpyAsync(dl::ptc_act(c, n, 0), in, native_bytes(c, DIRAC_F32, 0), hipMemcpyDeviceToDevice, s));
     return nullptr;
 }
@@ -735,7 +746,7 @@ dirac_status ptc_forward(dirac_ctx *c, dirac_ptc *n, void *out, const void *in, 
     check_no_alias(out, nb, in, nb);
     dl::ptc_ensure_acts(c, n);
     const void *x = ptc_input(c, n, in, s);
-    void *y = dl::ptc_in_place(out) ? out : nullptr;
+    void *y = dl::in_place(out) ? out : nullptr;
     dl::ptc_forward_acts(c, n, s, false, false, x, y);
     if (!y) HIP_CHECK(hipMemcpyAsync(out, dl::ptc_act(c, n, n->nlayers), nb, hipMemcpyDeviceToDevice, s));
     API_END
@@ -776,8 +787,8 @@ dirac_status ptc_backward(dirac_ctx *c, dirac_ptc *n, void *grad_in, const void 
     dl::ptc_ensure_acts(c, n);
     const void *x = ptc_input(c, n, in, s);
     dl::ptc_forward_acts(c, n, s, true, false, x);
-    if (grad_in && !dl::ptc_in_place(grad_in)) {
-        // the kernels' stores need 16-byte alignment: through acts[nlayers], which the gradients do not read
+    if (grad_in && !dl::in_place(grad_in)) {
+        // not where the kernels store: through acts[nlayers], which the gradients do not read
         dl::ptc_backward_acts(c, n, grad_out, dl::ptc_act(c, n, n->nlayers), s, x);
         HIP_CHECK(hipMemcpyAsync(grad_in, dl::ptc_act(c, n, n->nlayers), nb, hipMemcpyDeviceToDevice, s));
     } else {

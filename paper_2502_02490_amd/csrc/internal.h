@@ -40,6 +40,10 @@ void *pool_take(size_t n, size_t *got, int *dev);
 void pool_give(void *p, size_t bytes, int dev);
 void pool_trim(int dev);
 
+// api.hip: whether kernels of the current device can access a caller's memory where it lies: aligned, and not memory
+// of another device, which a copy reaches but which need not be mapped for this one.
+bool in_place(const void *p, size_t align = 16);
+
 // Device allocation owned by the context (freed in dirac_destroy).
 struct DevBuf {
     void *p = nullptr;

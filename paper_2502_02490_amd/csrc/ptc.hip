@@ -1150,10 +1150,8 @@ float *ptc_act(dirac_ctx *c, dirac_ptc *n, int l) {
     return (float *)((char *)n->acts.p + off);
 }
 
-// Input and output vectors a caller hands to the network are read and written in place when the kernels'
-// 16-byte accesses allow (in: acts[0] otherwise, copied by the caller of these functions).
-bool ptc_in_place(const void *p) { return ((uintptr_t)p & 15) == 0; }
-
+// Input and output vectors a caller hands to the network are read and written in place where the kernels can
+// (in_place; in: acts[0] otherwise, copied by the caller of these functions).
 // forward: the input is `in`, or acts[0] when that is NULL; leaves the output in `out`, or acts[nlayers], and,
 // with keep_all, every hidden layer's output in acts[l + 1] (the backward pass needs them).  With eo
 // the input's odd half must be zero, and only the even half of the output is formed (a network of
@@ -1196,7 +1194,7 @@ void ptc_backward_acts(dirac_ctx *c, dirac_ptc *n, const void *g_out, void *gin,
     for (int l = 0; l <= n->nlayers; ++l) maxc = std::max(maxc, n->ch[l]);
     char *gA = (char *)n->gbuf.p, *gB = gA + (size_t)maxc * chanb;
     const void *g = g_out;  // the gradient at the current layer's output
-    if (!ptc_in_place(g_out)) {
+    if (!in_place(g_out)) {
         HIP_CHECK(hipMemcpyAsync(gA, g_out, (size_t)n->ch[n->nlayers] * chanb, hipMemcpyDeviceToDevice, s));
         g = gA;
     }
