@@ -365,12 +365,15 @@ dirac_status dirac_apply(dirac_ctx *c, void *out, const void *in, dirac_prec pr,
     check_no_alias(out, nb, in, nb);
     if (lay == DIRAC_LAYOUT_NATIVE) {
         dl::full_apply(c, out, in, dagger != 0, pr, s);
-    } else if (dl::direct_layout(c, out, in)) {
+        return DIRAC_OK;
+    }
+    // staging also where this call needs none: the same call on other vectors may follow under graph capture
+    dl::PrecFields &f = c->f[pr];
+    f.user_in.alloc(native_bytes(c, pr, 0));
+    f.user_out.alloc(native_bytes(c, pr, 0));
+    if (dl::direct_layout(c, out, in)) {
         dl::full_apply_direct(c, out, in, lay, dagger != 0, pr, s);
     } else {
-        dl::PrecFields &f = c->f[pr];
-        f.user_in.alloc(native_bytes(c, pr, 0));
-        f.user_out.alloc(native_bytes(c, pr, 0));
         dl::spinor_import(c, f.user_in.p, in, 0, pr, lay, s);
         dl::full_apply(c, f.user_out.p, f.user_in.p, dagger != 0, pr, s);
         dl::spinor_export(c, out, f.user_out.p, 0, pr, lay, s);
@@ -392,12 +395,15 @@ dirac_status dirac_apply_eo(dirac_ctx *c, void *out, const void *in, dirac_prec 
     check_no_alias(out, nb, in, nb);
     if (lay == DIRAC_LAYOUT_NATIVE) {
         dl::schur_apply(c, out, in, dagger != 0, pr, s);
-    } else if (dl::direct_layout(c, out, in)) {
+        return DIRAC_OK;
+    }
+    // staging also where this call needs none: the same call on other vectors may follow under graph capture
+    dl::PrecFields &f = c->f[pr];
+    f.user_in.alloc(native_bytes(c, pr, 0));
+    f.user_out.alloc(native_bytes(c, pr, 0));
+    if (dl::direct_layout(c, out, in)) {
         dl::schur_apply_direct(c, out, in, lay, dagger != 0, pr, s);
     } else {
-        dl::PrecFields &f = c->f[pr];
-        f.user_in.alloc(native_bytes(c, pr, 0));
-        f.user_out.alloc(native_bytes(c, pr, 0));
         dl::spinor_import(c, f.user_in.p, in, 1, pr, lay, s);
         dl::schur_apply(c, f.user_out.p, f.user_in.p, dagger != 0, pr, s);
         dl::spinor_export(c, out, f.user_out.p, 1, pr, lay, s);
