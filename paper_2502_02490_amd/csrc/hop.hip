@@ -1,6 +1,8 @@
 // Hopping term between parities, fused with the clover field, and the even-odd Schur and full
 // operators built from it.  The kernels and their launch shapes are in hop_kernels.h, compiled
 // once per storage precision (hop_f64.hip, hop_f32.hip, hop_f16.hip, hop_bf16.hip).
+#include <cstdlib>
+
 #include "hop_launch.h"
 #include "internal.h"
 
@@ -73,11 +75,12 @@ bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 // (it loads 16 bytes at a time); larger ones are faster converted: its reads of the caller's sites, 192 or 96 bytes
 // apart, touch a cache line each.  D on a LEX vector in FP64: 12^4 30 us direct against 43 us converted,
 // 14x18x12x16 (24,192 sites) 51 against 52, 16^4 65 against 56; the Schur operator on an EO vector: 23 against
-// 28 us, 43 against 39, 46 against 42.
+// 28 us, 43 against 39, 46 against 42.  A launch shape forced by DIRAC_HOP_SHAPE is one of the NATIVE kernels', so
+// then every call is converted.
 constexpr int kDirSites = 16384;
 
 bool direct_layout(const dirac_ctx *c, const void *out, const void *in) {
-    return c->g.vh <= kDirSites && aligned16(out) && aligned16(in);
+    return c->g.vh <= kDirSites && aligned16(out) && aligned16(in) && !getenv("DIRAC_HOP_SHAPE");
 }
 
 void schur_apply_direct(dirac_ctx *c, void *out_e, const void *in_e, dirac_layout lay, int dagger, dirac_prec pr,
