@@ -123,11 +123,15 @@ typedef struct {
  * SU(3) plus one phase per link), builds the clover field on the device and
  * inverts its odd-site blocks.  Returns DIRAC_ESINGULAR if an odd-site block is
  * singular (the context is still created and must be destroyed).  Blocking.
- * Field memory of a destroyed context is kept for the next one, at most 1/32 of the device's
- * memory, and given back when an allocation of the library fails. */
+ * A program that creates contexts again after destroying others keeps the field memory of the
+ * destroyed ones for the next, at most 1/32 of the device's memory; it is given back when an
+ * allocation of the library fails, or by dirac_release_memory. */
 dirac_status dirac_create(const dirac_params *params, const void *su3_links, const double *u1_angles,
                           void *stream, dirac_ctx **out);
 dirac_status dirac_destroy(dirac_ctx *ctx);
+
+/* Give back the field memory kept of destroyed contexts on the current device. */
+dirac_status dirac_release_memory(void);
 
 /* Create a context from openQxD's storage of the gauge field (Sec. 4.1.4, Fig. gauge): the 8
  * links attached to every odd point, the odd points in eq. (ipt) order with cache block

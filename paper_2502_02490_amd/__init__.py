@@ -262,6 +262,11 @@ class Dirac:
         return info
 
 
+def release_memory():
+    """Give back the field memory that the library keeps of closed operators for the next ones (current GPU)."""
+    _lib.check(_lib.load().dirac_release_memory())
+
+
 def solve_batched(ops, xs, bs, nrhs, method=GCR, tol=1e-10, restart=32, max_iter=100000, layout="lex",
                   inner_prec="f32", inner_tol=None, stream=None):
     """Solve D_l x = b for nrhs right-hand sides on each lattice l (ops: Dirac objects).

@@ -15,7 +15,7 @@ LEX, EO, NATIVE, OPENQXD = 0, 1, 2, 3
 CGLS, GCR, MIXED_GCR, FGCR_PTC, FGCR_PTC_EO, FGCR_SAP = 0, 1, 2, 3, 4, 5
 
 # every symbol declared in include/dirac.h
-EXPORTS = ["dirac_create", "dirac_create_openqxd", "dirac_set_cache_block", "dirac_destroy", "dirac_load_clover", "dirac_get_clover", "clover_invert",
+EXPORTS = ["dirac_create", "dirac_create_openqxd", "dirac_set_cache_block", "dirac_destroy", "dirac_release_memory", "dirac_load_clover", "dirac_get_clover", "clover_invert",
            "dirac_native_bytes", "dirac_import", "dirac_export", "dirac_apply", "dirac_apply_eo", "dirac_apply_eo_multi",
            "dirac_apply_eo_noalloc",
            "dirac_apply_hop", "dirac_apply_clover", "dirac_sap", "dirac_solve", "dirac_solve_batched", "dirac_last_error",
@@ -65,6 +65,7 @@ def load(path: str = LIB_PATH):
     vp, i, st = ctypes.c_void_p, ctypes.c_int, ctypes.c_int
     lib.dirac_create.argtypes = [ctypes.POINTER(Params), vp, vp, vp, ctypes.POINTER(vp)]
     lib.dirac_destroy.argtypes = [vp]
+    lib.dirac_release_memory.argtypes = []
     lib.dirac_create_openqxd.argtypes = [ctypes.POINTER(Params), vp, vp, vp, vp, ctypes.POINTER(vp)]
     lib.dirac_set_cache_block.argtypes = [vp, vp]
     lib.dirac_load_clover.argtypes = [vp, vp, i, vp]

@@ -179,6 +179,7 @@ dirac_status dirac_create(const dirac_params *prm, const void *su3_links, const 
         for (int m = 0; m < 4; ++m) c->g.B[m] = prm->dims[m];
         c->g.cs = prm->cstar;
         c->g.h1 = prm->dims[1] / 2;
+        dl::pool_created();
         // scratch, released on return: the compressed links and the clover field are built from it
         planes.alloc_field(dl::link_planes_bytes(c->g));
         const void *U = readable_input(su3_links, (size_t)V * 4 * 9 * 16, 16, links, s);
@@ -280,6 +281,15 @@ dirac_status dirac_destroy(dirac_ctx *c) {
     c->flags.release();
     c->red.release();
     delete c;
+    dl::pool_destroyed();
+    API_END
+}
+
+dirac_status dirac_release_memory(void) {
+    API_BEGIN
+    int dev = -1;
+    HIP_CHECK(hipGetDevice(&dev));
+    dl::pool_trim(dev);
     API_END
 }
 

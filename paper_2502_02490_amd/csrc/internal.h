@@ -35,10 +35,13 @@ inline void require(bool ok, const std::string &msg, dirac_status s = DIRAC_EINV
 
 // pool.hip: device memory kept for the next context.  pool_take: a block of at least n bytes (*got) on
 // the current device (*dev); pool_give: back to the pool, when no work can touch the block any more;
-// pool_trim: free what the pool holds of a device.
+// pool_trim: free what the pool holds of a device; pool_created, pool_destroyed: a context is created, was destroyed
+// (the pool keeps blocks from the first creation after a destruction on).
 void *pool_take(size_t n, size_t *got, int *dev);
-void pool_give(void *p, size_t bytes, int dev);
+void pool_give(void *p, size_t bytes, int dev) noexcept;
 void pool_trim(int dev);
+void pool_created();
+void pool_destroyed();
 
 // api.hip: whether kernels of the current device can access a caller's memory where it lies: aligned, and not memory
 // of another device, which a copy reaches but which need not be mapped for this one.

@@ -3,11 +3,14 @@
 // it out again, so allocating the 1.1 GB of a 24^3 x 48 context afresh every time took 37 ms of the
 // 42 ms of a create / destroy pair, against 2 ms with the memory of the previous context.
 //
+// Nothing is kept until a program has shown that it goes from field to field: the memory of the contexts destroyed
+// on a device before another one is created there is freed, as it is where contexts live to the program's end.
 // Blocks enter only when no work can touch them any more (the caller has synchronised their device
 // or the one stream that used them), so any stream or thread may take them.  The pool holds at most
 // 1/32 of the device's memory; a block that kIdle later allocations did not want is freed, and so are
-// all of a device's blocks when an allocation on it fails.
+// all of a device's blocks when an allocation on it fails or dirac_release_memory is called.
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "internal.h"
@@ -26,10 +29,12 @@ struct Block {
 std::mutex g_mu;
 std::vector<Block> g_blocks;
 long g_clock = 0;
+constexpr int kDevices = 64;
+bool g_destroyed[kDevices], g_again[kDevices];  // a context was destroyed; another one was created after that
 
 size_t limit(int dev) {  // under g_mu
-    static size_t lim[64] = {};
-    if (dev < 0 || dev >= 64) return 0;
+    static size_t lim[kDevices] = {};
+    if (dev < 0 || dev >= kDevices || !g_again[dev]) return 0;
     if (!lim[dev]) {
         size_t free_b = 0, total = 0;
         if (hipMemGetInfo(&free_b, &total) != hipSuccess) {
@@ -42,6 +47,20 @@ size_t limit(int dev) {  // under g_mu
 }
 
 }  // namespace
+
+void pool_created() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return;
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_again[dev] = g_destroyed[dev];
+}
+
+void pool_destroyed() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return;
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_destroyed[dev] = true;
+}
 
 void *pool_take(size_t n, size_t *got, int *dev) {
     HIP_CHECK(hipGetDevice(dev));
@@ -85,30 +104,37 @@ void *pool_take(size_t n, size_t *got, int *dev) {
     return p;
 }
 
-void pool_give(void *p, size_t bytes, int dev) {
+void pool_give(void *p, size_t bytes, int dev) noexcept {
     int cur = -1;
+    bool kept = false;
     std::vector<void *> drop;
-    if (hipGetDevice(&cur) != hipSuccess || cur != dev) {
-        drop.push_back(p);
-    } else {
+    if (hipGetDevice(&cur) == hipSuccess && cur == dev) {
         std::lock_guard<std::mutex> lk(g_mu);
-        const size_t lim = limit(dev);
-        size_t held = bytes;
-        for (const Block &b : g_blocks)
-            if (b.dev == dev) held += b.bytes;
-        for (size_t k = 0; k < g_blocks.size() && held > lim;) {  // the oldest go first
-            if (g_blocks[k].dev == dev) {
-                held -= g_blocks[k].bytes;
-                drop.push_back(g_blocks[k].p);
-                g_blocks.erase(g_blocks.begin() + k);
-            } else {
-                ++k;
+        try {
+            const size_t lim = limit(dev);
+            size_t held = bytes;
+            for (const Block &b : g_blocks)
+                if (b.dev == dev) held += b.bytes;
+            if (bytes <= lim) {
+                g_blocks.reserve(g_blocks.size() + 1);
+                drop.reserve(g_blocks.size());
+                for (size_t k = 0; held > lim;) {  // the oldest go first
+                    if (g_blocks[k].dev == dev) {
+                        held -= g_blocks[k].bytes;
+                        drop.push_back(g_blocks[k].p);
+                        g_blocks.erase(g_blocks.begin() + k);
+                    } else {
+                        ++k;
+                    }
+                }
+                g_blocks.push_back(Block{p, bytes, dev, g_clock});
+                kept = true;
             }
+        } catch (const std::bad_alloc &) {  // no host memory for the list: the block is freed
         }
-        if (held > lim) drop.push_back(p);
-        else g_blocks.push_back(Block{p, bytes, dev, g_clock});
     }
     for (void *q : drop) (void)hipFree(q);
+    if (!kept) (void)hipFree(p);
 }
 
 void pool_trim(int dev) {
