@@ -514,9 +514,10 @@ __global__ __launch_bounds__(256) void k_ptc_tsum(PtcGeom a, int nparity, const 
 // The contraction is a real GEMM per 64-site tile: rows (pair = path NT + channel, spin, re/im) of
 // the transports, columns (near channel, spin, re/im), depth k = 64 colour + site; the four
 // (re/im, re/im) products of an output are combined in the final reduction.  FP32 operands are
-// split exactly into three BF16 parts (truncation: 8 + 8 + 8 bits), so every product is exact and
-// only the FP32 accumulation rounds, as in an FP32 contraction; of the nine products of two split
-// operands the last (2^-32 of the value) is left out.
+// split exactly into three BF16 parts (truncation: 8 + 8 + 8 bits), the second scaled by 2^8 and the third by 2^16
+// so that they keep the exponent of the value (unscaled, the parts of values below 1e-33 are subnormal in BF16 and
+// lose bits).  So every product is exact and only the FP32 accumulation rounds, as in an FP32 contraction; of the
+// nine products of two split operands the last (2^-32 of the value) is left out.
 //
 // A work-group of eight wavefronts, one per compute unit, sweeps its tiles.  Per tile it transposes
 // the near factor through LDS into registers (B operands, kept for all paths); per group of 8 pairs
@@ -526,13 +527,13 @@ __global__ __launch_bounds__(256) void k_ptc_tsum(PtcGeom a, int nparity, const 
 // group costs one barrier, and the raw data of the next group is loaded before the current one is
 // multiplied.  All nine paths of a tile run in one work-group (accumulators: 72 registers for 8 -> 8
 // channels), so the near factor is read once and the far factor's neighbours meet in L2.
-// The products of a group go to accumulators of their own, the smallest parts first, and are added
-// to the running ones in FP32: the matrix cores do not round their sums to nearest (a chain over all
+// The products of a group go to accumulators of their own, one for each power of 2^-8, and are added
+// to the running ones in FP32, the smallest parts first: the matrix cores do not round their sums to nearest (a chain over all
 // tiles drifted to 2.4e-6 of the result at 32^3 x 64).  The running sums are added to the work-group's
 // slice every kFlush tiles; one lane owns each entry of a slice (no atomics, deterministic).
 // Measured at 32^3 x 64 (FP32 vector contraction with the transports of x before -> now): 8 -> 8
 // channels 9.5 -> 3.65 ms, 8 -> 1 3.3 -> 0.76 ms, 1 -> 8 1.65 -> 1.10 ms; errors against 64 bits
-// 1.2-2.9e-7 -> 1.2-1.4e-7.  The 8 -> 8 kernel is bound by none of its parts alone: vector ALU 55 %
+// 1.2-2.9e-7 -> 1.0-1.4e-7.  The 8 -> 8 kernel is bound by none of its parts alone: vector ALU 55 %
 // busy (about 400 instructions per transport), matrix cores 18 %, 10 GB fetched; without cache
 // misses it takes 10 % less, without the matrix instructions 15 %, without the link products 5 %.
 template <int NT, int NL, bool NEARBF>
@@ -566,12 +567,12 @@ DEV int tile_order(const Geom &g, int per, int xcd, int j) {
     return ((j / bps) * 8 + xcd) * bps + j % bps;
 }
 
-// v = hi + mid + lo exactly, each with at most 8 significant bits (BF16 in the upper half word)
+// v = hi + 2^-8 mid + 2^-16 lo exactly, each with at most 8 significant bits (BF16 in the upper half word)
 DEV void split3(float v, uint32_t o[3]) {
     o[0] = __float_as_uint(v) & 0xffff0000u;
-    const float r1 = v - __uint_as_float(o[0]);
+    const float r1 = (v - __uint_as_float(o[0])) * 256.f;
     o[1] = __float_as_uint(r1) & 0xffff0000u;
-    o[2] = __float_as_uint(r1 - __uint_as_float(o[1]));
+    o[2] = __float_as_uint((r1 - __uint_as_float(o[1])) * 256.f);
 }
 DEV uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }  // upper halves
 // the value of the neighbouring lane (lane ^ 1)
@@ -777,8 +778,9 @@ __global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *_
 #pragma unroll
             for (int r = 0; r < W::RT; ++r) {
                 if (!mul || wr * W::RT + r >= rtiles) continue;
-                // with a split near factor the products of the two largest parts are summed apart
-                f32x4_t v[W::LS > 1 ? 2 : 1][W::CT];
+                // v[n]: the products of weight 2^-8n
+                constexpr int NV = W::LS > 1 ? 4 : 3;
+                f32x4_t v[NV][W::CT];
 #pragma unroll
                 for (auto &u : v)
 #pragma unroll
@@ -794,21 +796,22 @@ __global__ __launch_bounds__(512, 2) void k_ptc_wgrad(PtcGeom a, const float4 *_
                         for (int l = W::LS - 1; l >= 0; --l) {
                             if (q + l == 4) continue;
 #pragma unroll
-                            for (int c = 0; c < W::CT; ++c) {
-                                f32x4_t &u = v[W::LS > 1 && q + l == 0][c];
-                                u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, nb[l][c][ks], u, 0, 0, 0);
-                            }
+                            for (int c = 0; c < W::CT; ++c)
+                                v[q + l][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, nb[l][c][ks], v[q + l][c], 0, 0, 0);
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);  // bounds the LDS reads in flight (registers)
                 }
 #pragma unroll
-                for (auto &u : v)
+                for (int c = 0; c < W::CT; ++c) {
 #pragma unroll
-                    for (int c = 0; c < W::CT; ++c) {
+                    for (int e = 0; e < 4; ++e) {
+                        float u = v[NV - 1][c][e];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[grp][r][c][e] = fmaf(sign, u[c][e], acc[grp][r][c][e]);
+                        for (int n = NV - 2; n >= 0; --n) u = fmaf(u, 0x1p-8f, v[n][c][e]);
+                        acc[grp][r][c][e] = fmaf(sign, u, acc[grp][r][c][e]);
                     }
+                }
             }
             buf ^= 1;
         }
