@@ -585,7 +585,7 @@ dirac_status dirac_residual(dirac_ctx *c, void *r, const void *b, const void *x,
     // r = b - D x in place (element-wise), with |r|^2 and the non-finite flag
     B.lincomb(pr, pr, pr, 2, r, nullptr, 1.0, b, -1.0, r, rel_res ? sl : nullptr, 1.0, s);
     if (rel_res) {
-        B.mdot(pr, 2, b, 1, b, sl + 2, 1.0, s);
+        B.dot(pr, 2, b, b, sl + 2, 1.0, s);
         double h[4];
         read_slots(h, sl, 4, s);
         require(h[1] == 0.0 && std::isfinite(h[0]) && std::isfinite(h[2]), "non-finite value in the residual",
@@ -641,7 +641,7 @@ dirac_status dirac_dot(dirac_ctx *c, const void *a, const void *b, dirac_prec pr
     check_dev(b, nb, "b");
     dl::ensure_blas(c);
     double *sl = vec_slots(c);
-    c->work->blas.mdot(pr, sites == 0 ? 2 : 1, a, 1, b, sl + 4, 1.0, s);
+    c->work->blas.dot(pr, sites == 0 ? 2 : 1, a, b, sl + 4, 1.0, s);
     read_slots(dot, sl + 4, 2, s);
     API_END
 }
@@ -849,7 +849,7 @@ dirac_status ptc_train_step(dirac_ctx *c, dirac_ptc *n, const void *const *r, co
     std::vector<double> h(2 * (size_t)std::min(nbatch, kGroup)), f(std::min(nbatch, kGroup));
     for (int i0 = 0; i0 < nbatch; i0 += kGroup) {
         const int ng = std::min(kGroup, nbatch - i0);
-        for (int i = 0; i < ng; ++i) B.mdot(DIRAC_F32, 2, e[i0 + i], 1, e[i0 + i], sc + 2 * i, scale, s);
+        for (int i = 0; i < ng; ++i) B.dot(DIRAC_F32, 2, e[i0 + i], e[i0 + i], sc + 2 * i, scale, s);
         read_slots(h.data(), sc, 2 * ng, s);
         for (int i = 0; i < ng; ++i) {
             const double ne2 = h[2 * i];
@@ -902,7 +902,7 @@ dirac_status ptc_loss(dirac_ctx *c, dirac_ptc *n, const void *const *r, const vo
     double total = 0.0;
     for (int i = 0; i < nbatch; ++i) {
         dl::ptc_forward_acts(c, n, s, false, false, ptc_input(c, n, r[i], s));
-        B.mdot(DIRAC_F32, 2, e[i], 1, e[i], sc, 1.0, s);
+        B.dot(DIRAC_F32, 2, e[i], e[i], sc, 1.0, s);
         B.lincomb(DIRAC_F32, DIRAC_F32, DIRAC_F32, 2, d, nullptr, 1.0, dl::ptc_act(c, n, n->nlayers), -1.0, e[i],
                   sc + 2, 1.0, s);
         double h[4];

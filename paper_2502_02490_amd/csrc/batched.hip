@@ -74,7 +74,6 @@ namespace {
 
 constexpr int S_ALPHA = kSysScal - 64, S_XS = kSysScal - 62, S_ONE = kSysScal - 60;  // per-system free slots
 constexpr int S_TGT = kSysScal - 56;  // per-system target of the current GCR (normalised norm)
-constexpr int kMaxM = 64;
 constexpr int kPoll = 4;  // iterations between two host reads of the active counts
 
 bool graphs_enabled() {
@@ -425,7 +424,7 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
 
 void ensure_bwork(dirac_ctx *c, int m, int nrhs) {
     ensure_work(c, 1, DIRAC_F64, 1);
-    c->work->blas.reserve(c->V, kMaxM, nrhs);
+    c->work->blas.reserve(c->V, nrhs);
     if (!c->bwork) c->bwork = new BWork();
     BWork &w = *c->bwork;
     if (!w.s) HIP_CHECK(hipStreamCreateWithFlags(&w.s, hipStreamNonBlocking));
@@ -501,7 +500,7 @@ void solve_all(Batch &B, const dirac_solver_params *p, std::vector<dirac_solve_i
         all[l].assign(R, 1);
         upload_mask(L, all[l], L.act(), s);
         // |b_r|
-        Bl.mdot(DIRAC_F64, 2, L.w->f64[0].p, 1, L.w->f64[0].p, L.sp(S_MISC), scale(l), s, L.spec(L.act()));
+        Bl.dot(DIRAC_F64, 2, L.w->f64[0].p, L.w->f64[0].p, L.sp(S_MISC), scale(l), s, L.spec(L.act()));
         // eta-hat_e = b_e - D_eo A_oo^-1 b_o (all systems): even halves into eta, odd into r64
         void *eta = L.w->h64[0].p, *r64 = L.w->h64[2].p, *t64 = L.w->h64[3].p;
         halves(l, (char *)L.w->f64[0].p, eta, r64, true);

@@ -32,10 +32,10 @@ struct Blas {
     dirac_ctx *c = nullptr;
     DevBuf part, scal;  // partial sums, scalars
 
-    void reserve(int64_t nsites_max, int kmax, int nrhs = 1);
-    // out[j] = scale <Q_j, q>, j < k (complex, 2 doubles each)
-    void mdot(dirac_prec pr, int nh, const void *Q, int k, const void *q, double *out_dev, double scale, hipStream_t s,
-              const BatchSpec &bs = BatchSpec());
+    void reserve(int64_t nsites_max, int nrhs = 1);
+    // out = scale <x, y> (complex, 2 doubles)
+    void dot(dirac_prec pr, int nh, const void *x, const void *y, double *out_dev, double scale, hipStream_t s,
+             const BatchSpec &bs = BatchSpec());
     // Step k of a GCR cycle (basis vectors Q_0 .. Q_{k-1}, q = A p_k): the scalars beta_k and gamma_k and an estimate of
     // alpha_k, then q <- the new basis vector, rnew = r - alpha q (rnew may be r), |rnew|^2 in S_RED + 4, and
     // S_RED + 6 = 1 when nothing was left of q (then rnew = r, and the cycle should end), else 0; with ctl (one

@@ -103,50 +103,44 @@ DEV bool sys_of(const Bat &b, int &r, int &t) {
     return !b.active || b.active[r];
 }
 
-// partials[sys][blk][j] (complex) = sum over the group's sites of <Q_j, q>, j < k
+// partials[sys][blk] (complex) = sum over the group's sites of <a, b>
 template <typename S>
-__global__ __launch_bounds__(kRed) void k_mdot(Bat B, const typename St<S>::vec *Q, int k,
-                                               const typename St<S>::vec *q, double2 *partials) {
+__global__ __launch_bounds__(kRed) void k_dot(Bat B, const typename St<S>::vec *a, const typename St<S>::vec *b,
+                                              double2 *partials) {
     __shared__ double lds[2 * kRed / 64];
     int r, t;
     if (!sys_of(B, r, t)) return;
     const size_t vs = vstride<S>(B);
-    q += r * vs;
-    double a[24];
-    const bool on = t < B.n;
-    if (on) ld<S>(q, t, B.vh, a);
-    for (int j = 0; j < k; ++j) {
-        double v[2] = {0.0, 0.0};
-        if (on) {
-            double b[24];
-            ld_basis<S>(Q + ((size_t)j * B.nrhs + r) * vs, t, B.vh, b);
+    double v[2] = {0.0, 0.0};
+    if (t < B.n) {
+        double x[24], y[24];
+        ld<S>(b + r * vs, t, B.vh, x);
+        ld_basis<S>(a + r * vs, t, B.vh, y);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                v[0] = fma(b[2 * c], a[2 * c], v[0]);
-                v[0] = fma(b[2 * c + 1], a[2 * c + 1], v[0]);
-                v[1] = fma(b[2 * c], a[2 * c + 1], v[1]);
-                v[1] = fma(-b[2 * c + 1], a[2 * c], v[1]);
-            }
+        for (int c = 0; c < 12; ++c) {
+            v[0] = fma(y[2 * c], x[2 * c], v[0]);
+            v[0] = fma(y[2 * c + 1], x[2 * c + 1], v[0]);
+            v[1] = fma(y[2 * c], x[2 * c + 1], v[1]);
+            v[1] = fma(-y[2 * c + 1], x[2 * c], v[1]);
         }
-        group_sum<2>(v, lds);
-        if (threadIdx.x == 0) partials[(size_t)blockIdx.x * k + j] = make_double2(v[0], v[1]);
-        __syncthreads();
     }
+    group_sum<2>(v, lds);
+    if (threadIdx.x == 0) partials[blockIdx.x] = make_double2(v[0], v[1]);
 }
 
-// out_r[j] = scale * sum_b partials[r][b][j] (b ascending), nc doubles per entry; grid (nent, nrhs)
-__global__ __launch_bounds__(kRed) void k_reduce(int nblk, int nent, int nc, const double *partials, double scale,
-                                                 double *out, int sstride, const int *active) {
-    __shared__ double lds[4 * kRed / 64];
-    const int j = blockIdx.x, r = blockIdx.y;
+// out_r = scale * sum_b partials[r][b] (b ascending), nc <= 2 doubles; one work-group per system
+__global__ __launch_bounds__(kRed) void k_reduce(int nblk, int nc, const double *partials, double scale, double *out,
+                                                 int sstride, const int *active) {
+    __shared__ double lds[2 * kRed / 64];
+    const int r = blockIdx.x;
     if (active && !active[r]) return;
-    partials += (size_t)r * nblk * nent * nc;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    partials += (size_t)r * nblk * nc;
+    double v[2] = {0.0, 0.0};
     for (int b = threadIdx.x; b < nblk; b += kRed)
-        for (int c = 0; c < nc; ++c) v[c] += partials[((size_t)b * nent + j) * nc + c];
-    group_sum<4>(v, lds);
+        for (int c = 0; c < nc; ++c) v[c] += partials[(size_t)b * nc + c];
+    group_sum<2>(v, lds);
     if (threadIdx.x == 0)
-        for (int c = 0; c < nc; ++c) out[(size_t)r * sstride + j * nc + c] = scale * v[c];
+        for (int c = 0; c < nc; ++c) out[(size_t)r * sstride + c] = scale * v[c];
 }
 
 // ------------------------------------------------------------------ one GCR orthogonalisation step
@@ -760,11 +754,10 @@ int blas_grid(int64_t nsites) { return (int)((nsites + kRed - 1) / kRed); }
         default: throw Error(DIRAC_EINVAL, "unknown precision");                           \
     }
 
-void Blas::reserve(int64_t nsites_max, int kmax, int nrhs) {
-    const size_t nb = (size_t)blas_grid(nsites_max);
+void Blas::reserve(int64_t nsites_max, int nrhs) {
     nrhs = std::max(nrhs, 1);
-    part.alloc(std::max(nb * (size_t)nrhs * (size_t)std::max(kmax, 4) * 2 * sizeof(double) + 64,
-                        (size_t)nrhs * kGcrBlocks * kGcrEnt * sizeof(double)));
+    // the partial sums of the reductions by k_reduce, or of the GCR kernels
+    part.alloc((size_t)nrhs * std::max<size_t>(2 * (size_t)blas_grid(nsites_max), kGcrBlocks * kGcrEnt) * sizeof(double));
     const size_t n = (size_t)nrhs * kSysScal;
     if (scal.bytes < n * sizeof(double)) {
         scal.alloc(n * sizeof(double));
@@ -788,16 +781,15 @@ Bat make_bat(const dirac_ctx *c, int nh, const BatchSpec &bs) {
 }
 }  // namespace
 
-void Blas::mdot(dirac_prec pr, int nh, const void *Q, int k, const void *q, double *out_dev, double scale,
-                hipStream_t s, const BatchSpec &bs) {
+void Blas::dot(dirac_prec pr, int nh, const void *x, const void *y, double *out_dev, double scale, hipStream_t s,
+               const BatchSpec &bs) {
     const Bat b = make_bat(c, nh, bs);
-#define FN(S)                                                                                        \
-    k_mdot<S><<<b.nb * b.nrhs, kRed, 0, s>>>(b, (const typename St<S>::vec *)Q, k,                    \
-                                             (const typename St<S>::vec *)q, (double2 *)part.p);
+#define FN(S)                                                                                                     \
+    k_dot<S><<<b.nb * b.nrhs, kRed, 0, s>>>(b, (const typename St<S>::vec *)x, (const typename St<S>::vec *)y,     \
+                                            (double2 *)part.p);
     DISPATCH_PREC(pr, FN)
 #undef FN
-    k_reduce<<<dim3(k, b.nrhs), kRed, 0, s>>>(b.nb, k, 2, (const double *)part.p, scale, out_dev, b.sstride,
-                                              b.active);
+    k_reduce<<<b.nrhs, kRed, 0, s>>>(b.nb, 2, (const double *)part.p, scale, out_dev, b.sstride, b.active);
     HIP_CHECK(hipGetLastError());
 }
 
@@ -902,8 +894,7 @@ void Blas::lincomb(dirac_prec po, dirac_prec pa, dirac_prec pb, int nh, void *ou
     }
 #undef FN3
     if (out_dev)
-        k_reduce<<<dim3(1, bt.nrhs), kRed, 0, s>>>(bt.nb, 1, 2, (const double *)part.p, scale, out_dev, bt.sstride,
-                                                   bt.active);
+        k_reduce<<<bt.nrhs, kRed, 0, s>>>(bt.nb, 2, (const double *)part.p, scale, out_dev, bt.sstride, bt.active);
     HIP_CHECK(hipGetLastError());
 }
 
@@ -912,7 +903,7 @@ void Blas::cgls_xs(int nh, const double *rho, const double *wn, void *x, const v
     const int vh = (int)c->vh, n = nh * vh, nb = blas_grid(n);
     k_cgls_xs<double><<<nb, kRed, 0, s>>>(n, vh, rho, wn, (double2 *)x, (const double2 *)p, (double2 *)sv,
                                           (const double2 *)w, (double *)part.p);
-    k_reduce<<<dim3(1, 1), kRed, 0, s>>>(nb, 1, 1, (const double *)part.p, 1.0, out_dev, 0, nullptr);
+    k_reduce<<<1, kRed, 0, s>>>(nb, 1, (const double *)part.p, 1.0, out_dev, 0, nullptr);
     HIP_CHECK(hipGetLastError());
 }
 

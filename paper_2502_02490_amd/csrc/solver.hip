@@ -78,7 +78,7 @@ void ensure_blas(dirac_ctx *c) {
         c->work = new SolverWork();
         c->work->blas.c = c;
     }
-    c->work->blas.reserve(c->V, kMaxRestart);
+    c->work->blas.reserve(c->V);
     if (!c->work->pin) HIP_CHECK(hipHostMalloc((void **)&c->work->pin, 8 * sizeof(double), hipHostMallocDefault));
 }
 
@@ -269,7 +269,7 @@ dirac_status solve_native(dirac_ctx *c, const dirac_solver_params *p, bool x0, d
     require(c->f[DIRAC_F64].inv_ready[1], "odd-site clover inverse not available (singular block?)");
 
     // |b|^2 (normalised by the half-vector length, like every norm below)
-    B.mdot(DIRAC_F64, 2, bf, 1, bf, sc_ptr(w, S_MISC), scale, s);
+    B.dot(DIRAC_F64, 2, bf, bf, sc_ptr(w, S_MISC), scale, s);
     const double bn = std::sqrt(read_scalar(w, S_MISC, s));
     require(std::isfinite(bn), "right-hand side holds NaN or Inf", DIRAC_ENONFINITE);
     if (bn == 0.0) {
@@ -455,7 +455,7 @@ dirac_status solve_cgls(dirac_ctx *c, const dirac_solver_params *p, bool x0, dir
     w.P.alloc(3 * full64);
     char *rv = (char *)w.P.p, *pv = rv + full64, *wv = pv + full64;
     double *rho = sc_ptr(w, S_MISC + 8), *rho_new = sc_ptr(w, S_MISC + 10), *wn = sc_ptr(w, S_MISC + 12);
-    B.mdot(DIRAC_F64, 2, bf, 1, bf, sc_ptr(w, S_MISC), scale, s);
+    B.dot(DIRAC_F64, 2, bf, bf, sc_ptr(w, S_MISC), scale, s);
     const double bn = std::sqrt(read_scalar(w, S_MISC, s));
     require(std::isfinite(bn), "right-hand side holds NaN or Inf", DIRAC_ENONFINITE);
     if (!x0) B.lincomb(DIRAC_F64, DIRAC_F64, DIRAC_F64, 2, xf, nullptr, 0.0, bf, 0.0, nullptr, nullptr, 1.0, s);
@@ -472,13 +472,13 @@ dirac_status solve_cgls(dirac_ctx *c, const dirac_solver_params *p, bool x0, dir
         if (it > 0) ++info->restarts;
         full_apply(c, rv, sv, 1, DIRAC_F64, s);
         B.lincomb(DIRAC_F64, DIRAC_F64, DIRAC_F64, 2, pv, nullptr, 1.0, rv, 0.0, nullptr, nullptr, 1.0, s);
-        B.mdot(DIRAC_F64, 2, rv, 1, rv, rho, scale, s);
+        B.dot(DIRAC_F64, 2, rv, rv, rho, scale, s);
         while (it < p->max_iter) {
             full_apply(c, wv, pv, 0, DIRAC_F64, s);
-            B.mdot(DIRAC_F64, 2, wv, 1, wv, wn, scale, s);
+            B.dot(DIRAC_F64, 2, wv, wv, wn, scale, s);
             B.cgls_xs(2, rho, wn, xf, pv, sv, wv, sc_ptr(w, S_MISC + 6), s);
             full_apply(c, rv, sv, 1, DIRAC_F64, s);
-            B.mdot(DIRAC_F64, 2, rv, 1, rv, rho_new, scale, s);
+            B.dot(DIRAC_F64, 2, rv, rv, rho_new, scale, s);
             B.cgls_p(2, rho_new, rho, pv, rv, s);
             B.copy_scalar(rho_new, rho, s);
             ++it;

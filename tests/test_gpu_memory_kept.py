@@ -54,3 +54,30 @@ def test_memory_beside_live_contexts():
     r = subprocess.run([sys.executable, "-u", "-c", CHILD], cwd=ROOT, capture_output=True, text=True, timeout=90)
     flush(r.stdout)
     assert r.returncode == 0, r.stdout + r.stderr[-2000:]
+
+
+REDUCE = r"""
+import torch
+import paper_2502_02490_amd as P
+
+dims = (64, 32, 32, 32)
+U = torch.eye(3, dtype=torch.complex128, device="cuda").repeat(64 * 32 ** 3, 4, 1, 1)
+with P.Dirac(U, None, dims, 0.12, 1.0, 0.0, 1) as D:
+    x = D.native_empty("f32")
+    x.fill_(0.5)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    d = D.dot(x, x, "f32")
+    used = before - torch.cuda.mem_get_info()[0]
+    print("work space of the reductions", used, flush=True)
+    assert d == 0.25 * 24 * 64 * 32 ** 3
+    assert used <= 6 << 20  # two doubles a work-group and the scalars, in allocations of up to 2 MiB
+"""
+
+
+def test_work_space_of_the_reductions():
+    need_gpu()
+    flush("[gpu] work space of the reductions")
+    r = subprocess.run([sys.executable, "-u", "-c", REDUCE], cwd=ROOT, capture_output=True, text=True, timeout=90)
+    flush(r.stdout)
+    assert r.returncode == 0, r.stdout + r.stderr[-2000:]
