@@ -38,7 +38,7 @@ HOP_SHAPES = ["k_hop_p bs256 1/CU 2 neighbours/iteration streaming hints (persis
               "k_hop bs256 xcd-order", "k_hop bs256", "k_hop bs128 xcd-order", "k_hop bs64 xcd-order",
               "k_hop_t tt4 (time-tiled LDS)", "k_hop_t tt8 (time-tiled LDS)", "k_hop_p bs512 1/CU (persistent)",
               "k_hop_p bs256 2/CU (persistent)", "k_hop_p bs256 1/CU xcd-regions (persistent)",
-              "k_hop_d (direction-parallel)", "k_hop_p bs512 2/CU streaming hints (persistent)",
+              "k_hop_d (direction-parallel)", "k_hop_p bs256 1/CU 2 neighbours/iteration streaming hints (persistent; as shape 0)",
               "k_hop_ps bs256 1/CU (XCD slab sweep)", "k_hop_ps bs256 2/CU (XCD slab sweep)",
               "k_hop_ps bs128 2/CU (XCD slab sweep)", "k_hop_p bs256 2/CU 2 neighbours/iteration (persistent)",
               "k_hop_mr 2 RHS/work-item 1/CU streaming hints", "k_hop_mr 4 RHS/work-item 1/CU streaming hints",

@@ -975,12 +975,14 @@ struct HopShape {
 // its next-direction prefetch; x1s: the x1-split sweep (or block order); cw: the right-hand-side
 // blocked column walk with cw wavefronts per work-group and at most cr right-hand sides each,
 // pers work-groups per compute unit wanted (16-bit and FP32 storage only), db: its LDS staging
-// double-buffered; dir: the direction-parallel kernel.
+// double-buffered; dir: the direction-parallel kernel.  15 is shape 0 again: the number is kept, since forced shapes and
+// tuning files name shapes by it (512-wide work-groups, two per compute unit, with streaming hints were the fastest
+// shape on none of nine lattices from 8^4 to 96 x 48^3 in any precision with 1, 3 or 12 right-hand sides).
 const HopShape kShapes[] = {
     {256, 0, 0, 1, 0, 2, 1, 1}, {256, 0, 0, 1, 0, 1, 1, 1}, {256, 0, 0, 2, 0, 1, 1, 1}, {256, 0, 0, 1, 0, 1, 0, 1},
     {256, 0, 0, 1, 0, 2, 0, 1}, {256, 1, 0, 0, 0, 1, 0, 1}, {256, 0, 0, 0, 0, 1, 0, 1}, {128, 1, 0, 0, 0, 1, 0, 1},
     {64, 1, 0, 0, 0, 1, 0, 1},  {256, 1, 4, 0, 0, 1, 0, 1}, {512, 1, 8, 0, 0, 1, 0, 1}, {512, 0, 0, 1, 0, 1, 0, 1},
-    {256, 0, 0, 2, 0, 1, 0, 1}, {256, 1, 0, 1, 0, 1, 0, 1}, {512, 0, 0, 0, 0, 1, 0, 1, 0, 0, 0, 0, 0, 0, 1}, {512, 0, 0, 2, 0, 1, 1, 1},
+    {256, 0, 0, 2, 0, 1, 0, 1}, {256, 1, 0, 1, 0, 1, 0, 1}, {512, 0, 0, 0, 0, 1, 0, 1, 0, 0, 0, 0, 0, 0, 1}, {256, 0, 0, 1, 0, 2, 1, 1},
     {256, 0, 0, 1, 1, 1, 0, 1}, {256, 0, 0, 2, 1, 1, 0, 1}, {128, 0, 0, 2, 1, 1, 0, 1}, {256, 0, 0, 2, 0, 2, 0, 1},
     {256, 0, 0, 1, 0, 1, 1, 2}, {256, 0, 0, 1, 0, 1, 1, 4}, {256, 0, 0, 2, 0, 1, 1, 2},
     {256, 0, 0, 0, 0, 1, 1, 1, 4, 0}, {512, 0, 0, 0, 0, 1, 1, 1, 8, 0}, {256, 0, 0, 0, 0, 1, 1, 1, 4, 1},
@@ -1195,8 +1197,7 @@ void launch_hop(const HopArgs<S> &a, int shape, hipStream_t s) {
         else if (h.bs == 256) launch_slab<S, DAG, MODE, 256>(a, h.pers, s);
         else launch_slab<S, DAG, MODE, 128>(a, h.pers, s);
     } else if (h.pers) {
-        if (h.bs == 512 && h.nt) launch_persistent<S, DAG, MODE, 512, 1, true>(a, h.pers, 0, s);
-        else if (h.bs == 512) launch_persistent<S, DAG, MODE, 512>(a, h.pers, h.xcd, s);
+        if (h.bs == 512) launch_persistent<S, DAG, MODE, 512>(a, h.pers, h.xcd, s);
         else if (h.nt && h.npi == 4) launch_persistent<S, DAG, MODE, 256, 4, true>(a, h.pers, 0, s);
         else if (h.nt && h.npi == 2) launch_persistent<S, DAG, MODE, 256, 2, true>(a, h.pers, 0, s);
         else if (h.nt) launch_persistent<S, DAG, MODE, 256, 1, true>(a, h.pers, 0, s);
