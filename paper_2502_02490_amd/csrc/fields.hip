@@ -171,19 +171,35 @@ DEV int64_t user_site(const Geom &g, int p, int i, int lay, int half) {
 // (764 MB: the rate of a copy).
 template <typename U, typename S, int NR>
 __global__ __launch_bounds__(kBlock) void k_site_in(Geom g, int p0, int np, int lay, int half, const U *__restrict__ user,
-                                                     typename St<S>::vec *__restrict__ dst, size_t parity_vecs) {
+                                                     typename St<S>::vec *__restrict__ dst0,
+                                                     typename St<S>::vec *__restrict__ dst1) {
     using T = typename St<S>::acc;
     constexpr int W = St<S>::W, NP = NR / W;
+    constexpr int IT = NR * kSB / kBlock, NB = IT % 9 == 0 ? 9 : 6;  // reals per thread, loaded NB at a time
+    static_assert(NR * kSB % kBlock == 0 && IT % NB == 0, "whole batches of loads");
     __shared__ T t[kSB * (NR + 1)];
     __shared__ int64_t us[kSB];
     const int i0 = (int)blockIdx.x * kSB, ns = min(kSB, g.vh - i0), lane = threadIdx.x & (kSB - 1);
     for (int p = p0; p < p0 + np; ++p) {
         if (threadIdx.x < ns) us[threadIdx.x] = user_site(g, p, i0 + (int)threadIdx.x, lay, half) * NR;
         __syncthreads();
-        for (int k = threadIdx.x; k < ns * NR; k += kBlock) t[k + k / NR] = (T)user[us[k / NR] + k % NR];
+#pragma unroll
+        for (int b = 0; b < IT; b += NB) {
+            U v[NB];
+#pragma unroll
+            for (int e = 0; e < NB; ++e) {
+                const int k = threadIdx.x + (b + e) * kBlock;
+                if (k < ns * NR) v[e] = user[us[k / NR] + k % NR];
+            }
+#pragma unroll
+            for (int e = 0; e < NB; ++e) {
+                const int k = threadIdx.x + (b + e) * kBlock;
+                if (k < ns * NR) t[k + k / NR] = (T)v[e];
+            }
+        }
         __syncthreads();
         if (lane < ns) {
-            typename St<S>::vec *q = site_ptr(dst + (size_t)(p - p0) * parity_vecs, (uint32_t)(i0 + lane), NP);
+            typename St<S>::vec *q = site_ptr(p == p0 ? dst0 : dst1, (uint32_t)(i0 + lane), NP);
             for (int m = threadIdx.x >> 6; m < NP; m += kBlock / kSB) q[m * kSB] = St<S>::pack(t + lane * (NR + 1) + m * W);
         }
     }
@@ -255,7 +271,7 @@ void spinor_io(dirac_ctx *c, void *native, const void *user, bool in, int sites,
     const size_t pv = (size_t)(24 / St<S>::W) * c->g.vhp;  // vectors of a parity
     const int nb = c->g.vhp / kSB, p0 = sites == 2, np = sites == 0 ? 2 : 1, half = sites != 0;
     if (in)
-        k_site_in<U, S, 24><<<nb, kBlock, 0, s>>>(c->g, p0, np, lay, half, (const U *)user, (V *)native, pv);
+        k_site_in<U, S, 24><<<nb, kBlock, 0, s>>>(c->g, p0, np, lay, half, (const U *)user, (V *)native, (V *)native + pv);
     else
         k_site_out<U, S, 24><<<nb, kBlock, 0, s>>>(c->g, p0, np, lay, half, (const V *)native, (const V *)native + pv, (U *)user);
     HIP_CHECK(hipGetLastError());
@@ -391,10 +407,9 @@ void clover_import(dirac_ctx *c, const double *user, dirac_layout lay, hipStream
     require(lay == DIRAC_LAYOUT_LEX || lay == DIRAC_LAYOUT_EO || lay == DIRAC_LAYOUT_OPENQXD,
             "clover layout must be LEX, EO or OPENQXD");
     PrecFields &f = c->f[DIRAC_F64];
-    for (int p = 0; p < 2; ++p) {
-        f.clov[p].alloc_field((size_t)72 * sizeof(double) * c->g.vhp);
-        k_site_in<double, double, 72><<<c->g.vhp / kSB, kBlock, 0, s>>>(c->g, p, 1, lay, 0, user, (double2 *)f.clov[p].p, 0);
-    }
+    for (int p = 0; p < 2; ++p) f.clov[p].alloc_field((size_t)72 * sizeof(double) * c->g.vhp);
+    k_site_in<double, double, 72><<<c->g.vhp / kSB, kBlock, 0, s>>>(c->g, 0, 2, lay, 0, user, (double2 *)f.clov[0].p,
+                                                                     (double2 *)f.clov[1].p);
     HIP_CHECK(hipGetLastError());
     c->sap_ready = false;
     for (int q = 0; q < 4; ++q) {
