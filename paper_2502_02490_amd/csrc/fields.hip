@@ -166,9 +166,11 @@ DEV int64_t user_site(const Geom &g, int p, int i, int lay, int half) {
 // cache lines of one are still in L2 for the other): the caller's side is accessed with consecutive lanes on
 // consecutive reals of a site, the planes 1 KB at a time, and the block goes through LDS in between (an odd
 // row length in reals: no bank conflicts either way).  Bandwidth-bound; one thread per site on both sides
-// left the caller's side with 192 or 576 bytes between lanes.  A LEX vector of
-// 40 x 18 x 22 x 26 in FP64: in 38 -> 33 us, out 48 -> 28 us; a clover field of 24^3 x 48 out 200 -> 144 us
-// (764 MB: the rate of a copy).
+// left the caller's side with 192 or 576 bytes between lanes.  On the way in a thread issues six or nine loads
+// before it waits for the first (one at a time was slower than one thread per site for clover fields and for
+// FP32 vectors in EO order).  One thread per site -> now: a LEX vector of 40 x 18 x 22 x 26 in FP64 in 33 -> 26 us, out
+// 42 -> 25 us; an FP32 vector of 64 x 32^3 in EO order in 78 -> 70 us; a LEX clover field of 24^3 x 48 in 167 -> 145 us,
+// out 219 -> 168 us (764 MB: the rate of a copy).
 template <typename U, typename S, int NR>
 __global__ __launch_bounds__(kBlock) void k_site_in(Geom g, int p0, int np, int lay, int half, const U *__restrict__ user,
                                                      typename St<S>::vec *__restrict__ dst0,
