@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kRed) void k_reduce(int nblk, int nc, const double 
 //     <Q_k, r>, |r_new|^2 of the vectors as stored; then alpha = <Q_k, r> / |Q_k|^2 is known;
 //   k_gcr_correct: r_new -= (alpha - a) Q_k and |r_new|^2 anew, where |alpha - a|^2 |Q_k|^2 (what the estimate adds to the
 //     least |r_new|^2) is above `slack` |r_new|^2, 1e-10 or what rounding the stored r adds; else it returns at once
-//     (2 us), and alpha = a counts as taken.
+//     (3 to 5 us), and alpha = a counts as taken.
 // So the beta, the step and the solution's coefficients rest on sums over the stored vectors: the estimate
 // cancels where q nearly lies in the span of the Q_j, and with alpha and gamma from it alone directions with
 // |q_perp| / |q| below 1e-7 in FP64 (3e-5 in FP32) had to be left out, and solves that need one did not
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kRed) void k_reduce(int nblk, int nc, const double 
 // where 512 would leave compute units without a work-group.  On the smallest lattices (kWideSites) a thread would
 // still wait for one basis vector after the other (1.6 us each in FP64), so there (WIDE) a chunk is 64 sites and
 // wavefront w of eight takes the basis vectors w, w + 8, ...: at 8^4 a kernel of an FP64 GCR(32) step falls from 34
-// to 10 us on average; at 16^3 x 32 one right-hand side is slower that way (92 against 78 us per iteration).
+// to 9 us on average; at 16^3 x 32 one right-hand side is slower that way (92 against 78 us per iteration).
 // k_gcr_correct, which reads no basis vectors, takes one 16-byte vector per thread.  The partial sums and the
 // finishing work-group's reads of them are agent-scope accesses (the XCDs' L2s are not coherent with each
 // other), summed in a fixed order.
@@ -832,7 +832,9 @@ void Blas::gcr_step(dirac_prec pr, int nh, const void *Q, int k, void *q, const 
     const Bat b = make_bat(c, nh, bs);
     const int nblk = gcr_blocks(b);
     const int64_t nv = (int64_t)(b.n / b.vh) * (24 * real_size(pr) / 16) * padded_sites(b.vh);  // 16-byte vectors
-    const int nr = (int)std::min<int64_t>((nv + kGcr - 1) / kGcr, kGcrBlocks / 2);  // rarely with work: one per compute unit
+    // the correction, rarely with work: about one work-group per compute unit over all systems, so that the others'
+    // kernels do not hold it up for long (3,072 of them took 90 us to return among the lattices of a batch)
+    const int nr = (int)std::min<int64_t>((nv + kGcr - 1) / kGcr, std::max(kGcrBlocks / 2 / b.nrhs, 16));
 #define FNW(S, WIDE, BS)                                                                                              \
     k_gcr_step<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,                 \
                                                          (typename St<S>::vec *)q, (const typename St<S>::vec *)r,   \

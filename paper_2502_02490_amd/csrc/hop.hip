@@ -72,11 +72,12 @@ bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 // Operators on vectors in the caller's layout without conversion passes: the direction-parallel kernel reads and
 // writes them as they are.  Taken for lattices of at most kDirSites sites per parity and 16-byte aligned vectors
-// (it loads 16 bytes at a time); larger ones are faster converted: its reads of the caller's sites, 192 or 96 bytes
-// apart, touch a cache line each.  D on a LEX vector in FP64: 12^4 30 us direct against 43 us converted,
-// 14x18x12x16 (24,192 sites) 51 against 52, 16^4 65 against 56; the Schur operator on an EO vector: 23 against
-// 28 us, 43 against 39, 46 against 42.  A launch shape forced by DIRAC_HOP_SHAPE is one of the NATIVE kernels', so
-// then every call is converted.
+// (it loads 16 bytes at a time); on large ones its reads of the caller's sites, 192 or 96 bytes apart, touch a cache
+// line each and a conversion is faster.  Direct against converted, calls queued one after another: D on a LEX vector in FP64
+// 12^4 19 against 42 us, 16 x 8 x 16^2 (16,384 sites) 20 against 49, 14 x 18 x 12 x 16 (24,192) 32 against 40, 16^4 40 against
+// 44, 16^3 x 24 (49,152) 59 against 55; the Schur operator on an EO vector 16 against 32, 19 against 34, 31 against 37, 33
+// against 41, 48 against 49.  The line lies below the crossing, where direct calls are faster by half or more in every layout.
+// A launch shape forced by DIRAC_HOP_SHAPE is one of the NATIVE kernels', so then every call is converted.
 constexpr int kDirSites = 16384;
 
 bool direct_layout(const dirac_ctx *c, const void *out, const void *in) {

@@ -758,9 +758,10 @@ __global__ __launch_bounds__(64 * TT) void k_hop_t(HopArgs<S> a) {
 // a NATIVE intermediate keeps `in` NATIVE with chi_lay for chi), so a call on a small lattice needs no
 // conversion passes; with np = 2 one launch computes both parities of a full vector.
 // Bound by latency (two dependent memory accesses and two barriers, 6 us a launch).  At 8^4 in FP64 the
-// Schur operator on an EO vector takes 14.8 us, against 27.8 us for the best other shape between
-// conversion passes, D on a LEX vector 13 against 36 us; on NATIVE vectors it is the faster shape up to
-// about 10,000 sites per parity (12^4: 21 against 23 us in FP64, 16^4: 44 against 31 us).
+// Schur operator on an EO vector takes 12 us, against 27 us for the best other shape between
+// conversion passes, D on a LEX vector 9 against 36 us; on NATIVE vectors it is the faster shape up to
+// about 32,000 sites per parity in FP64 (12^4: 15 against 24 us, 16^4: 30.5 against 31.6, 32 x 16^3: 56 against 42)
+// and 65,000 in the 16-bit formats (32 x 16^3 in BF16: 20.7 against 23.2 us).
 template <typename S>
 struct HopDirArgs {
     Geom g;
