@@ -74,7 +74,7 @@ HOP_CLOV_KERNEL_32C64 = {
     2: ("k_hop_p<double, 0, 2, 256, 0, 1, true>", 131072), 3: ("k_hop_p<double, 0, 2, 256, 0, 1, false>", 65536),
     4: ("k_hop_p<double, 0, 2, 256, 0, 2, false>", 65536), 11: ("k_hop_p<double, 0, 2, 512, 0, 1, false>", 131072),
     12: ("k_hop_p<double, 0, 2, 256, 0, 1, false>", 131072), 13: ("k_hop_p<double, 0, 2, 256, 1, 1, false>", 65536),
-    15: ("k_hop_p<double, 0, 2, 512, 0, 1, true>", 262144),
+    15: ("k_hop_p<double, 0, 2, 256, 0, 2, true>", 65536),
     16: ("k_hop_ps<double, 0, 2, 256, 1, false>", 65536), 17: ("k_hop_ps<double, 0, 2, 256, 1, false>", 131072),
     18: ("k_hop_ps<double, 0, 2, 128, 1, false>", 65536), 19: ("k_hop_p<double, 0, 2, 256, 0, 2, false>", 131072),
     28: ("k_hop_p<double, 0, 2, 256, 0, 4, true>", 65536), 29: ("k_hop_p<double, 0, 2, 256, 0, 4, true>", 131072),
