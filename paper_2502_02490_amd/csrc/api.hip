@@ -493,6 +493,7 @@ dirac_status dirac_solve(dirac_ctx *c, void *x, const void *b, dirac_layout lay,
     dl::ensure_work(c, p->method == DIRAC_SOLVER_CGLS ? 1 : p->restart, inner, 1);
     void *bn = dl::solver_full64(c, 0), *xn = dl::solver_full64(c, 1);
     c->work->syncs = 0;
+    c->work->correct = false;
     if (lay == DIRAC_LAYOUT_NATIVE) {
         HIP_CHECK(hipMemcpyAsync(bn, b, nb, hipMemcpyDeviceToDevice, s));
         if (p->x0_given) HIP_CHECK(hipMemcpyAsync(xn, x, nb, hipMemcpyDeviceToDevice, s));

@@ -5,9 +5,9 @@
 // freezes converged systems.  The launch sequence of iteration k of a cycle, for all lattices at
 // once (one branch per lattice, so the lattices run concurrently), is captured into one hipGraph
 // and replayed: one graph launch per iteration for the whole batch.  Convergence is decided on the
-// device: after each iteration a small kernel per lattice compares each active system's residual
-// norm with its target, clears the system's mask entry, counts its iterations and the systems still
-// active; a last node gathers the counts of all lattices into one array, which the host reads only
+// device: after each iteration one kernel for all lattices compares each active system's residual
+// norm with its target, clears the system's mask entry, counts its iterations and, per lattice, the systems still
+// active, into one array, which the host reads only
 // every kPoll iterations and at the end of a cycle.  The end of a cycle (back-substitution, solution
 // update, true residual, restart decision) is device work too, in one graph per cycle length.
 // Method: FP64 even-odd GCR, or FP64 defect correction around a batched inner GCR in
@@ -39,8 +39,8 @@ struct BWork {
     hipStream_t ms = nullptr;  // the batch stream: graphs and the GCR cycles of all lattices
     hipEvent_t fork = nullptr;
     std::vector<hipEvent_t> ev;  // one per lattice: branch joins and stream hand-overs
-    DevBuf table, nact;          // device pointers to every lattice's active count; gathered counts
-    int *host_nact = nullptr;    // pinned copy of the gathered counts
+    DevBuf table, nact;          // every lattice's LatState; the counts of their active systems
+    int *host_nact = nullptr;    // pinned copy of the counts
     int nlat_cap = 0;
     std::vector<hipGraphExec_t> it_graphs, end_graphs;
     hipGraphExec_t start_graph = nullptr;
@@ -83,48 +83,58 @@ bool graphs_enabled() {
 
 // ------------------------------------------------------------------ device-side GCR control
 // Per-system counters of a lattice (int, R systems): [0, R) iterations, [R, 2R) restarts,
-// [2R, 3R) iterations in the current cycle, [3R, 4R) flags (1 converged, 2 non-finite),
-// [4R] systems still active.
+// [2R, 3R) iterations in the current cycle, [3R, 4R) flags (1 converged, 2 non-finite).
 
+// What the status kernel needs of a lattice.
+struct LatState {
+    int R;
+    int *act;
+    const int *cyc;
+    int *cnt;
+    const double *scal;
+};
+
+// One wavefront per lattice, for all lattices of the batch; out[l] = the systems of lattice l still active.
 // mode 0: after iteration k of a cycle (the systems in act); 1: start of a solve (the systems in
 // act); 2: end of a cycle, after the true residual (the systems in cyc).  A system whose residual
 // norm is not finite, or at most its target, leaves the active set; at the start and the end of a
-// cycle the latter is marked converged, and at the end of a cycle the others restart.  One
-// wavefront; the count of active systems is summed in a fixed order.  A system that took an empty step (GCR met a
+// cycle the latter is marked converged, and at the end of a cycle the others restart.
+// The count of active systems is summed in a fixed order.  A system that took an empty step (GCR met a
 // dependent direction) waits for the end of the cycle.
-__global__ void k_bat_status(int R, int mode, int k, int *act, const int *cyc, int *cnt, const double *scal) {
+__global__ void k_bat_status(const LatState *lat, int mode, int k, int *out) {
     __shared__ int part[64];
+    const LatState L = lat[blockIdx.x];
     int na = 0;
-    for (int q = threadIdx.x; q < R; q += 64) {
-        const bool in = mode == 2 ? cyc[q] != 0 : act[q] != 0;
+    for (int q = threadIdx.x; q < L.R; q += 64) {
+        const bool in = mode == 2 ? L.cyc[q] != 0 : L.act[q] != 0;
         if (in) {
-            const double *sq = scal + (size_t)q * kSysScal;
+            const double *sq = L.scal + (size_t)q * kSysScal;
             const double rn2 = sq[S_RED + 4];
             if (mode == 0) {
-                ++cnt[q];
-                cnt[2 * R + q] = k + 1;
+                ++L.cnt[q];
+                L.cnt[2 * L.R + q] = k + 1;
             }
             if (!isfinite(rn2)) {
-                cnt[3 * R + q] |= 2;
-                act[q] = 0;
+                L.cnt[3 * L.R + q] |= 2;
+                L.act[q] = 0;
             } else if (sqrt(rn2) <= sq[S_TGT]) {
-                act[q] = 0;
-                if (mode != 0) cnt[3 * R + q] |= 1;
+                L.act[q] = 0;
+                if (mode != 0) L.cnt[3 * L.R + q] |= 1;
             } else if (mode == 0) {
-                if (sq[S_RED + 6] != 0.0) act[q] = 0;  // an empty step: the rest of the cycle would repeat it
+                if (sq[S_RED + 6] != 0.0) L.act[q] = 0;  // an empty step: the rest of the cycle would repeat it
             } else if (mode == 2) {
-                act[q] = 1;
-                ++cnt[R + q];
+                L.act[q] = 1;
+                ++L.cnt[L.R + q];
             }
         }
-        na += act[q] != 0;
+        na += L.act[q] != 0;
     }
     part[threadIdx.x] = na;
     __syncthreads();
     if (threadIdx.x == 0) {
         int s = 0;
         for (int j = 0; j < 64; ++j) s += part[j];
-        cnt[4 * R] = s;
+        out[blockIdx.x] = s;
     }
 }
 
@@ -144,12 +154,6 @@ __global__ void k_sys_gather(int n, const double *src, int stride, double *dst) 
 __global__ void k_sys_scatter(int n, const double *src, double *dst, int stride) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r < n) dst[(size_t)r * stride] = src[r];
-}
-
-// out[l] = *src[l]: the active counts of all lattices into one array.
-__global__ void k_gather_counts(int n, const int *const *src, int *out) {
-    const int l = threadIdx.x;
-    if (l < n) out[l] = *src[l];
 }
 
 struct Lat {
@@ -243,11 +247,11 @@ struct Batch {
             HIP_CHECK(hipStreamWaitEvent(ms(), lead->ev[l], 0));
         }
     }
-    void gather(hipStream_t s) {
-        k_gather_counts<<<1, 64, 0, s>>>((int)lats.size(), (const int *const *)lead->table.p, (int *)lead->nact.p);
+    void status(int mode, int k) {  // on the batch stream, after the branches
+        k_bat_status<<<(unsigned)lats.size(), 64, 0, ms()>>>((const LatState *)lead->table.p, mode, k, (int *)lead->nact.p);
         HIP_CHECK(hipGetLastError());
     }
-    // total systems still active, read from the gathered counts (blocking)
+    // total systems still active (blocking)
     int poll() {
         HIP_CHECK(hipMemcpyAsync(lead->host_nact, lead->nact.p, lats.size() * sizeof(int), hipMemcpyDeviceToHost,
                                  ms()));
@@ -301,7 +305,7 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
         std::copy(start[l].begin(), start[l].begin() + R, pin_ints(L));
         std::copy(target[l].begin(), target[l].begin() + R, pin_doubles(L));
         HIP_CHECK(hipMemcpyAsync(L.act(), pin_ints(L), R * sizeof(int), hipMemcpyHostToDevice, ms));
-        HIP_CHECK(hipMemsetAsync(L.cnt(), 0, (4 * R + 1) * sizeof(int), ms));
+        HIP_CHECK(hipMemsetAsync(L.cnt(), 0, 4 * R * sizeof(int), ms));
         scatter_sys(L, S_TGT, ms);
         for (const unsigned long long v :
              {L.w->id, (unsigned long long)pr[l], (unsigned long long)R, (unsigned long long)(uintptr_t)x[l],
@@ -331,10 +335,8 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
                         L.spec(L.act()));
         blas(l).lincomb(pr[l], pr[l], pr[l], 1, L.w->P.p, nullptr, 1.0, b[l], 0.0, nullptr, L.sp(S_RED + 4),
                         scale(l), ms, L.spec(L.act()));
-        k_bat_status<<<1, 64, 0, ms>>>(R, 1, 0, L.act(), L.cyc(), L.cnt(), L.scal());
-        HIP_CHECK(hipGetLastError());
     }
-    B.gather(ms);
+    B.status(1, 0);
     int active = B.poll();  // also completes the uploads above from the pinned staging
     // the launch-shape tuner cannot time candidates inside a capture: one eager operator
     // application per lattice (on the residual, into basis slot 0, which iteration 0 overwrites)
@@ -354,8 +356,6 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
         // the residual of iteration k is its direction, slot k of P
         Bl.gcr_dots(pr[l], 1, Q, k, qk, P + k * kb, sc, s, L.spec(L.act()));
         Bl.gcr_step(pr[l], 1, Q, k, qk, P + k * kb, P + (k + 1) * kb, sc, s, L.spec(L.act()));
-        k_bat_status<<<1, 64, 0, s>>>(L.nrhs, 0, k, L.act(), L.cyc(), L.cnt(), L.scal());
-        HIP_CHECK(hipGetLastError());
     };
     auto cycle_start = [&](int l, hipStream_t s) {
         Lat &L = B.lats[l];
@@ -373,8 +373,6 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
         schur_apply(L.c, L.w->Q.p, x[l], 0, pr[l], s, L.nrhs, L.cyc());
         blas(l).lincomb(pr[l], pr[l], pr[l], 1, L.w->P.p, nullptr, 1.0, b[l], -1.0, L.w->Q.p, L.sp(S_RED + 4),
                         scale(l), s, L.spec(L.cyc()));
-        k_bat_status<<<1, 64, 0, s>>>(L.nrhs, 2, 0, L.act(), L.cyc(), L.cnt(), L.scal());
-        HIP_CHECK(hipGetLastError());
     };
     int it = 0;
     while (active > 0 && it < max_iter) {
@@ -385,7 +383,7 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
         for (int k = 0; k < m; ++k) {
             B.run_graph(use_graph, lw.it_graphs[k], [&](bool cap) {
                 B.branches(cap, [&](int l, hipStream_t s) { iteration(l, k, s); });
-                B.gather(ms);
+                B.status(0, k);
             });
             ++it;
             kmax = k + 1;
@@ -394,7 +392,7 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
         }
         B.run_graph(use_graph, lw.end_graphs[kmax], [&](bool cap) {
             B.branches(cap, [&](int l, hipStream_t s) { cycle_end(l, kmax, s); });
-            B.gather(ms);
+            B.status(2, 0);
         });
         active = B.poll();
     }
@@ -402,11 +400,11 @@ std::vector<BOut> gcr_batched(Batch &B, const std::vector<dirac_prec> &pr, const
     std::vector<BOut> out(nl);
     std::vector<std::vector<int>> hc(nl);
     for (int l = 0; l < nl; ++l)
-        HIP_CHECK(hipMemcpyAsync(pin_ints(B.lats[l]), B.lats[l].cnt(), (4 * B.lats[l].nrhs + 1) * sizeof(int),
+        HIP_CHECK(hipMemcpyAsync(pin_ints(B.lats[l]), B.lats[l].cnt(), 4 * B.lats[l].nrhs * sizeof(int),
                                  hipMemcpyDeviceToHost, ms));
     HIP_CHECK(hipStreamSynchronize(ms));
     ++B.syncs;
-    for (int l = 0; l < nl; ++l) hc[l].assign(pin_ints(B.lats[l]), pin_ints(B.lats[l]) + 4 * B.lats[l].nrhs + 1);
+    for (int l = 0; l < nl; ++l) hc[l].assign(pin_ints(B.lats[l]), pin_ints(B.lats[l]) + 4 * B.lats[l].nrhs);
     for (int l = 0; l < nl; ++l) {
         const int R = B.lats[l].nrhs;
         BOut &o = out[l];
@@ -435,7 +433,7 @@ void ensure_bwork(dirac_ctx *c, int m, int nrhs) {
     w.b.alloc(hb);
     w.act.alloc(nrhs * sizeof(int));
     w.cyc.alloc(nrhs * sizeof(int));
-    w.cnt.alloc((4 * nrhs + 1) * sizeof(int));
+    w.cnt.alloc(4 * nrhs * sizeof(int));
     w.stage.alloc(kPinDoubles * sizeof(double));
     if (!w.pin) HIP_CHECK(hipHostMalloc((void **)&w.pin, kPinBytes, hipHostMallocDefault));
     for (auto &d : w.h64) d.alloc(hb);
@@ -458,11 +456,15 @@ void ensure_lead(BWork &w, const std::vector<Lat> &lats) {
         HIP_CHECK(hipHostMalloc((void **)&w.host_nact, 64 * sizeof(int), hipHostMallocDefault));
         w.nlat_cap = 64;
     }
-    w.table.alloc(64 * sizeof(int *));
+    static_assert(64 * sizeof(LatState) <= kPinBytes, "the table fits the pinned staging");
+    w.table.alloc(64 * sizeof(LatState));
     w.nact.alloc(64 * sizeof(int));
-    const int **src = (const int **)w.pin;  // the leader's pinned staging (64 pointers fit)
-    for (int l = 0; l < nl; ++l) src[l] = (const int *)lats[l].w->cnt.p + 4 * lats[l].nrhs;
-    HIP_CHECK(hipMemcpyAsync(w.table.p, src, nl * sizeof(int *), hipMemcpyHostToDevice, w.ms));
+    LatState *src = (LatState *)w.pin;  // the leader's pinned staging
+    for (int l = 0; l < nl; ++l) {
+        Lat L = lats[l];
+        src[l] = LatState{L.nrhs, L.act(), L.cyc(), L.cnt(), L.scal()};
+    }
+    HIP_CHECK(hipMemcpyAsync(w.table.p, src, nl * sizeof(LatState), hipMemcpyHostToDevice, w.ms));
     HIP_CHECK(hipStreamSynchronize(w.ms));  // the staging is reused
 }
 

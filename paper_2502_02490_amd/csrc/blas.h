@@ -39,11 +39,15 @@ struct Blas {
     // Step k of a GCR cycle (basis vectors Q_0 .. Q_{k-1}, q = A p_k): the scalars beta_k and gamma_k and an estimate of
     // alpha_k, then q <- the new basis vector, rnew = r - alpha q (rnew may be r), |rnew|^2 in S_RED + 4, and
     // S_RED + 6 = 1 when nothing was left of q (then rnew = r, and the cycle should end), else 0; with ctl (one
-    // system) the iteration control of the cycle is advanced against `target`.
+    // system) the iteration control of the cycle is advanced against `target`.  defer: the correction of alpha is
+    // left to the caller, who calls gcr_correct where S_RED + 7 is not 0 (with ctl: ctl[3] = 1, ctl[0] = 0 until then).
     void gcr_dots(dirac_prec pr, int nh, const void *Q, int k, const void *q, const void *r, double scale, hipStream_t s,
                   const BatchSpec &bs = BatchSpec());
     void gcr_step(dirac_prec pr, int nh, const void *Q, int k, void *q, const void *r, void *rnew, double scale,
-                  hipStream_t s, const BatchSpec &bs = BatchSpec(), int *ctl = nullptr, double target = 0.0);
+                  hipStream_t s, const BatchSpec &bs = BatchSpec(), int *ctl = nullptr, double target = 0.0,
+                  bool defer = false);
+    void gcr_correct(dirac_prec pr, int nh, const void *q, void *rnew, double scale, hipStream_t s,
+                     const BatchSpec &bs = BatchSpec(), int *ctl = nullptr, double target = 0.0);
     // the coefficients S_C of x += sum_j c_j p_j after a cycle of n steps (counts[sys] when given), zero up to kmax
     void gcr_backsub(const int *counts, int n, int kmax, hipStream_t s, const BatchSpec &bs = BatchSpec());
     // x += xscale sum_j coef_j P_j, j < k (xscale_r = xscales[r * sstride] when given; system r sums
@@ -75,6 +79,7 @@ struct SolverWork {
     dirac_prec pr = DIRAC_F64;
     double *pin = nullptr;  // pinned host memory for the values a solve waits for (8 doubles)
     long syncs = 0;  // host waits on the device (value reads) since the current solve began
+    bool correct = false;  // a step of the current solve needed its correction: it follows every step
 };
 
 }  // namespace dl

@@ -152,8 +152,9 @@ __global__ __launch_bounds__(kRed) void k_reduce(int nblk, int nc, const double 
 //   k_gcr_step: Q_k = (q - sum_j beta_j Q_j) / gamma over q (k = 0: Q_0 = q, gamma = 1), r_new = r - a Q_k, and |Q_k|^2,
 //     <Q_k, r>, |r_new|^2 of the vectors as stored; then alpha = <Q_k, r> / |Q_k|^2 is known;
 //   k_gcr_correct: r_new -= (alpha - a) Q_k and |r_new|^2 anew, where |alpha - a|^2 |Q_k|^2 (what the estimate adds to the
-//     least |r_new|^2) is above `slack` |r_new|^2, 1e-10 or what rounding the stored r adds; else it returns at once
-//     (3 to 5 us), and alpha = a counts as taken.
+//     least |r_new|^2) is above `slack` |r_new|^2, 1e-10 or what rounding the stored r adds; else alpha = a counts as
+//     taken.  It follows every step of a batch, where it returns at once (3 to 5 us); a single solve leaves it out
+//     until a step needs it (`defer`), which costs up to three iterations queued for nothing, once per solve.
 // So the beta, the step and the solution's coefficients rest on sums over the stored vectors: the estimate
 // cancels where q nearly lies in the span of the Q_j, and with alpha and gamma from it alone directions with
 // |q_perp| / |q| below 1e-7 in FP64 (3e-5 in FP32) had to be left out, and solves that need one did not
@@ -436,7 +437,7 @@ template <typename S, bool WIDE, int BS>
 __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename St<S>::vec *Q, int k,
                                                  typename St<S>::vec *q, const typename St<S>::vec *rv,
                                                  typename St<S>::vec *rnew, double *part, double scale, double slack,
-                                                 double *scal, int *ctl, double target) {
+                                                 double *scal, int *ctl, double target, int defer) {
     __shared__ double sub[WIDE ? (BS / 64) : 1][WIDE ? 24 : 1][64];
     const int sys = (int)blockIdx.x / nblk, blk = (int)blockIdx.x - sys * nblk;
     if (B.active && !B.active[sys]) return;
@@ -556,7 +557,12 @@ __global__ __launch_bounds__(BS) void k_gcr_step(Bat B, int nblk, const typename
     scal[S_RED + 4] = rn2;
     scal[S_RED + 6] = empty ? 1.0 : 0.0;
     scal[S_RED + 7] = correct ? 1.0 : 0.0;
-    if (ctl && !correct) gcr_control(ctl, rn2, target, empty);
+    if (ctl && !correct) {
+        gcr_control(ctl, rn2, target, empty);
+    } else if (ctl && defer) {  // the cycle waits for the correction
+        ctl[3] = 1;
+        ctl[0] = 0;
+    }
 }
 
 // The vectors of a system are taken as they lie, 16 bytes a thread, kU loads of each in flight.
@@ -613,7 +619,11 @@ __global__ __launch_bounds__(kGcr) void k_gcr_correct(Bat B, int nblk, const typ
     if (threadIdx.x) return;
     const double rn2 = scale * v[0];
     scal[S_RED + 4] = rn2;
-    if (ctl) gcr_control(ctl, rn2, target, false);
+    if (ctl) {
+        ctl[3] = 0;
+        ctl[0] = 1;
+        gcr_control(ctl, rn2, target, false);
+    }
 }
 
 // x += xscale_r sum_j coef_j P_j (x and P may have different precisions)
@@ -828,26 +838,34 @@ void Blas::gcr_backsub(const int *counts, int n, int kmax, hipStream_t s, const 
 }
 
 void Blas::gcr_step(dirac_prec pr, int nh, const void *Q, int k, void *q, const void *r, void *rnew, double scale,
-                    hipStream_t s, const BatchSpec &bs, int *ctl, double target) {
+                    hipStream_t s, const BatchSpec &bs, int *ctl, double target, bool defer) {
     const Bat b = make_bat(c, nh, bs);
     const int nblk = gcr_blocks(b);
-    const int64_t nv = (int64_t)(b.n / b.vh) * (24 * real_size(pr) / 16) * padded_sites(b.vh);  // 16-byte vectors
-    // the correction, rarely with work: about one work-group per compute unit over all systems, so that the others'
-    // kernels do not hold it up for long (3,072 of them took 90 us to return among the lattices of a batch)
-    const int nr = (int)std::min<int64_t>((nv + kGcr - 1) / kGcr, std::max(kGcrBlocks / 2 / b.nrhs, 16));
 #define FNW(S, WIDE, BS)                                                                                              \
     k_gcr_step<S, WIDE, BS><<<nblk * b.nrhs, BS, 0, s>>>(b, nblk, (const typename St<S>::vec *)Q, k,                 \
                                                          (typename St<S>::vec *)q, (const typename St<S>::vec *)r,   \
-                                                         (typename St<S>::vec *)rnew, (double *)part.p, scale, gcr_slack(pr), (double *)scal.p, \
-                                                         ctl, target);
-#define FN(S)                                                                                                         \
-    if (gcr_wide(b)) { FNW(S, true, kGcr) } else if (gcr_block_size(b) == kGcr) { FNW(S, false, kGcr) } else { FNW(S, false, kGcr / 2) } \
-    k_gcr_correct<S><<<nr * b.nrhs, kGcr, 0, s>>>(b, nr, (const typename St<S>::vec *)q, (typename St<S>::vec *)rnew, \
-                                                  (double *)part.p, scale, (double *)scal.p,     \
-                                                  ctl, target);
+                                                         (typename St<S>::vec *)rnew, (double *)part.p, scale,       \
+                                                         gcr_slack(pr), (double *)scal.p, ctl, target, defer ? 1 : 0);
+#define FN(S) if (gcr_wide(b)) { FNW(S, true, kGcr) } else if (gcr_block_size(b) == kGcr) { FNW(S, false, kGcr) } else { FNW(S, false, kGcr / 2) }
     DISPATCH_PREC(pr, FN)
 #undef FN
 #undef FNW
+    HIP_CHECK(hipGetLastError());
+    if (!defer) gcr_correct(pr, nh, q, rnew, scale, s, bs, ctl, target);
+}
+
+void Blas::gcr_correct(dirac_prec pr, int nh, const void *q, void *rnew, double scale, hipStream_t s,
+                       const BatchSpec &bs, int *ctl, double target) {
+    const Bat b = make_bat(c, nh, bs);
+    const int64_t nv = (int64_t)(b.n / b.vh) * (24 * real_size(pr) / 16) * padded_sites(b.vh);  // 16-byte vectors
+    // rarely with work: about one work-group per compute unit over all systems, so that the others' kernels do not
+    // hold it up for long (3,072 of them took 90 us to return among the lattices of a batch)
+    const int nr = (int)std::min<int64_t>((nv + kGcr - 1) / kGcr, std::max(kGcrBlocks / 2 / b.nrhs, 16));
+#define FN(S)                                                                                                         \
+    k_gcr_correct<S><<<nr * b.nrhs, kGcr, 0, s>>>(b, nr, (const typename St<S>::vec *)q, (typename St<S>::vec *)rnew, \
+                                                  (double *)part.p, scale, (double *)scal.p, ctl, target);
+    DISPATCH_PREC(pr, FN)
+#undef FN
     HIP_CHECK(hipGetLastError());
 }
 

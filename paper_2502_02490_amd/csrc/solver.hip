@@ -39,7 +39,8 @@ using Precond = std::function<void(void *p, const void *r)>;
 double *sc_ptr(SolverWork &w, int slot) { return (double *)w.blas.scal.p + slot; }
 
 // Device-side iteration control of one GCR cycle without a preconditioner: ctl[0] = 1 while the
-// system is active, ctl[1] = iterations done in the cycle, ctl[2] = 1 after a non-finite residual.
+// system is active, ctl[1] = iterations done in the cycle, ctl[2] = 1 after a non-finite residual, ctl[3] = 1 while
+// step ctl[1] waits for its correction.
 // The last work-group of each iteration compares the updated residual norm with the target and clears
 // ctl[0] (also after an empty step); every kernel of a later iteration of the cycle takes ctl as its active mask and does
 // nothing, so the host only reads ctl every kPoll iterations and at the end of the cycle.
@@ -50,6 +51,7 @@ __global__ void k_gcr_ctl_start(int *ctl) {
         ctl[0] = 1;
         ctl[1] = 0;
         ctl[2] = 0;
+        ctl[3] = 0;
     }
 }
 
@@ -148,15 +150,22 @@ GcrOut gcr(dirac_ctx *c, SolverWork &w, dirac_prec pr, void *x, const void *b, b
             const int kmax = std::min(m, max_iter - out.iters);
             int *h = reinterpret_cast<int *>(w.pin);
             h[1] = h[2] = 0;
-            for (int k = 0; k < kmax; ++k) {
+            for (int k = 0; k < kmax;) {
                 char *qk = Q + k * hb;
                 schur_apply(c, qk, P + k * hb, 0, pr, s, 1, ctl);
                 B.gcr_dots(pr, nh, Q, k, qk, P + k * hb, scale, s, bs);
-                B.gcr_step(pr, nh, Q, k, qk, P + k * hb, P + (k + 1) * hb, scale, s, bs, ctl, target);
-                if ((k + 1) % kPoll == 0 || k + 1 == kmax) {
-                    read_pinned(w, ctl, 3 * sizeof(int), s);
-                    if (!h[0]) break;
+                B.gcr_step(pr, nh, Q, k, qk, P + k * hb, P + (k + 1) * hb, scale, s, bs, ctl, target, !w.correct);
+                ++k;
+                if (k % kPoll != 0 && k != kmax) continue;
+                read_pinned(w, ctl, 4 * sizeof(int), s);
+                if (h[3]) {  // the iterations queued after step h[1] did nothing: go on from there
+                    k = h[1];
+                    B.gcr_correct(pr, nh, Q + k * hb, P + (k + 1) * hb, scale, s, BatchSpec(), ctl, target);
+                    w.correct = true;
+                    if (++k < kmax) continue;
+                    read_pinned(w, ctl, 4 * sizeof(int), s);
                 }
+                if (!h[0]) break;
             }
             n = h[1];
             out.iters += n;
@@ -171,10 +180,14 @@ GcrOut gcr(dirac_ctx *c, SolverWork &w, dirac_prec pr, void *x, const void *b, b
                 // the next direction is r itself (slot k + 1) or M(r)
                 void *rk = M ? r : P + k * hb, *rn = M ? r : P + (k + 1) * hb;
                 B.gcr_dots(pr, nh, Q, k, qk, rk, scale, s);
-                B.gcr_step(pr, nh, Q, k, qk, rk, rn, scale, s);
-                read_pinned(w, sc_ptr(w, S_RED + 4), 3 * sizeof(double), s);
-                rn2 = w.pin[0];
+                B.gcr_step(pr, nh, Q, k, qk, rk, rn, scale, s, BatchSpec(), nullptr, 0.0, true);
+                read_pinned(w, sc_ptr(w, S_RED + 4), 4 * sizeof(double), s);
                 const bool empty = w.pin[2] != 0.0;
+                if (w.pin[3] != 0.0) {
+                    B.gcr_correct(pr, nh, qk, rn, scale, s);
+                    read_pinned(w, sc_ptr(w, S_RED + 4), sizeof(double), s);
+                }
+                rn2 = w.pin[0];
                 ++out.iters;
                 n = k + 1;
                 if (!std::isfinite(rn2)) {

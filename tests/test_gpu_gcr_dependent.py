@@ -85,3 +85,19 @@ def test_unreachable_tolerance_is_reported(prec):
         assert err.value.status == P._lib.ENOCONV
         info = D.solve(x, b, tol=1e-18, restart=24, max_iter=200, raise_on_noconv=False, **kw)
         assert info.true_rel_res < 1e-13 and info.iters <= 200
+
+
+@pytest.mark.parametrize("restart,max_iter", [(2, 40), (3, 40), (8, 2)])
+def test_correction_at_the_end_of_a_cycle(restart, max_iter):
+    """The step that needs its correction is the last or the last but one of a cycle, or the last that max_iter allows."""
+    need_gpu()
+    dims, eta, tol = DIMS[0], 1e-8, 1e-6
+    flush(f"[gpu] correction at the end of a cycle, restart {restart}, max_iter {max_iter}")
+    b = to_dev(two_waves(dims, eta))
+    with operator(dims) as D:
+        x = torch.zeros_like(b)
+        info = D.solve(x, b, method=P.GCR, tol=tol, restart=restart, max_iter=max_iter)
+        assert info.true_rel_res < tol and info.iters == 2
+        xs = torch.zeros((1,) + b.shape, dtype=b.dtype, device="cuda")
+        inf = P.solve_batched([D], [xs], [b[None].contiguous()], 1, method=P.GCR, tol=tol, restart=restart, max_iter=max_iter)
+        assert inf[0][0].true_rel_res < tol and inf[0][0].iters == 2
